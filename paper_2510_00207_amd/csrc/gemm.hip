@@ -8,12 +8,13 @@
 //   KSUM  C_e[Mdim x N]  = sum over rows r of e: A[r][.]^T B[r][.]  (wgrad):
 //         the reduction length K = counts[e] is ragged.
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16, 256 threads (2 x 2 waves), block tile
-// BM x BN x 64, each wave 32*FM x 32*FN. Both operands are staged in LDS
-// K-contiguous ([row][64] bf16 = 128 B per row) with the 16-byte chunk index
-// XOR-swizzled by (row & 7), double-buffered with register prefetch of the
-// next k-tile. Operands whose global layout is K-contiguous are copied with
-// 16-byte loads; operands contiguous along M or N are loaded as KT x 8
+// bf16 path: v_mfma_f32_32x32x16_bf16 over 256 x 256 tiles (gemm_wide_kernel) or,
+// where those are few, 256 x 128 tiles (gemm_narrow_kernel), the operands
+// streamed global -> LDS; a register-staged kernel takes row-mode reductions
+// that are no multiple of 32. That one: block tile BM x BN x 64, both operands
+// staged in LDS K-contiguous ([row][64] bf16 = 128 B per row) with the 16-byte
+// chunk index XOR-swizzled by (row & 7), double-buffered with register prefetch
+// of the next k-tile; operands contiguous along M or N are loaded as KT x 8
 // blocks and transposed in registers before the LDS write.
 // fp32 path (correctness workloads): a plain LDS-tiled FMA kernel with the
 // same modes and epilogues.
@@ -281,9 +282,10 @@ __device__ __forceinline__ void shared_block_tile(int P, int nrows, int ncols, i
 
 // Epilogue shared by the bf16 kernels: the accumulators of wave (wm, wn)
 // of the tile (each WM x WN, acc[i][j][4*g + q] = C[row wm*WM + i*32 + lane%32]
-// [col wn*WN + j*32 + 8*g + 4*(lane/32) + q]) to global memory, staged
+// [col wn*WN + j*32 + 8*g + 4*(lane/32) + q]; HALVES: row (i/2)*128 + wm*64 +
+// (i%2)*32 + .., col j*128 + wn*32 + ..) to global memory, staged
 // through LDS (smem: SMEM free bytes, at least (NT/64)*64*WN floats).
-template <int MODE, int EPI, int BM, int BN, int NT, int SMEM, int WM, int WN>
+template <int MODE, int EPI, int BM, int BN, int NT, int SMEM, int WM, int WN, bool HALVES = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&acc)[WM / 32][WN / 32],
                                               char* smem, int e, int mt, int n0, int row0,
                                               int rows_e, int cnt_e, int wm, int wn) {
@@ -306,6 +308,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
     bf16_t* C1 = static_cast<bf16_t*>(p.C1);
     const bf16_t* aux = static_cast<const bf16_t*>(p.aux);
     auto sidx = [&](int r, int c4) { return r * WN + ((c4 ^ (r & (SCH - 1))) << 2); };
+    // tile row of row rr of 64-row half hf, and tile column of the wave's column c
+    auto tile_row = [&](int hf, int rr) { return HALVES ? hf * 128 + wm * 64 + rr : wm * WM + hf * 64 + rr; };
+    auto tile_col = [&](int c) { return HALVES ? (c >> 5) * 128 + wn * 32 + (c & 31) : wn * WN + c; };
     // forward biases: a lane's items all lie in one 8-column group (the item
     // index is it * 64 + lane and 64 is a multiple of the groups per row), so
     // its 8 (dual: 2 x 8) bias values are loaded once, before any store (a
@@ -326,7 +331,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
         } else {
           constexpr int G8 = WN / 8;
           static_assert(64 % G8 == 0, "one column group per lane");
-          n = n0 + wn * WN + (lane % G8) * 8;
+          n = n0 + tile_col((lane % G8) * 8);
         }
         if (n < p.N) {
           if (p.bias0 != nullptr) load8(p.bias0 + (long)e * p.bias_estride + n, bias0);
@@ -348,8 +353,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
         for (int it = 0; it < APER; ++it) {
           const int item = it * 64 + lane;
           const int rr = item / AG8, c8 = item % AG8;
-          const int ti = wm * WM + hf * 64 + rr;
-          const int n = n0 + wn * WN + c8 * 8;
+          const int ti = tile_row(hf, rr);
+          const int n = n0 + tile_col(c8 * 8);
           const bool ok = mt * BM + ti < rows_e && n < p.N;
           const long off = ok ? (long)(row0 + ti) * p.ldaux + n : 0;  // (clamped: every load issued)
           hr[it] = raw8_load(aux + off);
@@ -385,7 +390,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
           const int item = it * 64 + lane;
           const int rr = item / G8, c8 = item % G8;  // c8: 8-group among the distinct columns
           const int jp = c8 >> 2, cin = (c8 & 3) * 8;  // pair and offset inside its 32
-          const int ti = wm * WM + hf * 64 + rr;
+          const int ti = tile_row(hf, rr);
           const int li = mt * BM + ti;
           const int n = n0 + wn * (WN / 2) + jp * 32 + cin;
           if (li >= rows_e || n >= p.N) continue;
@@ -423,8 +428,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
         auto dst_of = [&](int it, bool& ok) {
           const int item = it * 64 + lane;
           const int rr = item / G4, c4 = item % G4;
-          const int m = mt * BM + wm * WM + hf * 64 + rr;
-          const int n = n0 + wn * WN + c4 * 4;
+          const int m = mt * BM + tile_row(hf, rr);
+          const int n = n0 + tile_col(c4 * 4);
           ok = m < p.Mdim && n < p.N;  // N and nsplit are multiples of 8
           return (n < p.nsplit) ? D0 + (long)e * p.c_estride + (long)m * p.ldc + n
                                 : D1 + (long)e * p.c_estride + (long)m * p.ldc + (n - p.nsplit);
@@ -466,9 +471,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
         for (int it = 0; it < PER; ++it) {
           const int item = it * 64 + lane;
           const int rr = item / G8, c8 = item % G8;
-          const int ti = wm * WM + hf * 64 + rr;
+          const int ti = tile_row(hf, rr);
           const int li = mt * BM + ti;
-          const int n = n0 + wn * WN + c8 * 8;
+          const int n = n0 + tile_col(c8 * 8);
           if (li >= rows_e || n >= p.N) continue;
           const bool data = li < cnt_e;
           float v[8];
@@ -683,12 +688,12 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmParams p) {
 // ---------------------------------------------------------------------------
 // bf16 kernel with direct-to-LDS operand streaming
 // ---------------------------------------------------------------------------
-// 256 x 256 block tile, 512 threads (2 x 4 waves of 128 x 64), BK = 32, a
-// ring of 4 LDS stages (32 KB each: A then B). Operands go global -> LDS with
-// bounds-checked buffer_load_dwordx4 ... lds (no staging registers; reads
-// past a buffer's range return zeros, which masks ragged expert rows and the
-// ragged reduction of the weight gradients). Each wave load fills one 1 KB
-// block of LDS in lane order; the source chunk of each lane is chosen so the
+// gemm_narrow_kernel: 256 x 128 block tile, BK = 32, a ring of 3 LDS stages (24
+// KB each: A then B). Operands go global -> LDS with bounds-checked
+// buffer_load_dwordx4 ... lds (no staging registers; reads past a buffer's range
+// return zeros, which masks ragged expert rows and the ragged reduction of the
+// weight gradients). Each wave load fills one 1 KB block of LDS in lane order;
+// the source chunk of each lane is chosen so the
 // block holds the swizzled layout:
 //   K-contiguous operand: [256 rows][32 k] (64 B rows), chunk c of row r at
 //     physical chunk c ^ ((r / 4) % 4); fragments via ds_read_b128.
@@ -830,6 +835,14 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+}
+
 __device__ __forceinline__ int kc_off(int row, int chunk) {
   return row * 64 + (((chunk ^ (row >> 2)) & 3) << 4);
 }
@@ -858,23 +871,19 @@ __device__ __forceinline__ bf16x8 frag_mnc(const char* region, int cb, int kk, i
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW>
-__global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmParams p) {
-  // Waves of 128 x 64 accumulators, two along M:
-  //   wide:   256 x 256 tiles, 8 waves, 4 stages of the k-tile ring (128 KB
-  //           of LDS, one block per CU);
-  //   narrow: 256 x 128 tiles, 4 waves, 3 stages (72 KB, up to two blocks per
-  //           CU), for launches whose wide tiles would leave CUs idle.
-  constexpr int BM = 256, BN = NARROW ? 128 : 256, NT = NARROW ? 256 : 512;
-  constexpr int WGM = 2, WGN = NARROW ? 2 : 4;
-  constexpr int NW = NT / 64;          // waves
-  constexpr int NST = NARROW ? 3 : 4;  // stages of the k-tile ring
+template <int MODE, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(GemmParams p) {
+  // 4 waves of 128 x 64 accumulators, two along M and two along N, 3 stages of
+  // the k-tile ring: 72 KB of LDS, two blocks per CU
+  constexpr int BM = 256, BN = 128, NT = 256;
+  constexpr int WGM = 2, WGN = 2;
+  constexpr int NW = NT / 64;  // waves
+  constexpr int NST = 3;       // stages of the k-tile ring
   constexpr int A_BYTES = BM * DBK * 2, STB = A_BYTES + BN * DBK * 2;  // bytes per stage
   constexpr int BPA = (BM / 16) / NW, BPB = (BN / 16) / NW;  // 1 KB blocks per wave per stage
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
-  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
-  static_assert(!DUAL || !NARROW, "the dual forward pairs 128-column W1 and W3 panels");
-  constexpr int PWB = DUAL ? 128 : BN;  // B panel width (M/N-contiguous B)
+  static_assert(EPI != EPI_SWIGLU_FWD, "the dual forward pairs 128-column W1 and W3 panels");
+  constexpr int PWB = BN;  // B panel width (M/N-contiguous B)
   // the k-tile ring, reused by the epilogue's staging (64 fp32 rows per wave)
   constexpr int SMEM = NST * STB > NW * 64 * WN * 4 ? NST * STB : NW * 64 * WN * 4;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -908,8 +917,7 @@ __global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmPar
     row0 = __builtin_amdgcn_readlane(seg_o, 0);
     cnt_e = clip_rows(row0, __builtin_amdgcn_readlane(seg_c, 0), p.rows_cap);
   }
-  constexpr int NCOLS = DUAL ? BN / 2 : BN;
-  const int n0 = nt * NCOLS;
+  const int n0 = nt * BN;
   const int Kred = (MODE == MODE_ROWS) ? p.K : cnt_e;
   // a padding-only tile (padded layout) has nothing to reduce: zeros
   int nk = (MODE == MODE_ROWS && cnt_e <= mt * BM) ? 0 : (Kred + DBK - 1) / DBK;
@@ -960,17 +968,10 @@ __global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmPar
     b_kstep = DBK * 2;
   } else if constexpr (MODE == MODE_ROWS) {  // weights [K][N] per expert
     const long span = (long)p.K * p.ldb;
-    if constexpr (DUAL) {  // panel 0: W1 columns n0.., panel 1: W3 columns n0..
-      rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
-      rb1 = make_rsrc(B1 + (long)e * p.b_estride + n0, (span - n0) * 2);
+    rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
+    rb1 = rb0;
 #pragma unroll
-      for (int i = 0; i < BPB; ++i) boff[i] = mnc_off((wave + NW * i) & 7, 128, p.ldb);
-    } else {
-      rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
-      rb1 = rb0;
-#pragma unroll
-      for (int i = 0; i < BPB; ++i) boff[i] = mnc_off(wave + NW * i, BN, p.ldb);
-    }
+    for (int i = 0; i < BPB; ++i) boff[i] = mnc_off(wave + NW * i, BN, p.ldb);
     b_kstep = DBK * p.ldb * 2;
   } else {  // KSUM: element (r, n) at B + (row0 + r) * ldb + n
     rb0 = make_rsrc(B0 + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
@@ -1014,9 +1015,7 @@ __global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmPar
         dma16(second ? rb1 : rb0, sb + (wave_s + NW * i) * 1024, boff[i] + kb);
       } else {
         const unsigned kb = (unsigned)kt * (unsigned)b_kstep;
-        // blocks 8..15 hold the W3 panel
-        const int blk = wave_s + NW * i;
-        dma16((DUAL && blk >= 8) ? rb1 : rb0, sb + blk * 1024, boff[i] + kb);
+        dma16(rb0, sb + (wave_s + NW * i) * 1024, boff[i] + kb);
       }
     }
   };
@@ -1083,8 +1082,6 @@ __global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmPar
         for (int j = 0; j < FN; ++j) {
           if constexpr (B_KC)
             bfr[set][j] = frag_kc(sb, wn * WN + j * 32 + (lane & 31), kk, lane);
-          else if constexpr (DUAL)  // pairs (h1, h3) of 32 columns: W1 panel, W3 panel
-            bfr[set][j] = frag_mnc<PWB>(sb, (j & 1) * 128 + wn * (WN / 2) + (j >> 1) * 32, kk, lane);
           else
             bfr[set][j] = frag_mnc<PWB>(sb, wn * WN + j * 32, kk, lane);
         }
@@ -1217,6 +1214,308 @@ __global__ __launch_bounds__(NARROW ? 256 : 512, 2) void gemm_dma_kernel(GemmPar
   __syncthreads();  // all LDS reads done before the epilogue reuses the stages
   gemm_epilogue<MODE, EPI, BM, BN, NT, SMEM, WM, WN>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm,
                                                      wn);
+}
+
+// ---------------------------------------------------------------------------
+// bf16 kernel, 256 x 256 tiles: two wave groups taking turns on the matrix pipes
+// ---------------------------------------------------------------------------
+// 8 waves, two along M (wm) and four along N (wn), one of each wm on every SIMD.
+// A k-tile is 64 deep and held as two 128-row A halves and two 128-column B
+// halves of 16 KB; a wave multiplies 64 rows of each A half by 32 columns of
+// each B half, one (A half, B half) pair a phase: 8 v_mfma_f32_32x32x16_bf16, 256
+// cycles of a matrix pipe. Phases of tile t: (A0, BX), (A0, BY), (A1, BY), (A1,
+// BX), X = t % 2, Y = 1 - X, so that the half a phase starts to use was read
+// from LDS one phase before and its registers were free by then.
+//
+// A phase is a memory part (LDS reads of the next phase's half, two LDS-DMA
+// loads of a half of tile t + 2, the wait for the half that the next phase
+// reads), a barrier, the MFMAs, a barrier. The waves of wm = 1 run one part
+// behind those of wm = 0, so on every SIMD one wave's MFMAs run beside the
+// other's memory part, and no wave waits for its own reads or loads: the reads
+// have a whole part to arrive, the loads six phases (10 of a wave's loads, 80
+// KB a block, stay in flight). A half's LDS is refilled two phases after its
+// read, when the barriers between have ordered every wave's reads before it.
+//
+// What it measured, and why 64 deep: 32-deep tiles (a four-stage ring, one
+// barrier a tile, reads interleaved with the MFMAs of the same wave) fetched the
+// K-contiguous operands in 64-byte pieces of 128-byte lines and kept the pipes
+// busy 0.56-0.72 of the cycles; here it is 0.67-0.81 (SwiGLU experts of 16384
+// rows at M = 4096, H = 14336: W1|W3 forward 6.68 -> 5.99 ms, W2 forward 3.21 ->
+// 2.92, their dgrads 3.82 -> 3.24 and 7.08 -> 6.03, both weight gradients 9.33
+// -> 9.04). Power is what is left: the clock falls to 1.54-1.6 GHz as the pipes
+// get busier, and waiting for four more loads, issuing the loads first, or
+// raising the MFMAs' wave priority changed nothing (0.0 to 0.5% slower).
+constexpr int WBK = 64;           // k depth of a tile
+constexpr int kHalf = 128 * WBK * 2;  // bytes of a half tile: 128 rows (or columns) x 64 k
+
+// Fragments of a half tile (32 rows or columns from a wave's first one).
+// K-contiguous: [128 rows][64 k], 128-byte rows, 16-byte chunk c of row r at
+// c ^ ((r / 2) % 8); M/N-contiguous: [64 k][128 columns], 256-byte rows, chunk
+// m of k-row k at m ^ (4 (k % 4)), two transposing reads a fragment. A lane's
+// address is one base register, an XOR with the k step (K-contiguous) or the
+// 32-column block (M/N-contiguous), and an immediate offset.
+__device__ __forceinline__ int half_base(bool kc, int r0, int lane) {
+  if (kc) return lds_off(r0 + (lane & 31), lane >> 5);
+  const int G = lane >> 4, sl = lane & 15;
+  const int col = r0 + (G & 1) * 16 + 4 * (sl & 3), kr = (G >> 1) * 8 + (sl >> 2);
+  return kr * 256 + (((col >> 3) ^ ((kr & 3) << 2)) << 4) + ((col & 7) << 1);
+}
+// fragment of 32-row block i (rows r0 + 32 i ..; r0 a multiple of 64 where i > 0) at k step kk
+template <bool KC>
+__device__ __forceinline__ bf16x8 half_frag(const char* h, int base, int i, int kk) {
+  if constexpr (KC) {
+    return *reinterpret_cast<const bf16x8*>(h + (base ^ (kk << 5)) + i * 4096);
+  } else {
+    const char* a = h + (base ^ (i << 6)) + kk * 4096;
+    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)a);
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a + 1024));
+    const short __attribute__((ext_vector_type(8))) v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  }
+}
+
+template <int MODE, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
+  constexpr int BM = 256, BN = 256;
+  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
+  constexpr int SMEM = 8 * kHalf;  // two k-tiles of two A and two B halves
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void_t*)smem);
+
+  // ---- which tile ----
+  int e = 0, mt = 0, nt = 0, row0 = 0, rows_e = 0, cnt_e = 0;
+  int seg_o = 0, seg_c = 0;  // KSUM: segment ranges, one lane per segment
+  if constexpr (MODE == MODE_ROWS) {
+    int off_e = 0;
+    if (!row_tile_of_block<BM>(p, blockIdx.x, e, mt, nt, rows_e, cnt_e, off_e)) return;
+    rows_e = clip_rows(off_e, rows_e, p.rows_cap);
+    cnt_e = clip_rows(off_e, cnt_e, p.rows_cap);
+    row0 = off_e + mt * BM;
+  } else {
+    const int mtn = (p.Mdim + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
+    e = blockIdx.x / (mtn * ntn);
+    shared_block_tile(blockIdx.x - e * (mtn * ntn), mtn, ntn, mt, nt);
+    const int g = lane;
+    seg_o = g < p.nseg ? seg_offset(p, g, e) : 0;
+    seg_c = g < p.nseg ? seg_count(p, g, e) : 0;
+    row0 = __builtin_amdgcn_readlane(seg_o, 0);
+    cnt_e = clip_rows(row0, __builtin_amdgcn_readlane(seg_c, 0), p.rows_cap);
+  }
+  constexpr int NCOLS = DUAL ? BN / 2 : BN;
+  const int n0 = nt * NCOLS;
+
+  const bf16_t* A = static_cast<const bf16_t*>(p.A);
+  const bf16_t* B0 = static_cast<const bf16_t*>(p.B0);
+  const bf16_t* B1 = static_cast<const bf16_t*>(p.B1);
+
+  // ---- buffer resources and per-lane source offsets (bytes) ----
+  // A wave fills 1 KB blocks wave and wave + 8 of each half: 8 rows of a
+  // K-contiguous half, 4 k-rows of an M/N-contiguous one.
+  const int kc8 = ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) * 8;  // k of a K-contiguous chunk
+  const int kc_row = 8 * wave + (lane >> 3);
+  const int mnc_k = 4 * wave + (lane >> 4);
+  const int mnc_c = ((lane & 15) ^ ((lane >> 4) << 2)) * 8;
+  const unsigned aoff = (unsigned)(A_KC ? ((long)kc_row * p.lda + kc8) * 2 : ((long)mnc_k * p.lda + mnc_c) * 2);
+  const unsigned boff = (unsigned)(B_KC ? ((long)kc_row * p.ldb + kc8) * 2 : ((long)mnc_k * p.ldb + mnc_c) * 2);
+  // byte steps: second block of a half, second half, k-tile
+  const unsigned a_blk = (unsigned)((A_KC ? 64 : 32) * p.lda * 2), a_half = (unsigned)(A_KC ? 128 * p.lda * 2 : 256);
+  const unsigned b_blk = (unsigned)((B_KC ? 64 : 32) * p.ldb * 2),
+                 b_half = (unsigned)(DUAL ? 0 : B_KC ? 128 * p.ldb * 2 : 256);
+  const unsigned a_kt = (unsigned)(A_KC ? WBK * 2 : WBK * p.lda * 2);
+  const unsigned b_kt = (unsigned)(B_KC ? WBK * 2 : WBK * p.ldb * 2);
+
+  u32x4 ra, rb0, rb1;
+  int nk, nk0 = 1 << 30;  // k-tiles, those before the K split
+  int k_lim = 0;          // ROWS: reduction length (of the part before the split)
+  if constexpr (MODE == MODE_ROWS) {
+    ra = make_rsrc(A + (long)row0 * p.lda, (long)(cnt_e - mt * BM) * p.lda * 2);
+    const long span = (long)p.K * p.ldb;
+    if constexpr (B_KC) {
+      const long valid = (long)(p.N - n0) * p.ldb * 2;
+      rb0 = make_rsrc(B0 + (long)e * p.b_estride + (long)n0 * p.ldb, valid);
+      rb1 = B1 != nullptr ? make_rsrc(B1 + (long)e * p.b_estride + (long)n0 * p.ldb, valid) : rb0;
+    } else {
+      rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
+      rb1 = DUAL ? make_rsrc(B1 + (long)e * p.b_estride + n0, (span - n0) * 2) : rb0;
+    }
+    k_lim = min(p.K, p.ksplit);
+    nk = (k_lim + WBK - 1) / WBK;
+    if (B_KC && p.K > p.ksplit) {
+      nk0 = nk;
+      nk += (p.K - p.ksplit + WBK - 1) / WBK;
+    }
+    // a padding-only tile (padded layout) has nothing to reduce: zeros
+    if (cnt_e <= mt * BM) nk = 0;
+  } else {
+    const int m0 = mt * BM;
+    ra = make_rsrc(A + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
+    rb0 = make_rsrc(B0 + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
+    rb1 = rb0;
+    nk = (cnt_e + WBK - 1) / WBK;
+  }
+  auto bind_segment = [&](int g) {  // KSUM: segment g (g >= 1) of the reduction
+    row0 = g < 64 ? __builtin_amdgcn_readlane(seg_o, g) : seg_offset(p, g, e);
+    cnt_e = clip_rows(row0, g < 64 ? __builtin_amdgcn_readlane(seg_c, g) : seg_count(p, g, e),
+                      p.rows_cap);
+    const int m0 = mt * BM;
+    ra = make_rsrc(A + g * p.a_sstride + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
+    rb0 = make_rsrc(B0 + g * p.b_sstride + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
+    rb1 = rb0;
+    nk = (cnt_e + WBK - 1) / WBK;
+  };
+
+  // Loads of half h of tile t's operand A or B. Chunks past the reduction
+  // length (and every chunk of a tile past the last) are out of the buffer's
+  // range: they load zeros without traffic. The tile's byte offset stays in a
+  // scalar register (opaque to the compiler, which would otherwise step a
+  // vector register per load along the loop, and spill it).
+  auto issue = [&](u32x4 r, unsigned dst, unsigned voff, unsigned so, unsigned blk, bool kc, int lim) {
+    unsigned so2 = so + blk;
+    asm("" : "+s"(so), "+s"(so2));
+    unsigned o = voff + so, o2 = voff + so2;
+    if (kc) {
+      const bool ok = kc8 < lim;
+      o = ok ? o : 0xFFFFFFF0u;
+      o2 = ok ? o2 : 0xFFFFFFF0u;
+    }
+    dma16(r, dst, o);
+    dma16(r, dst + 8192, o2);
+  };
+  auto issue_a = [&](int t, int h) {
+    const unsigned dst = lds0 + ((t & 1) << 16) + h * kHalf + wave * 1024;
+    if constexpr (A_KC) {
+      const bool sec = t >= nk0;
+      const int k0 = (sec ? t - nk0 : t) * WBK, lim = (sec ? p.K - p.ksplit : k_lim) - k0;
+      issue(ra, dst, aoff, (unsigned)((k0 + (sec ? p.ksplit : 0)) * 2) + h * a_half, a_blk, true, lim);
+    } else {
+      issue(ra, dst, aoff, (unsigned)t * a_kt + h * a_half, a_blk, false, 0);
+    }
+  };
+  auto issue_b = [&](int t, int h) {
+    const unsigned dst = lds0 + ((t & 1) << 16) + (2 + h) * kHalf + wave * 1024;
+    if constexpr (B_KC) {
+      const bool sec = t >= nk0;
+      const int k0 = (sec ? t - nk0 : t) * WBK, lim = (sec ? p.K - p.ksplit : k_lim) - k0;
+      issue(sec ? rb1 : rb0, dst, boff, (unsigned)(k0 * 2) + h * b_half, b_blk, true, lim);
+    } else {
+      issue((DUAL && h) ? rb1 : rb0, dst, boff, (unsigned)t * b_kt + h * b_half, b_blk, false, 0);
+    }
+  };
+
+  floatx16 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  auto barrier = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  int abase = half_base(A_KC, wm * 64, lane), bbase = half_base(B_KC, wn * 32, lane);
+  auto k_loop = [&](auto nh_c) {
+    constexpr int NH = decltype(nh_c)::value;  // live A halves of this wave
+    bf16x8 af[2][2][4], bfr[2][4];  // [half][32-row block][k step], [half][k step]
+    // (the bases marked as changed: every XOR of them kept across the loop
+    // would cost a register)
+    auto read_a = [&](int buf, int h) {
+      if (h < NH) {
+        asm("" : "+v"(abase));
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            af[h][i][kk] = half_frag<A_KC>(smem + buf * 4 * kHalf + h * kHalf, abase, i, kk);
+      }
+    };
+    auto read_b = [&](int buf, int h) {
+      if (NH > 0) {
+        asm("" : "+v"(bbase));
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          bfr[h][kk] = half_frag<B_KC>(smem + buf * 4 * kHalf + (2 + h) * kHalf, bbase, 0, kk);
+      }
+    };
+    auto phase = [&](auto&& mem, int ha, int hb) {
+      mem();
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<10>();
+      barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if (ha < NH) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[2 * ha + i][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                bfr[hb][kk], af[ha][i][kk], acc[2 * ha + i][hb], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      wait_lgkm0();
+      barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto tile = [&](int t, auto par_c) {
+      constexpr int X = decltype(par_c)::value, Y = 1 - X;
+      phase([&] { read_b(X, Y); issue_a(t + 2, 0); }, 0, X);
+      phase([&] { read_a(X, 1); issue_b(t + 2, X); }, 0, Y);
+      phase([&] { read_a(Y, 0); issue_b(t + 2, Y); }, 1, Y);
+      phase([&] { read_b(Y, Y); issue_a(t + 2, 1); }, 1, X);
+    };
+    if (nk > 0) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        issue_a(t, 0);
+        issue_b(t, t);
+        issue_b(t, 1 - t);
+        issue_a(t, 1);
+      }
+      wait_vm<10>();
+      barrier();
+      read_a(0, 0);
+      read_b(0, 0);
+      wait_lgkm0();
+      barrier();
+      if (wave >= 4) barrier();
+      for (int t = 0;; t += 2) {
+        tile(t, IntC<0>{});
+        if (t + 1 >= nk) break;
+        tile(t + 1, IntC<1>{});
+        if (t + 2 >= nk) break;
+      }
+      if (wave < 4) barrier();
+    }
+  };
+  if constexpr (MODE == MODE_KSUM) {
+    for (int g = 0; g < p.nseg; ++g) {
+      if (g > 0) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();  // every load and LDS read of the last segment done before the refill
+        bind_segment(g);
+      }
+      k_loop(IntC<2>{});
+    }
+  } else {
+    // live 64-row halves of this wave (wave-uniform): rows wm * 64 and 128 + wm * 64
+    const int live = cnt_e - mt * BM - wm * 64;
+    if (live > 128) k_loop(IntC<2>{});
+    else if (live > 0) k_loop(IntC<1>{});
+    else k_loop(IntC<0>{});
+  }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();  // all loads landed and LDS reads done before the epilogue reuses the stages
+  gemm_epilogue<MODE, EPI, BM, BN, 512, SMEM, 128, 64, true>(p, acc, smem, e, mt, n0, row0, rows_e,
+                                                              cnt_e, wm, wn);
 }
 
 // ---------------------------------------------------------------------------
@@ -1528,8 +1827,12 @@ hipError_t launch_dma(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   }
   if (blocks == 0) return hipSuccess;
   return traced(kind, st, [&] {
-    hipLaunchKernelGGL((gemm_dma_kernel<MODE, A_KC, B_KC, EPI, NARROW>), dim3((unsigned)blocks),
-                       dim3(NARROW ? 256 : 512), 0, st, p);
+    if constexpr (NARROW)
+      hipLaunchKernelGGL((gemm_narrow_kernel<MODE, A_KC, B_KC, EPI>), dim3((unsigned)blocks),
+                         dim3(256), 0, st, p);
+    else
+      hipLaunchKernelGGL((gemm_wide_kernel<MODE, A_KC, B_KC, EPI>), dim3((unsigned)blocks),
+                         dim3(512), 0, st, p);
   });
 }
 
