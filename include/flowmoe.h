@@ -280,7 +280,7 @@ enum {
   FLOWMOE_K_GATHER = 3,          /* row gather into x_disp (dispatch) */
   FLOWMOE_K_FFN1 = 4,            /* grouped GEMM h = X W1 (+ W3), activation epilogue */
   FLOWMOE_K_FFN2 = 5,            /* grouped GEMM y = a W2 */
-  FLOWMOE_K_SWIGLU_ACT = 6,      /* fp32 SwiGLU activation */
+  FLOWMOE_K_SWIGLU_ACT = 6,      /* (not launched: the fp32 SwiGLU activation is part of ffn1) */
   FLOWMOE_K_COMBINE = 7,         /* combine, and dispatch backward (gather-sum; in
                                     flowmoe_layer_bwd fused with dx += d_logits W_g^T) */
   FLOWMOE_K_COMBINE_BWD = 8,     /* combine backward */

@@ -16,8 +16,8 @@
 // chunk index XOR-swizzled by (row & 7), double-buffered with register prefetch
 // of the next k-tile; operands contiguous along M or N are loaded as KT x 8
 // blocks and transposed in registers before the LDS write.
-// fp32 path (correctness workloads): a plain LDS-tiled FMA kernel with the
-// same modes and epilogues.
+// fp32 path: v_mfma_f32_32x32x2_f32 over 128-, 64- or 32-row x 128-column tiles,
+// the same modes and epilogues.
 #include <math.h>
 
 #include <algorithm>
@@ -63,7 +63,6 @@ struct GemmParams {
   long ldc, ldc1;
   long c_estride;    // KSUM: per-expert stride of C
   int nsplit;        // EPI_WGRAD: first column that goes to C1
-  int coloff;        // column offset added to C0 stores (fp32 split forward)
   const void* aux;   // h (GELU) or [h1 | h3] (SwiGLU), ld = ldaux
   long ldaux;
   int Hh;            // SwiGLU: H (offset of the second half)
@@ -1519,156 +1518,273 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel: 64 x 64 tiles, 16-deep k steps, 4 x 4 outputs per thread
+// fp32 kernel: v_mfma_f32_32x32x2_f32
 // ---------------------------------------------------------------------------
-template <int MODE, bool B_KC, int EPI>
+// Tiles of BM = 32 FM rows x 128 columns, 4 waves side by side along the columns:
+// every wave holds all BM rows of its 32 columns (and, DUAL, the same 32 columns
+// of W3), so that a ragged tile's dead 32-row blocks are skipped by all four
+// alike. 16-deep k-tiles, double-buffered through registers into LDS.
+//
+// The matrix pipes bound it (64 cycles an instruction, 157 TFLOP/s): an
+// instruction needs one A and one B value a lane, so LDS and memory are nearly
+// idle. A step of the k order takes k and k + 4 (a lane's half-wave takes k % 8
+// in 0..3 or 4..7), so that a K-contiguous operand is read 16 bytes a lane for
+// four instructions. One launch of the fused SwiGLU forward replaces two GEMMs
+// and an activation pass. Measured against the 64 x 64 FMA tiles it replaced
+// (fp32 layer of T = 4096, M = 512, H = 1024, E = 32, k = 2, one launch each):
+// forward 291 and 278 -> 126 and 117 us, dgrads 396 and 353 -> 123 and 118, weight
+// gradients 207 -> 119: 68-73 TFLOP/s, with the experts' 256 +- 16 rows and the
+// last partial round of blocks taking most of the rest.
+constexpr int FK = 16;         // k depth of a tile
+constexpr int FPK = FK + 4;    // LDS pitch of a K-contiguous row (floats): 16 rows, 16 bank groups
+constexpr int FPB = 128 + 8;   // pitch of a k-row of B: rows k and k + 4 on other halves of the banks
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+template <int MODE, bool B_KC, int EPI, int FM>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-  constexpr int TB = 64, TK = 16;
-  __shared__ float As[TK][TB + 1];
-  __shared__ float Bs[TK][TB + 1];
-  const int tid = threadIdx.x;
+  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
+  constexpr int NB = DUAL ? 2 : 1;
+  constexpr int BM = 32 * FM, BN = 128;
+  constexpr bool A_KC = MODE == MODE_ROWS;
+  constexpr int FPA = A_KC ? FPK : BM + 8;               // pitch of A's rows / k-rows
+  constexpr int ASZ = A_KC ? BM * FPK : FK * FPA;        // floats of an A tile
+  constexpr int BSZ = B_KC ? BN * FPK : FK * FPB;
+  constexpr int ACH = BM * FK / 4, BCH = BN * FK / 4;    // 16-byte chunks of a tile
+  constexpr int AL = (ACH + 255) / 256, BL = BCH / 256;  // chunks a thread
+  __shared__ __attribute__((aligned(16))) float smem[2][ASZ + NB * BSZ];
+  const int tid = threadIdx.x, lane = tid & 63, h2 = lane >> 5, lr = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
   int e = 0, mt = 0, nt = 0, row0 = 0, rows_e = 0, cnt_e = 0;
+  const int ntn = (p.N + BN - 1) / BN;
   if constexpr (MODE == MODE_ROWS) {
-    nt = blockIdx.x / p.mt_bound;
-    const int ml = blockIdx.x % p.mt_bound;
-    int acc_t = 0;
-    mt = -1;
-    for (e = 0; e < p.E; ++e) {
-      const int c = seg_count(p, 0, e);
-      const int r = p.padC ? p.padC : c;
-      const int te = (r + TB - 1) / TB;
-      if (ml < acc_t + te) {
-        mt = ml - acc_t;
-        rows_e = r;
-        cnt_e = c;
-        break;
-      }
-      acc_t += te;
-    }
-    if (mt < 0) return;
-    rows_e = clip_rows(seg_offset(p, 0, e), rows_e, p.rows_cap);
-    cnt_e = clip_rows(seg_offset(p, 0, e), cnt_e, p.rows_cap);
-    row0 = seg_offset(p, 0, e) + mt * TB;
+    // column tiles fastest; lane x holds expert x (as row_tile_of_block)
+    const int vb = xcd_remap(blockIdx.x, gridDim.x);
+    nt = vb % ntn;
+    const int ml = vb / ntn;
+    const bool live = lane < p.E;
+    const int c = live ? seg_count(p, 0, lane) : 0;
+    const int o = live ? seg_offset(p, 0, lane) : 0;
+    const int r = live ? (p.padC ? p.padC : c) : 0;
+    const int te = (r + BM - 1) / BM;
+    const int inc = wave_incl_scan(te);
+    const uint64_t hit = __ballot(live && ml < inc && ml >= inc - te);
+    if (hit == 0) return;
+    e = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
+    mt = ml - (__builtin_amdgcn_readlane(inc, e) - __builtin_amdgcn_readlane(te, e));
+    const int off = __builtin_amdgcn_readlane(o, e);
+    rows_e = clip_rows(off, __builtin_amdgcn_readlane(r, e), p.rows_cap);
+    cnt_e = clip_rows(off, __builtin_amdgcn_readlane(c, e), p.rows_cap);
+    row0 = off + mt * BM;
   } else {
-    const int mtn = (p.Mdim + TB - 1) / TB, ntn = (p.N + TB - 1) / TB;
-    e = blockIdx.x / (mtn * ntn);
-    const int rem = blockIdx.x % (mtn * ntn);
+    const int mtn = (p.Mdim + BM - 1) / BM;
+    const int vb = xcd_remap(blockIdx.x, gridDim.x);
+    e = vb / (mtn * ntn);
+    const int rem = vb - e * (mtn * ntn);
     mt = rem / ntn;
-    nt = rem % ntn;
-    cnt_e = clip_rows(seg_offset(p, 0, e), seg_count(p, 0, e), p.rows_cap);
-    row0 = seg_offset(p, 0, e);
+    nt = rem - mt * ntn;
   }
-  const int n0 = nt * TB;
-  const float* A = static_cast<const float*>(p.A);
-  const float* B0 = static_cast<const float*>(p.B0);
-  const float* B1 = static_cast<const float*>(p.B1);
-  const int ty = tid >> 4, tx = tid & 15;
-  float acc[4][4] = {};
-  // KSUM: segments (chunks) one after the other into the same accumulators
-  const int nseg = (MODE == MODE_KSUM) ? p.nseg : 1;
+  const int n0 = nt * BN;
+  // live 32-row blocks (weight gradients: of the Mdim rows)
+  const int live_rows = MODE == MODE_ROWS ? cnt_e - mt * BM : p.Mdim - mt * BM;
+  const int nf = min(FM, (max(0, live_rows) + 31) / 32);
+
+  floatx16 acc[FM][NB];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][b][r] = 0.f;
+
+  const int nseg = MODE == MODE_KSUM ? p.nseg : 1;
   for (int g = 0; g < nseg; ++g) {
-    if (g > 0) {
+    const float* A = static_cast<const float*>(p.A);
+    const float* B0 = static_cast<const float*>(p.B0);
+    const float* B1 = static_cast<const float*>(p.B1);
+    int Kred = p.K;
+    if constexpr (MODE == MODE_KSUM) {
       row0 = seg_offset(p, g, e);
-      cnt_e = clip_rows(row0, seg_count(p, g, e), p.rows_cap);
-      A = static_cast<const float*>(p.A) + g * p.a_sstride;
-      B0 = static_cast<const float*>(p.B0) + g * p.b_sstride;
+      Kred = clip_rows(row0, seg_count(p, g, e), p.rows_cap);
+      A += g * p.a_sstride + (long)row0 * p.lda + mt * BM;
+      B0 += g * p.b_sstride + (long)row0 * p.ldb + n0;
+    } else {
+      A += (long)row0 * p.lda;
+      B0 += (long)e * p.b_estride + (B_KC ? (long)n0 * p.ldb : n0);
+      if (B1 != nullptr) B1 += (long)e * p.b_estride + (B_KC ? (long)n0 * p.ldb : n0);
+      if (nf == 0) Kred = 0;  // a padding-only tile: zeros
     }
-    const int Kred = (MODE == MODE_ROWS) ? p.K : cnt_e;
-    for (int k0 = 0; k0 < Kred; k0 += TK) {
-      for (int q = tid; q < TK * TB; q += 256) {
-        const int kk = q / TB, ii = q % TB;
-        const int k = k0 + kk;
-        float av = 0.f, bv = 0.f;
-        if (k < Kred) {
-          if constexpr (MODE == MODE_ROWS) {
-            if (mt * TB + ii < cnt_e) av = A[(long)(row0 + ii) * p.lda + k];
+    const int nk = (Kred + FK - 1) / FK;
+
+    floatx4 ra[AL], rb[NB][BL];
+    auto load = [&](int k0) {
+#pragma unroll
+      for (int u = 0; u < AL; ++u) {
+        const int q = tid + 256 * u;
+        ra[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (A_KC) {
+          const int r = q / (FK / 4), k = k0 + 4 * (q % (FK / 4));
+          if (q < ACH && r < live_rows && k < Kred)
+            ra[u] = *reinterpret_cast<const floatx4*>(A + (long)r * p.lda + k);
+        } else {
+          const int k = k0 + q / (BM / 4), m = 4 * (q % (BM / 4));
+          if (q < ACH && k < Kred && m < live_rows)
+            ra[u] = *reinterpret_cast<const floatx4*>(A + (long)k * p.lda + m);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < BL; ++u) {
+        const int q = tid + 256 * u;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          rb[b][u] = floatx4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (B_KC) {
+            const int n = q / (FK / 4), k = k0 + 4 * (q % (FK / 4));
+            if (n0 + n < p.N && k < Kred)
+              rb[b][u] = *reinterpret_cast<const floatx4*>(
+                  k < p.ksplit ? B0 + (long)n * p.ldb + k : B1 + (long)n * p.ldb + (k - p.ksplit));
           } else {
-            if (mt * TB + ii < p.Mdim) av = A[(long)(row0 + k) * p.lda + mt * TB + ii];
-          }
-          const int n = n0 + ii;
-          if (n < p.N) {
-            if constexpr (MODE == MODE_KSUM) {
-              bv = B0[(long)(row0 + k) * p.ldb + n];
-            } else if constexpr (B_KC) {
-              bv = (k < p.ksplit) ? B0[(long)e * p.b_estride + (long)n * p.ldb + k]
-                                  : B1[(long)e * p.b_estride + (long)n * p.ldb + (k - p.ksplit)];
-            } else {
-              bv = B0[(long)e * p.b_estride + (long)k * p.ldb + n];
-            }
+            const int k = k0 + q / (BN / 4), n = 4 * (q % (BN / 4));
+            if (n0 + n < p.N && k < Kred)
+              rb[b][u] = *reinterpret_cast<const floatx4*>((DUAL && b ? B1 : B0) + (long)k * p.ldb + n);
           }
         }
-        As[kk][ii] = av;
-        Bs[kk][ii] = bv;
       }
+    };
+    auto store = [&](float* sm) {
+#pragma unroll
+      for (int u = 0; u < AL; ++u) {
+        const int q = tid + 256 * u;
+        if (ACH % 256 == 0 || q < ACH)
+          *reinterpret_cast<floatx4*>(sm + (A_KC ? (q / (FK / 4)) * FPA + 4 * (q % (FK / 4))
+                                                 : (q / (BM / 4)) * FPA + 4 * (q % (BM / 4)))) = ra[u];
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int u = 0; u < BL; ++u) {
+          const int q = tid + 256 * u;
+          *reinterpret_cast<floatx4*>(sm + ASZ + b * BSZ +
+                                      (B_KC ? (q / (FK / 4)) * FPK + 4 * (q % (FK / 4))
+                                            : (q / (BN / 4)) * FPB + 4 * (q % (BN / 4)))) = rb[b][u];
+        }
+    };
+    if (nk > 0) {
+      load(0);
+      if (g > 0) __syncthreads();  // the last segment's reads are done
+      store(smem[0]);
       __syncthreads();
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt + 1 < nk) load((kt + 1) * FK);
+      const float* sa = smem[kt & 1];
+      const float* sb = sa + ASZ;
 #pragma unroll
-      for (int kk = 0; kk < TK; ++kk) {
-        float a[4], b[4];
+      for (int k8 = 0; k8 < FK; k8 += 8) {
+        const int kh = k8 + 4 * h2;  // this half-wave's four k
+        floatx4 bv[NB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+        for (int b = 0; b < NB; ++b) {
+          const float* s = sb + b * BSZ;
+          if constexpr (B_KC) {
+            bv[b] = *reinterpret_cast<const floatx4*>(s + (w * 32 + lr) * FPK + kh);
+          } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+            for (int q = 0; q < 4; ++q) bv[b][q] = s[(kh + q) * FPB + w * 32 + lr];
+          }
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FM; ++i) {
+          if (i >= nf) break;
+          floatx4 av;
+          if constexpr (A_KC) {
+            av = *reinterpret_cast<const floatx4*>(sa + (i * 32 + lr) * FPA + kh);
+          } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+            for (int q = 0; q < 4; ++q) av[q] = sa[(kh + q) * FPA + i * 32 + lr];
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+              acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q], bv[b][q], acc[i][b], 0, 0, 0);
+        }
       }
+      if (kt + 1 < nk) store(smem[(kt + 1) & 1]);
       __syncthreads();
     }
   }
+
+  // ---- epilogue: acc[i][b][r] is row 32 i + 8 (r / 4) + 4 h2 + r % 4, column n0 + 32 w + lr
   float* C0 = static_cast<float*>(p.C0);
   float* C1 = static_cast<float*>(p.C1);
   const float* aux = static_cast<const float*>(p.aux);
+  const int n = n0 + w * 32 + lr;
+  if (n >= p.N) return;
+  float bias0 = 0.f, bias1 = 0.f;
+  if constexpr (MODE == MODE_ROWS && (EPI == EPI_STORE || EPI == EPI_GELU_FWD || DUAL)) {
+    if (p.bias0 != nullptr) bias0 = p.bias0[(long)e * p.bias_estride + n];
+    if (DUAL && p.bias1 != nullptr) bias1 = p.bias1[(long)e * p.bias_estride + n];
+  }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ti = ty * 4 + i;
+  for (int i = 0; i < FM; ++i) {
+    // a block's loads go out before its stores
+    float h1[16], h3[16];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= p.N) continue;
+    for (int r = 0; r < 16; ++r) {
+      const int ti = 32 * i + 8 * (r >> 2) + 4 * h2 + (r & 3);
+      h1[r] = h3[r] = 0.f;
       if constexpr (MODE == MODE_ROWS) {
-        const int li = mt * TB + ti;
-        if (li >= rows_e) continue;
-        float v = (li < cnt_e) ? acc[i][j] : 0.f;
-        if constexpr (EPI == EPI_STORE || EPI == EPI_GELU_FWD) {
-          if (li < cnt_e && p.bias0 != nullptr) v += p.bias0[(long)e * p.bias_estride + n];
+        if constexpr (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) {
+          if (mt * BM + ti < rows_e) {
+            const float* a = aux + (long)(row0 + ti) * p.ldaux + n;
+            h1[r] = *a;
+            if constexpr (EPI == EPI_SWIGLU_BWD) h3[r] = a[p.Hh];
+          }
         }
+      } else if (p.accumulate) {
+        const int m = mt * BM + ti;
+        if (m < p.Mdim)
+          h1[r] = n < p.nsplit ? C0[(long)e * p.c_estride + (long)m * p.ldc + n]
+                               : C1[(long)e * p.c_estride + (long)m * p.ldc + (n - p.nsplit)];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int ti = 32 * i + 8 * (r >> 2) + 4 * h2 + (r & 3);
+      float v = acc[i][0][r];
+      if constexpr (MODE == MODE_ROWS) {
+        const int li = mt * BM + ti;
+        if (li >= rows_e) continue;
+        const bool data = li < cnt_e;
+        v = data ? v + bias0 : 0.f;
         const long g = row0 + ti;
         if constexpr (EPI == EPI_STORE) {
-          C0[g * p.ldc + p.coloff + n] = v;
+          C0[g * p.ldc + n] = v;
         } else if constexpr (EPI == EPI_GELU_FWD) {
           C0[g * p.ldc + n] = v;
           C1[g * p.ldc1 + n] = gelu_f(v);
+        } else if constexpr (DUAL) {
+          const float v3 = data ? acc[i][NB - 1][r] + bias1 : 0.f;
+          C0[g * p.ldc + n] = v;
+          C0[g * p.ldc + p.Hh + n] = v3;
+          C1[g * p.ldc1 + n] = silu_f(v) * v3;
         } else if constexpr (EPI == EPI_GELU_BWD) {
-          C0[g * p.ldc + n] = v * gelu_grad_f(aux[g * p.ldaux + n]);
+          C0[g * p.ldc + n] = v * gelu_grad_f(h1[r]);
         } else if constexpr (EPI == EPI_SWIGLU_BWD) {
-          const float h1 = aux[g * p.ldaux + n], h3 = aux[g * p.ldaux + p.Hh + n];
-          const float sg = sigmoid_f(h1);
-          C0[g * p.ldc + n] = v * h3 * sg * (1.f + h1 * (1.f - sg));
-          C0[g * p.ldc + p.Hh + n] = v * h1 * sg;
+          const float sg = sigmoid_f(h1[r]);
+          C0[g * p.ldc + n] = v * h3[r] * sg * (1.f + h1[r] * (1.f - sg));
+          C0[g * p.ldc + p.Hh + n] = v * h1[r] * sg;
         }
       } else {
-        const int m = mt * TB + ti;
+        const int m = mt * BM + ti;
         if (m >= p.Mdim) continue;
         float* dst = (n < p.nsplit) ? C0 + (long)e * p.c_estride + (long)m * p.ldc + n
                                     : C1 + (long)e * p.c_estride + (long)m * p.ldc + (n - p.nsplit);
-        *dst = p.accumulate ? *dst + acc[i][j] : acc[i][j];
+        *dst = p.accumulate ? h1[r] + v : v;
       }
     }
-  }
-}
-
-// fp32 SwiGLU activation: a = silu(h1) * h3 over the live rows
-__global__ void swiglu_act_f32_kernel(const float* __restrict__ h, float* __restrict__ a,
-                                      const int32_t* __restrict__ offsets, int E, long rows,
-                                      int padded, int H) {
-  const long live = padded ? rows : min((long)offsets[E], rows);  // (cut at the buffers)
-  const long n = live * H;
-  for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < n; q += (long)gridDim.x * blockDim.x) {
-    const long r = q / H;
-    const int c = (int)(q % H);
-    const float h1 = h[r * 2 * H + c], h3 = h[r * 2 * H + H + c];
-    a[q] = h1 * sigmoid_f(h1) * h3;
   }
 }
 
@@ -1864,21 +1980,35 @@ hipError_t run_gemm_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st)
   return run_bf16<MODE, A_KC, B_KC, EPI, 256, 256, 512>(kind, s, p, st);
 }
 
+template <int MODE, bool B_KC, int EPI, int FM>
+hipError_t launch_f32(int kind, const Shape& s, GemmParams p, hipStream_t st) {
+  constexpr int BM = 32 * FM;
+  const long rt = (MODE == MODE_ROWS) ? rows_tiles_bound(s, BM) : (long)s.E * ((p.Mdim + BM - 1) / BM);
+  const long blocks = rt * ((p.N + 127) / 128);
+  if (blocks == 0) return hipSuccess;
+  return traced(kind, st, [&] {
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE, B_KC, EPI, FM>), dim3((unsigned)blocks), dim3(256), 0,
+                       st, p);
+  });
+}
+
+// Rows a tile: 128, or 64 or 32 where taller tiles would be too few to even out
+// over the 256 CUs (several blocks share one). Row mode: below 2048 tiles (8192
+// rows of 32 experts at N = 512: 32 rows 116 us, 64 rows 146, 128 rows 155; the
+// fused SwiGLU forward of 8 experts at N = 2048, K = 1024: 64 rows 645, 128 rows
+// 800, its two accumulator sets leaving one wave a SIMD, so 64 rows at most).
+// Weight gradients have full tiles only: below 512 (E = 8, 2048 x 1024: 128 rows
+// 335 us, 64 rows 396; E = 32, 1024 x 512: 120 and 121).
 template <int MODE, bool B_KC, int EPI>
 hipError_t run_f32(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   if (MODE == MODE_KSUM && p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
-  long blocks;
-  if (MODE == MODE_ROWS) {
-    p.mt_bound = rows_tiles_bound(s, 64);
-    blocks = (long)p.mt_bound * ((p.N + 63) / 64);
-  } else {
-    blocks = (long)s.E * ((p.Mdim + 63) / 64) * ((p.N + 63) / 64);
-  }
-  if (blocks == 0) return hipSuccess;
-  return traced(kind, st, [&] {
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE, B_KC, EPI>), dim3((unsigned)blocks), dim3(256), 0, st,
-                       p);
-  });
+  if (s.rows == 0 && MODE == MODE_ROWS) return hipSuccess;
+  const long rows = MODE == MODE_ROWS ? s.rows : (long)s.E * p.Mdim;
+  const long nt = (p.N + 127) / 128, least = MODE == MODE_ROWS ? 2048 : 512;
+  if constexpr (EPI != EPI_SWIGLU_FWD)
+    if ((rows + 127) / 128 * nt >= least) return launch_f32<MODE, B_KC, EPI, 4>(kind, s, p, st);
+  if ((rows + 63) / 64 * nt >= least) return launch_f32<MODE, B_KC, EPI, 2>(kind, s, p, st);
+  return launch_f32<MODE, B_KC, EPI, 1>(kind, s, p, st);
 }
 
 #define FLOWMOE_TRY(x)                 \
@@ -2069,17 +2199,7 @@ hipError_t launch_expert_ffn(const Shape& s, const void* x_disp, const int32_t* 
       FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, false, EPI_GELU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
   } else {
     if (swiglu) {
-      p.B1 = nullptr;
-      FLOWMOE_TRY((run_f32<MODE_ROWS, false, EPI_STORE>(FLOWMOE_K_FFN1, s, p, st)));
-      p.B0 = w3;
-      p.coloff = H;
-      p.bias0 = b3;
-      FLOWMOE_TRY((run_f32<MODE_ROWS, false, EPI_STORE>(FLOWMOE_K_FFN1, s, p, st)));
-      FLOWMOE_TRY(traced(FLOWMOE_K_SWIGLU_ACT, st, [&] {
-        hipLaunchKernelGGL(swiglu_act_f32_kernel, dim3(1024), dim3(256), 0, st,
-                           (const float*)h_save, (float*)a_save, offsets, s.E, s.rows,
-                           s.layout == FLOWMOE_PADDED, H);
-      }));
+      FLOWMOE_TRY((run_f32<MODE_ROWS, false, EPI_SWIGLU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
     } else {
       FLOWMOE_TRY((run_f32<MODE_ROWS, false, EPI_GELU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
     }

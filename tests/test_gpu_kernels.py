@@ -719,3 +719,49 @@ def test_combine_and_backward_steps(dtype, layout):
                             None, 1, ws, nws)
     torch.cuda.synchronize()
     assert_close(host(dwg), 2 * g["dw_gate"], dtype, "dw_gate accumulated")
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("cnt,M,H", [
+    ([7000, 0, 129, 9000, 31], 40, 2056),   # row mode: 128-row tiles (SwiGLU forward: 64)
+    ([4000, 65, 3935, 1], 40, 2056),        # row mode: 64-row tiles, reductions of 2 1/2 k-tiles
+    ([0, 1, 15, 16, 17, 33, 8, 5], 1032, 1032),  # weight gradients: 128-row tiles
+    ([31, 0, 33, 1], 1032, 1032),           # weight gradients: 64-row tiles
+], ids=["rows128", "rows64", "wgrad128", "wgrad64"])
+def test_expert_ffn_f32_tiles(cnt, M, H, act):
+    """fp32 experts at sizes that take the taller tiles of the fp32 GEMM (the
+    smaller tests take its 32-row ones): ragged last tiles in rows, columns
+    and reduction, empty experts, two accumulated passes. fp32 tolerance: the
+    sums' rounding is about 1e-6 of the largest value."""
+    need_gpu()
+    d, E, C = dev(), len(cnt), max(cnt)
+    cnt = np.array(cnt)
+    T = int(cnt.sum())
+    rt = oracle.route(np.repeat(np.arange(E), cnt)[:, None], E, C, "packed")
+    inp = make_inputs(get_config("balanced", T=T, M=M, H=H, E=E, k=1, dtype="f32", act=act, seed=12))
+    x64, dy64 = (oracle.dispatch(as_f64(inp[n]), rt["row_src"], 1) for n in ("x", "dy"))
+    x, dy = (torch.from_numpy(v).to(d).float() for v in (x64, dy64))
+    w = {n: to_torch(inp[n], d) for n in ("w1", "w3", "w2")}
+    w64 = [None if inp[n] is None else as_f64(inp[n]) for n in ("w1", "w3", "w2")]
+    counts, offsets = (torch.from_numpy(rt[n].astype(np.int32)).to(d) for n in ("counts", "offsets"))
+    HW = 2 * H if act == "swiglu" else H
+    h, a, y, dx = (torch.full((T, n), 5.0, device=d) for n in (HW, H, M, M))
+    dw1, dw2 = torch.full((E, M, H), 9.0, device=d), torch.full((E, H, M), 9.0, device=d)
+    dw3 = torch.full((E, M, H), 9.0, device=d) if act == "swiglu" else None
+    s = _shape(T, M, H, E, 1, C, "f32", act, "packed")
+    nws = L.flowmoe_workspace_bytes(s, L.WS_FFN_BWD)
+    ws = torch.empty(nws, dtype=torch.uint8, device=d)
+    L.flowmoe_expert_ffn(s, x, counts, offsets, w["w1"], w["w3"], w["w2"], h, a, y)
+    for acc in (0, 1):
+        L.flowmoe_expert_ffn_bwd(s, dy, x, h, a, counts, offsets, w["w1"], w["w3"], w["w2"], dx, dw1,
+                                 dw3, dw2, acc, ws, nws)
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(x64, rt["counts"], rt["offsets"], *w64, act)
+    rdx, rdw1, rdw3, rdw2 = oracle.expert_ffn_bwd(dy64, x64, ref, rt["counts"], rt["offsets"], *w64,
+                                                  act)[:4]
+    hw = ref["h1"] if act == "gelu" else np.concatenate([ref["h1"], ref["h3"]], axis=1)
+    for got, want, n in ((h, hw, "h_save"), (a, ref["a"], "a_save"), (y, ref["y_disp"], "y_disp"),
+                         (dx, rdx, "dx_disp"), (dw1, 2 * rdw1, "dw1"), (dw2, 2 * rdw2, "dw2"),
+                         (dw3, None if rdw3 is None else 2 * rdw3, "dw3")):
+        if got is not None:
+            assert_close(host(got), want, "f32", n, tol=1e-5)
