@@ -15,7 +15,6 @@ namespace flowmoe {
 namespace {
 
 constexpr int kGateThreads = 256;
-constexpr int kGateLdsFloats = 8192;  // x staging budget: 32 KB of LDS
 
 __host__ __device__ inline int pow2_at_least(int e) {
   int p = 1;
@@ -255,57 +254,88 @@ __device__ __forceinline__ void topk_extract(const float* logit, int E, int k, i
   if (p == 0) topk_store<KM>(tk, k, z, idx_out, w_out);
 }
 
-// Fused gate: per block 4 waves; each wave has G = 64/EP segments, each
-// segment TPG tokens. x rows of the block are staged in LDS as float.
-template <typename TIn>
-__global__ __launch_bounds__(kGateThreads) void gate_topk_kernel(
-    const TIn* __restrict__ x, const TIn* __restrict__ wg, const float* __restrict__ bias,
+// Fused gate of fp32 layers: min(256, 64 EP) threads, EP lanes a token (lane e
+// the expert), TPT tokens a lane. x and W_g go through LDS in chunks of 64 of
+// the M reduction (float4 loads, the next chunk's in flight while this one is
+// used); every logit is one chain of FMAs over ascending m. Latency binds it
+// (67 MFLOP at T = 4096, M = 512, E = 32): with W_g read from memory in that
+// chain and 128 blocks it took 146 us (279 in a layer step); 18 us now (T = 16384,
+// M = 4096, E = 64: 2173 -> 378 us; T = 256, M = 64, E = 4: 13.6 -> 8.1), the same bits.
+template <int EP>
+__global__ __launch_bounds__(EP >= 4 ? 256 : 64 * EP) void gate_topk_kernel(
+    const float* __restrict__ x, const float* __restrict__ wg, const float* __restrict__ bias,
     float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ w, int T, int M,
-    int E, int k, int EP, int TPG, int xchunk, int full) {
-  extern __shared__ float xs[];  // [tokens_per_block][xchunk]
-  const int G = 64 / EP;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int seg = lane / EP, e = lane % EP;
-  const int tpb = 4 * G * TPG;  // tokens per block
-  const int t0 = blockIdx.x * tpb;
-  // token slot of (wave, seg, i) inside the block: wave-major
-  const int base_slot = (wave * G + seg) * TPG;
+    int E, int k, int full) {
+  constexpr int NT = EP >= 4 ? 256 : 64 * EP;
+  constexpr int TPT = EP >= 16 ? 2 : 1;       // tokens a lane
+  constexpr int TPB = NT / EP * TPT;          // tokens a block (at most 64)
+  constexpr int MC = 64, XP = MC + 4;         // chunk; LDS pitch of a token
+  constexpr int XL = (TPB * MC / 4 + NT - 1) / NT, WL = (MC * EP / 4 + NT - 1) / NT;
+  __shared__ __attribute__((aligned(16))) float xs[TPB * XP];
+  __shared__ __attribute__((aligned(16))) float ws[MC * EP];
+  const int tid = threadIdx.x, e = tid % EP, slot = tid / EP * TPT;
+  const int t0 = blockIdx.x * TPB;
   const bool evalid = e < E;
-
-  float acc[8];
+  const int es = evalid ? e : 0;
+  float4 xr[XL], wr[WL];
+  auto load = [&](int m0) {
+    const int mc = min(MC, M - m0);  // a multiple of 8
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-
-  for (int m0 = 0; m0 < M; m0 += xchunk) {
-    const int mc = min(xchunk, M - m0);
-    __syncthreads();
-    // stage x[t0 .. t0+tpb) [m0 .. m0+mc) as float
-    for (int q = threadIdx.x; q < tpb * mc; q += kGateThreads) {
-      int tt = q / mc, mm = q % mc;
-      int t = t0 + tt;
-      xs[tt * xchunk + mm] = (t < T) ? Elem<TIn>::load(x + (size_t)t * M + m0 + mm) : 0.f;
+    for (int u = 0; u < XL; ++u) {
+      const int q = tid + NT * u, t = t0 + q / (MC / 4), m = 4 * (q % (MC / 4));
+      xr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (q < TPB * MC / 4 && t < T && m < mc)
+        xr[u] = *reinterpret_cast<const float4*>(x + (size_t)t * M + m0 + m);
+    }
+#pragma unroll
+    for (int u = 0; u < WL; ++u) {  // rows m0 .. m0 + mc of W_g are contiguous
+      const int q = tid + NT * u;
+      wr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (q < mc * E / 4) wr[u] = *reinterpret_cast<const float4*>(wg + (size_t)m0 * E + 4 * q);
+    }
+  };
+  float acc[TPT];
+#pragma unroll
+  for (int i = 0; i < TPT; ++i) acc[i] = 0.f;
+  load(0);
+  for (int m0 = 0; m0 < M; m0 += MC) {
+    __syncthreads();  // the last chunk's reads are done
+#pragma unroll
+    for (int u = 0; u < XL; ++u) {
+      const int q = tid + NT * u;
+      if (q < TPB * MC / 4) *reinterpret_cast<float4*>(xs + q / (MC / 4) * XP + 4 * (q % (MC / 4))) = xr[u];
+    }
+#pragma unroll
+    for (int u = 0; u < WL; ++u) {
+      const int q = tid + NT * u;
+      if (q < MC * EP / 4) *reinterpret_cast<float4*>(ws + 4 * q) = wr[u];
     }
     __syncthreads();
-    if (evalid) {
-      const TIn* wcol = wg + (size_t)m0 * E + e;
-      for (int mm = 0; mm < mc; ++mm) {
-        float wv = Elem<TIn>::load(wcol + (size_t)mm * E);
+    if (m0 + MC < M) load(m0 + MC);
+    const int mc = min(MC, M - m0);
+#pragma unroll 4
+    for (int mm = 0; mm < mc; mm += 4) {
+      float wv[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (i < TPG) acc[i] += xs[(base_slot + i) * xchunk + mm] * wv;
+      for (int q = 0; q < 4; ++q) wv[q] = ws[(mm + q) * E + es];
+#pragma unroll
+      for (int i = 0; i < TPT; ++i) {
+        const float4 xv = *reinterpret_cast<const float4*>(xs + (slot + i) * XP + mm);
+        acc[i] = fmaf(xv.x, wv[0], acc[i]);
+        acc[i] = fmaf(xv.y, wv[1], acc[i]);
+        acc[i] = fmaf(xv.z, wv[2], acc[i]);
+        acc[i] = fmaf(xv.w, wv[3], acc[i]);
       }
     }
   }
   const float b = (bias != nullptr && evalid) ? bias[e] : 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (i < TPG) {
-      const int t = t0 + base_slot + i;
-      if (t < T) {  // uniform across the segment
-        float l = acc[i] + b;
-        if (evalid) logits[(size_t)t * E + e] = l;
-        topk_write(l, e, evalid, EP, k, full, idx + (size_t)t * k, w + (size_t)t * k);
-      }
+  for (int i = 0; i < TPT; ++i) {
+    const int t = t0 + slot + i;
+    if (t < T) {  // uniform across the token's lanes
+      const float l = acc[i] + b;
+      if (evalid) logits[(size_t)t * E + e] = l;
+      topk_write(l, e, evalid, EP, k, full, idx + (size_t)t * k, w + (size_t)t * k);
     }
   }
 }
@@ -1232,17 +1262,24 @@ hipError_t launch_gate_topk(const Shape& s, const void* x, const void* w_gate, c
 #undef FLOWMOE_GATE_KERNEL
     });
   }
-  const int G = 64 / EP;
-  const int TPG = G >= 8 ? 1 : 8 / G;
-  const int tpb = 4 * G * TPG;
-  const int blocks = (s.T + tpb - 1) / tpb;
-  int xchunk = kGateLdsFloats / tpb;
-  if (xchunk > 256) xchunk = 256;
-  const size_t lds = (size_t)tpb * xchunk * sizeof(float);
   return traced(FLOWMOE_K_GATE, st, [&] {
-    hipLaunchKernelGGL(gate_topk_kernel<float>, dim3(blocks), dim3(kGateThreads), lds, st,
-                       (const float*)x, (const float*)w_gate, bias, logits, idx, w, s.T, s.M,
-                       s.E, s.k, EP, TPG, xchunk, full);
+#define FLOWMOE_GATE_F32(EPV)                                                                    \
+  case EPV: {                                                                                    \
+    constexpr int NT = EPV >= 4 ? 256 : 64 * EPV, TPB = NT / EPV * (EPV >= 16 ? 2 : 1);          \
+    hipLaunchKernelGGL(gate_topk_kernel<EPV>, dim3((s.T + TPB - 1) / TPB), dim3(NT), 0, st,      \
+                       (const float*)x, (const float*)w_gate, bias, logits, idx, w, s.T, s.M,    \
+                       s.E, s.k, full);                                                          \
+  } break
+    switch (EP) {
+      FLOWMOE_GATE_F32(1);
+      FLOWMOE_GATE_F32(2);
+      FLOWMOE_GATE_F32(4);
+      FLOWMOE_GATE_F32(8);
+      FLOWMOE_GATE_F32(16);
+      FLOWMOE_GATE_F32(32);
+      FLOWMOE_GATE_F32(64);
+    }
+#undef FLOWMOE_GATE_F32
   });
 }
 

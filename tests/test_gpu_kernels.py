@@ -765,3 +765,25 @@ def test_expert_ffn_f32_tiles(cnt, M, H, act):
                          (dw3, None if rdw3 is None else 2 * rdw3, "dw3")):
         if got is not None:
             assert_close(host(got), want, "f32", n, tol=1e-5)
+
+
+@pytest.mark.parametrize("T,M,E,k", [(65, 8, 1, 1), (64, 72, 2, 2), (129, 200, 3, 2), (33, 64, 8, 3),
+                                     (31, 136, 17, 4), (9, 1032, 60, 8)])
+def test_gate_f32_edges(T, M, E, k):
+    """The fp32 gate at one expert up to 64 lanes a token, token counts around a
+    block and reductions that are no multiple of its 64-deep chunks."""
+    need_gpu()
+    d = dev()
+    rng = np.random.default_rng(T)
+    x, wg = rng.standard_normal((T, M)).astype("f4"), (0.1 * rng.standard_normal((M, E))).astype("f4")
+    b = rng.standard_normal(E).astype("f4")
+    lg = torch.full((T, E), 7.0, device=d)
+    idx = torch.full((T, k), -5, dtype=torch.int32, device=d)
+    w = torch.full((T, k), 7.0, device=d)
+    s = _shape(T, M, 8, E, k, 0, "f32")
+    L.flowmoe_gate_topk(s, *(torch.from_numpy(v).to(d) for v in (x, wg, b)), lg, idx, w)
+    # M products of |x w| < 2, summed in fp32: 1e-5 of the largest logit
+    assert_close(host(lg), x.astype("f8") @ wg.astype("f8") + b, "f32", "logits", tol=1e-5)
+    ridx, rw = oracle.topk_select(host(lg), k)
+    assert np.array_equal(idx.cpu().numpy(), ridx)
+    assert_close(host(w), rw, "f32", "topk_w", tol=1e-5)
