@@ -8,14 +8,8 @@
 //   KSUM  C_e[Mdim x N]  = sum over rows r of e: A[r][.]^T B[r][.]  (wgrad):
 //         the reduction length K = counts[e] is ragged.
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16 over 256 x 256 tiles (gemm_wide_kernel) or,
-// where those are few, 256 x 128 tiles (gemm_narrow_kernel), the operands
-// streamed global -> LDS; a register-staged kernel takes row-mode reductions
-// that are no multiple of 32. That one: block tile BM x BN x 64, both operands
-// staged in LDS K-contiguous ([row][64] bf16 = 128 B per row) with the 16-byte
-// chunk index XOR-swizzled by (row & 7), double-buffered with register prefetch
-// of the next k-tile; operands contiguous along M or N are loaded as KT x 8
-// blocks and transposed in registers before the LDS write.
+// bf16 path: v_mfma_f32_32x32x16_bf16 over 256 x 256 or, where those are few, 256 x
+// 128 tiles, the operands streamed global -> LDS.
 // fp32 path: v_mfma_f32_32x32x2_f32 over 128-, 64- or 32-row x 128-column tiles,
 // the same modes and epilogues.
 #include <math.h>
@@ -109,10 +103,8 @@ __device__ __forceinline__ int seg_count(const GemmParams& p, int g, int e) {
 }
 
 // ---------------------------------------------------------------------------
-// bf16 MFMA kernel
+// bf16 kernels: tile order, LDS layout, epilogue
 // ---------------------------------------------------------------------------
-constexpr int BK = 64;
-
 // LDS tile layout: 128-byte rows (64 bf16 of K), 16-byte chunks XOR-swizzled
 // by (row / 2) % 8. A ds_read_b128 is serviced 16 lanes per cycle over 64
 // banks; the 16 consecutive rows it touches then fall into 16 distinct
@@ -120,102 +112,6 @@ constexpr int BK = 64;
 __device__ __forceinline__ int lds_off(int row, int chunk) {
   return row * 128 + (((chunk ^ (row >> 1)) & 7) << 4);
 }
-
-// pack 16-bit column `col` of two 8 x bf16 rows into one dword (lo = r0)
-__device__ __forceinline__ uint32_t pick2(const uint4& r0, const uint4& r1, int col) {
-  const uint32_t* a = reinterpret_cast<const uint32_t*>(&r0);
-  const uint32_t* b = reinterpret_cast<const uint32_t*>(&r1);
-  const uint32_t x = a[col >> 1], y = b[col >> 1];
-  return (col & 1) ? ((x >> 16) | (y & 0xFFFF0000u)) : ((x & 0xFFFFu) | (y << 16));
-}
-
-// K-contiguous tile loader: ROWS x BK tile in 16-byte chunks. Thread t owns
-// chunk c = t % 8 of rows r0 + p * NT/8 (r0 = t / 8), p < NP. Rows at or past
-// `lim` and chunks at or past K load zeros. Chunks at k >= ksplit come from
-// the second source at k - ksplit.
-template <int ROWS, int NT>
-struct KcLoader {
-  static constexpr int NP = ROWS * 8 / NT;
-  static constexpr int RSTEP = NT / 8;  // rows between a thread's chunks
-  const bf16_t* base0;  // row r0, k = 0
-  const bf16_t* base1;  // second source, row r0, k = 0
-  long rstride;         // elements between rows r0 + p*RSTEP and r0 + (p+1)*RSTEP
-  int lim, r0, c;
-  uint4 v[NP];
-  __device__ __forceinline__ void init(const bf16_t* b0, const bf16_t* b1, long ld, int limit) {
-    r0 = threadIdx.x >> 3;
-    c = threadIdx.x & 7;
-    base0 = b0 + (long)r0 * ld;
-    base1 = b1 + (long)r0 * ld;
-    rstride = (long)RSTEP * ld;
-    lim = limit;
-  }
-  __device__ __forceinline__ void load(int k0, int K, int ksplit) {
-    const int k = k0 + c * 8;
-    const bool second = k >= ksplit;
-    const bf16_t* b = second ? base1 + (k - ksplit) : base0 + k;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      if (r0 + p * RSTEP < lim && k < K)
-        v[p] = *reinterpret_cast<const uint4*>(b + p * rstride);
-      else
-        v[p] = make_uint4(0, 0, 0, 0);
-    }
-  }
-  __device__ __forceinline__ void store(char* lds) const {
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-      *reinterpret_cast<uint4*>(lds + lds_off(r0 + p * RSTEP, c)) = v[p];
-  }
-};
-
-// MN-contiguous tile loader: element (row i, k) at col + k*ld, where each
-// thread owns one group of 8 rows (g) and KT consecutive k (kg); the KT x 8
-// block is transposed in registers before the LDS write.
-template <int ROWS, int NT>
-struct MncLoader {
-  static constexpr int KT = ROWS * BK / (8 * NT);  // k rows per thread: 4 or 8
-  static constexpr int KG = BK / KT;                    // k groups per tile
-  const bf16_t* col;  // (k = 0, first row of my group)
-  long ld;
-  bool ok;
-  int kg, g;
-  uint4 v[KT];
-  __device__ __forceinline__ void load(int k0, int Klim) {
-    const bf16_t* b = col + (long)(k0 + kg * KT) * ld;
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      const int k = k0 + kg * KT + j;
-      if (ok && k < Klim)
-        v[j] = *reinterpret_cast<const uint4*>(b + (long)j * ld);
-      else
-        v[j] = make_uint4(0, 0, 0, 0);
-    }
-  }
-  // Threads of odd groups store their rows in the order 1,0,3,2,..., so one
-  // store instruction writes rows of both parities (both halves of the banks).
-  __device__ __forceinline__ void store(char* lds) const {
-    const bool odd = g & 1;
-#pragma unroll
-    for (int ii = 0; ii < 8; ++ii) {
-      const int row = g * 8 + (ii ^ (int)odd);
-      if constexpr (KT == 8) {
-        uint4 a, b;  // column ii and column ii ^ 1 of the 8 x 8 block
-        a.x = pick2(v[0], v[1], ii);      b.x = pick2(v[0], v[1], ii ^ 1);
-        a.y = pick2(v[2], v[3], ii);      b.y = pick2(v[2], v[3], ii ^ 1);
-        a.z = pick2(v[4], v[5], ii);      b.z = pick2(v[4], v[5], ii ^ 1);
-        a.w = pick2(v[6], v[7], ii);      b.w = pick2(v[6], v[7], ii ^ 1);
-        *reinterpret_cast<uint4*>(lds + lds_off(row, kg)) = odd ? b : a;
-      } else {
-        uint2 a, b;
-        a.x = pick2(v[0], v[1], ii);      b.x = pick2(v[0], v[1], ii ^ 1);
-        a.y = pick2(v[2], v[3], ii);      b.y = pick2(v[2], v[3], ii ^ 1);
-        const int kin = kg * KT;  // element offset of my k group in the tile
-        *reinterpret_cast<uint2*>(lds + lds_off(row, kin >> 3) + ((kin & 7) << 1)) = odd ? b : a;
-      }
-    }
-  }
-};
 
 __device__ __forceinline__ float silu_f(float z) { return z * sigmoid_f(z); }
 
@@ -225,22 +121,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   const int q = nblocks >> 3, rem = nblocks & 7;
   const int x = bid & 7, i = bid >> 3;
   return x * q + (x < rem ? x : rem) + i;
-}
-
-// Weight-gradient tile vbid (after xcd_remap, so that each XCD takes a
-// contiguous range): expert e, then groups of 4 m tiles that walk the mtn x
-// ntn grid m tile fastest. The 32 tiles that an XCD runs at once are 4 m x 8
-// n tiles sharing 12 operand panels through its L2 (a walk along n alone
-// shares 33: 1 A and 32 B panels); on the large layer's weight gradients
-// that walk fetched ~12x their operands' bytes from HBM.
-__device__ __forceinline__ void ksum_tile(int vbid, int mtn, int ntn, int& e, int& mt, int& nt) {
-  constexpr int G = 4;
-  e = vbid / (mtn * ntn);
-  const int rem = vbid - e * (mtn * ntn);
-  const int g = rem / (G * ntn), rg = rem - g * (G * ntn);
-  const int gm = min(G, mtn - g * G);  // m tiles in this group
-  nt = rg / gm;
-  mt = g * G + (rg - nt * gm);
 }
 
 // Tile of dispatch position P (blocks go to the 8 XCDs round-robin: position
@@ -279,37 +159,33 @@ __device__ __forceinline__ void shared_block_tile(int P, int nrows, int ncols, i
   nt = cb * SB + lc;
 }
 
-// Epilogue shared by the bf16 kernels: the accumulators of wave (wm, wn)
-// of the tile (each WM x WN, acc[i][j][4*g + q] = C[row wm*WM + i*32 + lane%32]
-// [col wn*WN + j*32 + 8*g + 4*(lane/32) + q]; HALVES: row (i/2)*128 + wm*64 +
-// (i%2)*32 + .., col j*128 + wn*32 + ..) to global memory, staged
-// through LDS (smem: SMEM free bytes, at least (NT/64)*64*WN floats).
-template <int MODE, int EPI, int BM, int BN, int NT, int SMEM, int WM, int WN, bool HALVES = false>
-__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&acc)[WM / 32][WN / 32],
+// Epilogue of the bf16 kernel: the accumulators of wave (wm, wn) of the tile,
+// acc[i][j][4*g + q] = C[row (i/2)*128 + wm*64 + (i%2)*32 + lane%32]
+//                       [col j*128 + wn*32 + 8*g + 4*(lane/32) + q],
+// to global memory, staged through LDS (smem: SMEM free bytes).
+template <int MODE, int EPI, int BM, int SMEM, int WN>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&acc)[4][WN / 32],
                                               char* smem, int e, int mt, int n0, int row0,
                                               int rows_e, int cnt_e, int wm, int wn) {
-  constexpr int FM = WM / 32, FN = WN / 32;
+  constexpr int FM = 4, FN = WN / 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // acc[i][j][4*g + q] is C[row wm*WM + i*32 + lane%32]
-  //                        [col wn*WN + j*32 + 8*g + 4*(lane/32) + q], q = 0..3
   const int lrow = lane & 31, lcol = 4 * (lane >> 5);
   {
-    // The wave's WM x WN tile goes out 64 rows at a time through its own LDS
+    // The wave's 128 x WN tile goes out 64 rows at a time through its own LDS
     // region (fp32, 16-byte chunks XOR-swizzled by row), then each lane
     // writes 8 consecutive outputs of one row: full 128-byte lines (bf16
     // rows of the dispatched buffers, or fp32 rows of the weight gradients).
     // The main loop ended with a barrier, so the tile buffers are free.
-    static_assert(FM % 2 == 0, "staged epilogue works on 64-row halves");
     constexpr int SCH = WN / 4;  // 16-byte chunks per staged row
-    static_assert((NT / 64) * 64 * WN * 4 <= SMEM, "stage does not fit");
+    static_assert(8 * 64 * WN * 4 <= SMEM, "stage does not fit");
     float* stage = reinterpret_cast<float*>(smem) + wave * 64 * WN;
     bf16_t* C0 = static_cast<bf16_t*>(p.C0);
     bf16_t* C1 = static_cast<bf16_t*>(p.C1);
     const bf16_t* aux = static_cast<const bf16_t*>(p.aux);
-    auto sidx = [&](int r, int c4) { return r * WN + ((c4 ^ (r & (SCH - 1))) << 2); };
+    auto sidx = [&](int r, int c4) { return r * WN + ((c4 ^ ((SCH == 8 ? r >> 1 : r) & (SCH - 1))) << 2); };
     // tile row of row rr of 64-row half hf, and tile column of the wave's column c
-    auto tile_row = [&](int hf, int rr) { return HALVES ? hf * 128 + wm * 64 + rr : wm * WM + hf * 64 + rr; };
-    auto tile_col = [&](int c) { return HALVES ? (c >> 5) * 128 + wn * 32 + (c & 31) : wn * WN + c; };
+    auto tile_row = [&](int hf, int rr) { return hf * 128 + wm * 64 + rr; };
+    auto tile_col = [&](int c) { return (c >> 5) * 128 + wn * 32 + (c & 31); };
     // forward biases: a lane's items all lie in one 8-column group (the item
     // index is it * 64 + lane and 64 is a multiple of the groups per row), so
     // its 8 (dual: 2 x 8) bias values are loaded once, before any store (a
@@ -530,179 +406,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
   }
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI, int BM, int BN, int NT>
-__global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmParams p) {
-  constexpr int WGN = NT / 128;  // waves along N (two along M)
-  constexpr int WM = BM / 2, WN = BN / WGN;
-  constexpr int FM = WM / 32, FN = WN / 32;
-  static_assert(EPI != EPI_SWIGLU_FWD || (FN % 2) == 0, "dual forward needs W1/W3 column pairs");
-  __shared__ __attribute__((aligned(16))) char smem[2 * (BM + BN) * 128];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int vbid = xcd_remap(blockIdx.x, gridDim.x);
-
-  // ---- which tile --------------------------------------------------------
-  int e = 0, mt = 0, nt = 0, row0 = 0, rows_e = 0, cnt_e = 0;
-  if constexpr (MODE == MODE_ROWS) {
-    // column tiles fastest: concurrent blocks share the A rows of one tile
-    const int ntn = p.ntiles;
-    nt = vbid % ntn;
-    const int ml = vbid / ntn;
-    int acc_t = 0;
-    mt = -1;
-    for (e = 0; e < p.E; ++e) {
-      const int c = seg_count(p, 0, e);
-      const int r = p.padC ? p.padC : c;
-      const int te = (r + BM - 1) / BM;
-      if (ml < acc_t + te) {
-        mt = ml - acc_t;
-        rows_e = r;
-        cnt_e = c;
-        break;
-      }
-      acc_t += te;
-    }
-    if (mt < 0) return;
-    rows_e = clip_rows(seg_offset(p, 0, e), rows_e, p.rows_cap);
-    cnt_e = clip_rows(seg_offset(p, 0, e), cnt_e, p.rows_cap);
-    row0 = seg_offset(p, 0, e) + mt * BM;  // first global row of this tile
-  } else {
-    ksum_tile(vbid, (p.Mdim + BM - 1) / BM, (p.N + BN - 1) / BN, e, mt, nt);
-    cnt_e = clip_rows(seg_offset(p, 0, e), seg_count(p, 0, e), p.rows_cap);
-    row0 = seg_offset(p, 0, e);
-  }
-  constexpr int NCOLS = (EPI == EPI_SWIGLU_FWD) ? BN / 2 : BN;  // distinct output columns per tile
-  const int n0 = nt * NCOLS;
-
-  // ---- loaders -------------------------------------------------------------
-  const bf16_t* A = static_cast<const bf16_t*>(p.A);
-  const bf16_t* B0 = static_cast<const bf16_t*>(p.B0);
-  const bf16_t* B1 = static_cast<const bf16_t*>(p.B1);
-  int Kred;  // reduction length
-  if constexpr (MODE == MODE_ROWS) Kred = p.K; else Kred = cnt_e;
-
-  KcLoader<BM, NT> la;
-  MncLoader<BM, NT> lam;
-  if constexpr (A_KC) {  // ROWS: A rows are the expert's rows
-    const bf16_t* a0 = A + (long)row0 * p.lda;
-    la.init(a0, a0, p.lda, cnt_e - mt * BM);
-  } else {  // KSUM: A[i][k] = A[(row0 + k) * lda + m0 + i]
-    lam.kg = tid % MncLoader<BM, NT>::KG;
-    lam.g = tid / MncLoader<BM, NT>::KG;
-    const int i0 = mt * BM + lam.g * 8;
-    lam.ok = i0 < p.Mdim;
-    lam.ld = p.lda;
-    lam.col = A + (long)row0 * p.lda + i0;
-  }
-  KcLoader<BN, NT> lb;
-  MncLoader<BN, NT> lbm;
-  if constexpr (B_KC) {  // ROWS dgrad: B[k][n] at B + e*estride + n*ldb + k
-    const bf16_t* b0 = B0 + (long)e * p.b_estride + (long)n0 * p.ldb;
-    const bf16_t* b1 = (B1 != nullptr) ? B1 + (long)e * p.b_estride + (long)n0 * p.ldb : b0;
-    lb.init(b0, b1, p.ldb, p.N - n0);
-  } else {
-    lbm.kg = tid % MncLoader<BN, NT>::KG;
-    lbm.g = tid / MncLoader<BN, NT>::KG;
-    lbm.ld = p.ldb;
-    if constexpr (MODE == MODE_ROWS) {
-      const bf16_t* base = B0;
-      int n = n0 + lbm.g * 8;
-      if constexpr (EPI == EPI_SWIGLU_FWD) {
-        const int cc = lbm.g * 8;  // tile column: 32-column blocks alternate W1 / W3
-        base = ((cc >> 5) & 1) ? B1 : B0;
-        n = n0 + (cc >> 6) * 32 + (cc & 31);
-      }
-      lbm.ok = n < p.N;
-      lbm.col = base + (long)e * p.b_estride + n;
-    } else {  // KSUM: B[k][n] = B[(row0 + k) * ldb + n]
-      const int n = n0 + lbm.g * 8;
-      lbm.ok = n < p.N;
-      lbm.col = B0 + (long)row0 * p.ldb + n;
-    }
-  }
-
-  auto load_tiles = [&](int k0) {
-    if constexpr (A_KC) la.load(k0, Kred, 1 << 30); else lam.load(k0, Kred);
-    if constexpr (B_KC) lb.load(k0, Kred, p.ksplit); else lbm.load(k0, Kred);
-  };
-  auto store_tiles = [&](int buf) {
-    char* a_s = smem + buf * (BM + BN) * 128;
-    char* b_s = a_s + BM * 128;
-    if constexpr (A_KC) la.store(a_s); else lam.store(a_s);
-    if constexpr (B_KC) lb.store(b_s); else lbm.store(b_s);
-  };
-
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int nk = (Kred + BK - 1) / BK;
-  if (nk > 0) {
-    load_tiles(0);
-    store_tiles(0);
-    __syncthreads();
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    const bool more = kt + 1 < nk;
-    if (more) load_tiles((kt + 1) * BK);
-    const char* a_s = smem + (kt & 1) * (BM + BN) * 128;
-    const char* b_s = a_s + BM * 128;
-    // fragments of step kk+1 are read while the MFMAs of step kk run
-    bf16x8 af[2][FM], bfr[2][FN];
-    auto read_frags = [&](int kk, int set) {
-      const int ch = kk * 2 + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-        af[set][i] = *reinterpret_cast<const bf16x8*>(a_s + lds_off(wm * WM + i * 32 + (lane & 31), ch));
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        bfr[set][j] = *reinterpret_cast<const bf16x8*>(b_s + lds_off(wn * WN + j * 32 + (lane & 31), ch));
-    };
-    read_frags(0, 0);
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      if (kk + 1 < BK / 16) read_frags(kk + 1, (kk + 1) & 1);
-      // B as the first operand: the result tile is C^T, so each lane ends up
-      // with 4 consecutive output columns of one row
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i],
-                                                              acc[i][j], 0, 0, 0);
-    }
-    if (more) store_tiles((kt + 1) & 1);
-    __syncthreads();
-  }
-
-  gemm_epilogue<MODE, EPI, BM, BN, NT, (int)sizeof(smem), WM, WN>(p, acc, smem, e, mt, n0, row0, rows_e,
-                                                                   cnt_e, wm, wn);
-}
-
-// ---------------------------------------------------------------------------
-// bf16 kernel with direct-to-LDS operand streaming
-// ---------------------------------------------------------------------------
-// gemm_narrow_kernel: 256 x 128 block tile, BK = 32, a ring of 3 LDS stages (24
-// KB each: A then B). Operands go global -> LDS with bounds-checked
-// buffer_load_dwordx4 ... lds (no staging registers; reads past a buffer's range
-// return zeros, which masks ragged expert rows and the ragged reduction of the
-// weight gradients). Each wave load fills one 1 KB block of LDS in lane order;
-// the source chunk of each lane is chosen so the
-// block holds the swizzled layout:
-//   K-contiguous operand: [256 rows][32 k] (64 B rows), chunk c of row r at
-//     physical chunk c ^ ((r / 4) % 4); fragments via ds_read_b128.
-//   M/N-contiguous operand: panels of [32 k][PW cols] (PW*2 B rows), 16-byte
-//     chunk m of row k at m ^ (4 * (k % 4)); fragments via two
-//     ds_read_b64_tr_b16, which hand lane l' of each 16-lane group element
-//     l' % 4 of lane 4q + l'/4 in slot q: lanes aimed at rows k0 + s/4,
-//     columns c0 + 4 (s % 4) receive the K-contiguous 4-vectors the MFMA wants.
-// Requires the reduction length of the row mode to be a multiple of 32.
-constexpr int DBK = 32;
 constexpr int kRowGroup = 4;  // row tiles per group of the row-mode tile order
 
 template <int V>
@@ -842,398 +545,30 @@ __device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
   __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
 }
 
-__device__ __forceinline__ int kc_off(int row, int chunk) {
-  return row * 64 + (((chunk ^ (row >> 2)) & 3) << 4);
-}
-
-// K-contiguous fragment: row `row`, k16 step kk
-__device__ __forceinline__ bf16x8 frag_kc(const char* region, int row, int kk, int lane) {
-  return *reinterpret_cast<const bf16x8*>(region + kc_off(row, kk * 2 + (lane >> 5)));
-}
-
-// M/N-contiguous fragment of 32 columns starting at tile column cb
-template <int PW>
-__device__ __forceinline__ bf16x8 frag_mnc(const char* region, int cb, int kk, int lane) {
-  const int G = lane >> 4, sl = lane & 15;
-  const int col = cb + (G & 1) * 16 + 4 * (sl & 3);
-  const int pc = col % PW;
-  const char* pb = region + (col / PW) * (DBK * PW * 2);
-  v4i16 h[2];
-#pragma unroll
-  for (int ins = 0; ins < 2; ++ins) {
-    const int k = kk * 16 + (G >> 1) * 8 + 4 * ins + (sl >> 2);
-    const char* a = pb + k * (PW * 2) + ((((pc >> 3) ^ ((k & 3) << 2))) << 4) + ((pc & 7) << 1);
-    h[ins] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)a);
-  }
-  const v4i16 lo = h[0], hi = h[1];
-  const short __attribute__((ext_vector_type(8))) v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-template <int MODE, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(GemmParams p) {
-  // 4 waves of 128 x 64 accumulators, two along M and two along N, 3 stages of
-  // the k-tile ring: 72 KB of LDS, two blocks per CU
-  constexpr int BM = 256, BN = 128, NT = 256;
-  constexpr int WGM = 2, WGN = 2;
-  constexpr int NW = NT / 64;  // waves
-  constexpr int NST = 3;       // stages of the k-tile ring
-  constexpr int A_BYTES = BM * DBK * 2, STB = A_BYTES + BN * DBK * 2;  // bytes per stage
-  constexpr int BPA = (BM / 16) / NW, BPB = (BN / 16) / NW;  // 1 KB blocks per wave per stage
-  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
-  static_assert(EPI != EPI_SWIGLU_FWD, "the dual forward pairs 128-column W1 and W3 panels");
-  constexpr int PWB = BN;  // B panel width (M/N-contiguous B)
-  // the k-tile ring, reused by the epilogue's staging (64 fp32 rows per wave)
-  constexpr int SMEM = NST * STB > NW * 64 * WN * 4 ? NST * STB : NW * 64 * WN * 4;
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  // the LDS-DMA destinations in scalar registers: the ring's LDS address and
-  // the wave index (both wave-uniform)
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void_t*)smem);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-
-  // ---- which tile ----
-  int e = 0, mt = 0, nt = 0, row0 = 0, rows_e = 0, cnt_e = 0;
-  int seg_o = 0, seg_c = 0;  // KSUM: segment ranges, one lane per segment
-  if constexpr (MODE == MODE_ROWS) {
-    int off_e = 0;
-    if (!row_tile_of_block<BM>(p, blockIdx.x, e, mt, nt, rows_e, cnt_e, off_e)) return;
-    rows_e = clip_rows(off_e, rows_e, p.rows_cap);
-    cnt_e = clip_rows(off_e, cnt_e, p.rows_cap);
-    row0 = off_e + mt * BM;
-  } else {
-    // expert e's mtn x ntn tiles, walked in shared 16 x 16 blocks
-    const int mtn = (p.Mdim + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
-    e = blockIdx.x / (mtn * ntn);
-    shared_block_tile(blockIdx.x - e * (mtn * ntn), mtn, ntn, mt, nt);
-    // lane g holds segment g's first row and count of this expert (g < 64):
-    // every segment's range in one memory round trip
-    const int g = lane;
-    seg_o = g < p.nseg ? seg_offset(p, g, e) : 0;
-    seg_c = g < p.nseg ? seg_count(p, g, e) : 0;
-    row0 = __builtin_amdgcn_readlane(seg_o, 0);
-    cnt_e = clip_rows(row0, __builtin_amdgcn_readlane(seg_c, 0), p.rows_cap);
-  }
-  const int n0 = nt * BN;
-  const int Kred = (MODE == MODE_ROWS) ? p.K : cnt_e;
-  // a padding-only tile (padded layout) has nothing to reduce: zeros
-  int nk = (MODE == MODE_ROWS && cnt_e <= mt * BM) ? 0 : (Kred + DBK - 1) / DBK;
-
-  const bf16_t* A = static_cast<const bf16_t*>(p.A);
-  const bf16_t* B0 = static_cast<const bf16_t*>(p.B0);
-  const bf16_t* B1 = static_cast<const bf16_t*>(p.B1);
-
-  // ---- buffer resources and per-lane source offsets (bytes, k0 = 0) ----
-  // Each wave issues BPA A and BPB B block loads per stage: blocks wave + NW*i.
-  // An M/N-contiguous panel of PW columns holds 64 / (PW / 8) k-rows per
-  // block, 16-byte chunks XOR-swizzled by k-row.
-  auto mnc_off = [&](int b, int pw, long ld) {
-    const int cpr = pw / 8, kr = (64 / cpr) * b + lane / cpr;
-    const int cm = (lane % cpr) ^ ((kr & 3) << 2);
-    return (unsigned)(((long)kr * ld + cm * 8) * 2);
-  };
-  u32x4 ra, rb0, rb1;
-  unsigned aoff[BPA], boff[BPB];
-  int a_kstep, b_kstep;  // byte step per k-tile
-  if constexpr (A_KC) {  // rows of the expert: [rows][K]
-    const long valid = (long)(cnt_e - mt * BM) * p.lda;
-    ra = make_rsrc(A + (long)row0 * p.lda, valid * 2);
-#pragma unroll
-    for (int i = 0; i < BPA; ++i) {
-      const int b = wave + NW * i, row = 16 * b + (lane >> 2);
-      const int c = (lane & 3) ^ ((row >> 2) & 3);
-      aoff[i] = (unsigned)(((long)row * p.lda + c * 8) * 2);
-    }
-    a_kstep = DBK * 2;
-  } else {  // KSUM: element (m, r) at A + (row0 + r) * lda + m; one panel of 256
-    const int m0 = mt * BM;
-    ra = make_rsrc(A + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
-#pragma unroll
-    for (int i = 0; i < BPA; ++i) aoff[i] = mnc_off(wave + NW * i, 256, p.lda);
-    a_kstep = DBK * p.lda * 2;
-  }
-  if constexpr (B_KC) {  // rows n: [N][K] per expert; k >= ksplit from B1
-    const long valid = (long)(p.N - n0) * p.ldb;
-    rb0 = make_rsrc(B0 + (long)e * p.b_estride + (long)n0 * p.ldb, valid * 2);
-    rb1 = (B1 != nullptr) ? make_rsrc(B1 + (long)e * p.b_estride + (long)n0 * p.ldb, valid * 2) : rb0;
-#pragma unroll
-    for (int i = 0; i < BPB; ++i) {
-      const int b = wave + NW * i, row = 16 * b + (lane >> 2);
-      const int c = (lane & 3) ^ ((row >> 2) & 3);
-      boff[i] = (unsigned)(((long)row * p.ldb + c * 8) * 2);
-    }
-    b_kstep = DBK * 2;
-  } else if constexpr (MODE == MODE_ROWS) {  // weights [K][N] per expert
-    const long span = (long)p.K * p.ldb;
-    rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
-    rb1 = rb0;
-#pragma unroll
-    for (int i = 0; i < BPB; ++i) boff[i] = mnc_off(wave + NW * i, BN, p.ldb);
-    b_kstep = DBK * p.ldb * 2;
-  } else {  // KSUM: element (r, n) at B + (row0 + r) * ldb + n
-    rb0 = make_rsrc(B0 + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
-    rb1 = rb0;
-#pragma unroll
-    for (int i = 0; i < BPB; ++i) boff[i] = mnc_off(wave + NW * i, BN, p.ldb);
-    b_kstep = DBK * p.ldb * 2;
-  }
-
-  // KSUM: bind segment g (g >= 1) of the reduction: the expert's rows in the
-  // g-th chunk's buffers (same per-lane offsets and k steps)
-  auto bind_segment = [&](int g) {
-    if constexpr (MODE == MODE_KSUM) {
-      row0 = g < 64 ? __builtin_amdgcn_readlane(seg_o, g) : seg_offset(p, g, e);
-      cnt_e = clip_rows(row0, g < 64 ? __builtin_amdgcn_readlane(seg_c, g) : seg_count(p, g, e),
-                        p.rows_cap);
-      const bf16_t* Ag = A + g * p.a_sstride;
-      const bf16_t* Bg = B0 + g * p.b_sstride;
-      const int m0 = mt * BM;
-      ra = make_rsrc(Ag + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
-      rb0 = make_rsrc(Bg + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
-      rb1 = rb0;
-      nk = (cnt_e + DBK - 1) / DBK;
-    }
-  };
-
-  // Loads of k-tile kt into stage `stage`, in two parts: part 0 takes this
-  // wave's first ceil(n / 2) of its n blocks of each operand, part 1 the rest.
-  auto issue_part = [&](int kt, int stage, int q) {
-    const unsigned sa = lds0 + (unsigned)(stage * STB), sb = sa + A_BYTES;
-    const unsigned ka = (unsigned)kt * (unsigned)a_kstep;
-    constexpr int HA = (BPA + 1) / 2, HB = (BPB + 1) / 2;
-#pragma unroll
-    for (int i = q ? HA : 0; i < (q ? BPA : HA); ++i) dma16(ra, sa + (wave_s + NW * i) * 1024, aoff[i] + ka);
-#pragma unroll
-    for (int i = q ? HB : 0; i < (q ? BPB : HB); ++i) {
-      if constexpr (B_KC) {
-        const int k0 = kt * DBK;
-        const bool second = k0 >= p.ksplit;
-        const unsigned kb = (unsigned)((second ? k0 - p.ksplit : k0) * 2);
-        dma16(second ? rb1 : rb0, sb + (wave_s + NW * i) * 1024, boff[i] + kb);
-      } else {
-        const unsigned kb = (unsigned)kt * (unsigned)b_kstep;
-        dma16(rb0, sb + (wave_s + NW * i) * 1024, boff[i] + kb);
-      }
-    }
-  };
-  auto issue = [&](int kt, int stage) {
-    issue_part(kt, stage, 0);
-    issue_part(kt, stage, 1);
-  };
-
-  floatx16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // Ring of NST k-tiles: tile t lives in stage t % NST. Every wave loads its
-  // share of each tile; a barrier after a wave's own loads of tile t have
-  // landed (s_waitcnt vmcnt) makes the whole tile visible. Tile t's stage is
-  // refilled (tile t + NST) only after the barrier that follows every wave's
-  // last LDS read of tile t.
-  auto prologue = [&] {
-#pragma unroll
-    for (int s = 0; s < NST; ++s)
-      if (s < nk) issue(s, s);
-  };
-
-  // wait until this wave's loads of tile t have landed, given that the loads
-  // of tiles up to min(t + ahead, nk - 1) have been issued
-  constexpr int LPT = BPA + BPB;  // loads per wave per k-tile
-  auto wait_tile = [&](int t, int ahead) {
-    const int younger = min(ahead, nk - 1 - t);  // tiles issued after t
-    if (younger >= 3) wait_vm_lgkm0<3 * LPT>();
-    else if (younger == 2) wait_vm_lgkm0<2 * LPT>();
-    else if (younger == 1) wait_vm_lgkm0<LPT>();
-    else wait_vm_lgkm0<0>();
-  };
-  auto barrier = [] {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-
-  // The k loop for a wave whose first FML 32-row fragments hold live rows
-  // (FML = FM for every wave of a tile with 256 live rows; the short last
-  // tile of an expert skips the MFMAs and A reads of rows past its count).
-  auto k_loop = [&](auto fml_c) {
-    constexpr int FML = decltype(fml_c)::value;
-    // Fragments of one 16-deep k step; two sets so that the LDS reads of the
-    // next step are in flight while the MFMAs of the current one run.
-    bf16x8 af[2][FM], bfr[2][FN];
-    auto read_frags = [&](int stage, int kk, int set) {
-      if constexpr (FML > 0) {
-        const char* sa = smem + stage * STB;
-        const char* sb = sa + A_BYTES;
-#pragma unroll
-        for (int i = 0; i < FML; ++i) {
-          if constexpr (A_KC)
-            af[set][i] = frag_kc(sa, wm * WM + i * 32 + (lane & 31), kk, lane);
-          else
-            af[set][i] = frag_mnc<256>(sa, wm * WM + i * 32, kk, lane);
-        }
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (B_KC)
-            bfr[set][j] = frag_kc(sb, wn * WN + j * 32 + (lane & 31), kk, lane);
-          else
-            bfr[set][j] = frag_mnc<PWB>(sb, wn * WN + j * 32, kk, lane);
-        }
-      }
-    };
-    // LDS read instructions per fragment set (ds_read_b128 for a K-contiguous
-    // fragment, two ds_read_b64_tr_b16 for an M/N-contiguous one)
-    constexpr int NRD = FML == 0 ? 0 : FML * (A_KC ? 1 : 2) + FN * (B_KC ? 1 : 2);
-    constexpr int NMF = FML * FN;
-    auto mfma_rows = [&](int set, int i0, int i1) {
-#pragma unroll
-      for (int i = i0; i < i1; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i], acc[i][j], 0, 0, 0);
-    };
-    // One half k-step: the LDS reads of the next set interleaved with the
-    // first half of this set's MFMAs, then one part of a k-tile's loads (if
-    // any) between the two halves of the MFMAs, so that the memory pipe takes
-    // the loads a few at a time while the matrix pipe stays busy. The
-    // scheduling barriers keep the inline-asm loads where they are. A wave
-    // issues the second half of its MFMAs at raised priority: of the two
-    // waves of a SIMD the older one otherwise ran ahead and then waited at
-    // the k-tile barrier for a quarter of the loop while the other finished
-    // alone (large layer 32.0 -> 31.4 ms per step; raising it over both
-    // halves or the whole half step measured slower).
-    auto half_step = [&](int set, auto&& reads, auto&& loads) {
-      reads();
-      mfma_rows(set, 0, FML / 2);
-      if constexpr (NRD > 0) {
-#pragma unroll
-        for (int q = 0; q < NRD; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, (NMF / 2 + NRD - 1) / NRD, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NMF / 2, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      loads();
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_rows(set, FML / 2, FML);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-
-    if (nk > 0) {
-      wait_tile(0, NST - 1);
-      barrier();
-      read_frags(0, 0, 0);
-    }
-    // All tiles but the last: the barrier sits between the two k steps, so
-    // each half pairs the MFMAs of one step with the reads of the next.
-    // The loads of tile kt + NST go out in two parts: the first in the
-    // second half of iteration kt (its stage was freed by that iteration's
-    // barrier), the second in the first half of iteration kt + 1, both before
-    // the wait that needs them (iteration kt + NST - 1).
-    // Iteration kt of the ring. In the steady state (1 <= kt < nk - NST)
-    // every load exists and the wait always leaves the loads of NST - 2
-    // tiles in flight: that instance has no branches (a branch per
-    // iteration for the wait's count and the loads' bounds cost ~2% on the
-    // large layer).
-    auto iter = [&](int kt, auto steady_c) {
-      constexpr bool S = decltype(steady_c)::value == 1;
-      const int stage = kt % NST;
-      // step 1 of tile kt is read while step 0 runs; second part of tile kt + NST - 1
-      half_step(
-          0, [&] { read_frags(stage, 1, 1); },
-          [&] {
-            const int tl = kt + NST - 1;
-            if (S || (tl >= NST && tl < nk)) issue_part(tl, tl % NST, 1);
-          });
-      // this wave's reads of tile kt are done (lgkmcnt 0) and its loads of
-      // tile kt + 1 have landed; after the barrier every wave's have
-      if constexpr (S) wait_vm_lgkm0<(NST - 2) * LPT>();
-      else wait_tile(kt + 1, NST - 2);
-      barrier();
-      // step 0 of tile kt + 1 is read while step 1 of tile kt runs; first part
-      // of tile kt + NST into the stage tile kt leaves
-      half_step(
-          1, [&] { read_frags((kt + 1) % NST, 0, 0); },
-          [&] {
-            if (S || kt + NST < nk) issue_part(kt + NST, stage, 0);
-          });
-    };
-    int kt = 0;
-    if (nk > 1) iter(kt++, IntC<0>{});
-    for (; kt + NST < nk; ++kt) iter(kt, IntC<1>{});
-    for (; kt + 1 < nk; ++kt) iter(kt, IntC<0>{});
-    if (nk > 0) {
-      read_frags((nk - 1) % NST, 1, 1);
-      mfma_rows(0, 0, FML);
-      if constexpr (NRD > 0) {
-#pragma unroll
-        for (int q = 0; q < NRD; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one DS read
-          __builtin_amdgcn_sched_group_barrier(0x008, (NMF + NRD - 1) / NRD, 0);  // MFMAs
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NMF, 0);  // the rest of the MFMAs
-      }
-      mfma_rows(1, 0, FML);
-    }
-  };
-  if constexpr (MODE == MODE_KSUM) {
-    // every row of a weight-gradient tile is live; segments one after the
-    // other into the same accumulators, the ring drained between them
-    for (int g = 0; g < p.nseg; ++g) {
-      if (g > 0) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();  // all LDS reads of the last segment done before the refill
-        bind_segment(g);
-      }
-      prologue();
-      k_loop(IntC<FM>{});
-    }
-  } else {
-    prologue();
-    // live 32-row fragments of this wave (wave-uniform)
-    const int live = min(BM, max(0, cnt_e - mt * BM));
-    const int fml = __builtin_amdgcn_readfirstlane(min(FM, max(0, (live - wm * WM + 31) / 32)));
-    if (fml > FM / 2) k_loop(IntC<FM>{});
-    else if (fml > 0) k_loop(IntC<FM / 2>{});
-    else k_loop(IntC<0>{});
-  }
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();  // all LDS reads done before the epilogue reuses the stages
-  gemm_epilogue<MODE, EPI, BM, BN, NT, SMEM, WM, WN>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm,
-                                                     wn);
-}
-
 // ---------------------------------------------------------------------------
-// bf16 kernel, 256 x 256 tiles: two wave groups taking turns on the matrix pipes
+// bf16 kernel: two wave groups taking turns on the matrix pipes
 // ---------------------------------------------------------------------------
 // 8 waves, two along M (wm) and four along N (wn), one of each wm on every SIMD.
-// A k-tile is 64 deep and held as two 128-row A halves and two 128-column B
-// halves of 16 KB; a wave multiplies 64 rows of each A half by 32 columns of
-// each B half, one (A half, B half) pair a phase: 8 v_mfma_f32_32x32x16_bf16, 256
-// cycles of a matrix pipe. Phases of tile t: (A0, BX), (A0, BY), (A1, BY), (A1,
-// BX), X = t % 2, Y = 1 - X, so that the half a phase starts to use was read
-// from LDS one phase before and its registers were free by then.
+// A k-tile is 64 deep and held as two 128-row A halves and two (wide: 256 x 256
+// tiles) or one (narrow: 256 x 128) 128-column B halves of 16 KB; a wave
+// multiplies 64 rows of each A half by 32 columns of each B half, one (A half, B
+// half) pair a phase: 8 v_mfma_f32_32x32x16_bf16, 256 cycles of a matrix pipe.
+// Phases of wide tile t: (A0, BX), (A0, BY), (A1, BY), (A1, BX), X = t % 2, Y = 1 -
+// X, so that the half a phase starts to use was read from LDS one phase before and
+// its registers were free by then; of narrow tile t: (A0, B), (A1, B), tile t + 1's
+// B in the other of two register sets.
 //
-// A phase is a memory part (LDS reads of the next phase's half, two LDS-DMA
-// loads of a half of tile t + 2, the wait for the half that the next phase
-// reads), a barrier, the MFMAs, a barrier. The waves of wm = 1 run one part
-// behind those of wm = 0, so on every SIMD one wave's MFMAs run beside the
-// other's memory part, and no wave waits for its own reads or loads: the reads
-// have a whole part to arrive, the loads six phases (10 of a wave's loads, 80
-// KB a block, stay in flight). A half's LDS is refilled two phases after its
-// read, when the barriers between have ordered every wave's reads before it.
+// A phase is a memory part (LDS reads of the next phase's half, LDS-DMA loads of
+// a half of a later tile, the wait for the half that the next phase reads), a
+// barrier, the MFMAs, a barrier. The waves of wm = 1 run one part behind those of
+// wm = 0, so on every SIMD one wave's MFMAs run beside the other's memory part,
+// and no wave waits for its own reads or loads: the reads have a whole part to
+// arrive, the loads six phases (wide; four narrow), 80 KB a block staying in
+// flight. A half's LDS is refilled two phases after its read, when the barriers
+// between have ordered every wave's reads before it.
+//
+// The last tile of a reduction (of either part of a split one) may be ragged:
+// K-contiguous chunks past its length are masked to zeros.
 //
 // What it measured, and why 64 deep: 32-deep tiles (a four-stage ring, one
 // barrier a tile, reads interleaved with the MFMAs of the same wave) fetched the
@@ -1241,9 +576,15 @@ __global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(GemmParams p) {
 // busy 0.56-0.72 of the cycles; here it is 0.67-0.81 (SwiGLU experts of 16384
 // rows at M = 4096, H = 14336: W1|W3 forward 6.68 -> 5.99 ms, W2 forward 3.21 ->
 // 2.92, their dgrads 3.82 -> 3.24 and 7.08 -> 6.03, both weight gradients 9.33
-// -> 9.04). Power is what is left: the clock falls to 1.54-1.6 GHz as the pipes
-// get busier, and waiting for four more loads, issuing the loads first, or
-// raising the MFMAs' wave priority changed nothing (0.0 to 0.5% slower).
+// -> 9.04). What is left there is power and the L2 -> LDS stream (64 KB a tile at
+// about 26 bytes a cycle): the clock falls to 1.54-1.6 GHz as the pipes get
+// busier, and waiting for four more loads, issuing the loads first, or raising
+// the MFMAs' wave priority changed nothing (0.0 to 0.5% slower). Narrow tiles
+// need 48 KB for half the products; they replaced 4-wave ones of 32-deep tiles,
+// two blocks to a CU (16 experts of mostly few rows, N = 1024, K = 4096: 100 -> 73
+// us forward, 76 -> 59 dgrad) and a register-staged kernel for reductions that
+// are no multiple of 32 (8 experts of 750 rows, N = 1024, K = 2728: 108 -> 58 us;
+// K = 5456 in two parts: 183 -> 126).
 constexpr int WBK = 64;           // k depth of a tile
 constexpr int kHalf = 128 * WBK * 2;  // bytes of a half tile: 128 rows (or columns) x 64 k
 
@@ -1273,11 +614,15 @@ __device__ __forceinline__ bf16x8 half_frag(const char* h, int base, int i, int 
   }
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
-  constexpr int BM = 256, BN = 256;
+template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
+  constexpr int BM = 256, BN = NARROW ? 128 : 256;
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
-  constexpr int SMEM = 8 * kHalf;  // two k-tiles of two A and two B halves
+  static_assert(!DUAL || !NARROW, "the dual forward pairs 128-column W1 and W3 halves");
+  // k-tiles in LDS (stages), the halves of one (A0, A1, B0 and wide B1) and its bytes
+  constexpr int NST = NARROW ? 3 : 2, NB = NARROW ? 1 : 2, STB = (2 + NB) * kHalf;
+  constexpr int SMEM = 9 * kHalf;  // 144 KB
+  static_assert(NST * STB <= SMEM, "k-tiles do not fit");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1372,7 +717,8 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
   // range: they load zeros without traffic. The tile's byte offset stays in a
   // scalar register (opaque to the compiler, which would otherwise step a
   // vector register per load along the loop, and spill it).
-  auto issue = [&](u32x4 r, unsigned dst, unsigned voff, unsigned so, unsigned blk, bool kc, int lim) {
+  auto issue = [&](u32x4 r, unsigned dst, unsigned voff, unsigned so, unsigned blk, bool kc, int lim,
+                   bool both = true) {
     unsigned so2 = so + blk;
     asm("" : "+s"(so), "+s"(so2));
     unsigned o = voff + so, o2 = voff + so2;
@@ -1382,20 +728,19 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
       o2 = ok ? o2 : 0xFFFFFFF0u;
     }
     dma16(r, dst, o);
-    dma16(r, dst + 8192, o2);
+    if (both) dma16(r, dst + 8192, o2);
   };
-  auto issue_a = [&](int t, int h) {
-    const unsigned dst = lds0 + ((t & 1) << 16) + h * kHalf + wave * 1024;
+  auto issue_a_to = [&](int t, int h, unsigned dst, bool both) {
     if constexpr (A_KC) {
       const bool sec = t >= nk0;
       const int k0 = (sec ? t - nk0 : t) * WBK, lim = (sec ? p.K - p.ksplit : k_lim) - k0;
-      issue(ra, dst, aoff, (unsigned)((k0 + (sec ? p.ksplit : 0)) * 2) + h * a_half, a_blk, true, lim);
+      issue(ra, dst, aoff, (unsigned)((k0 + (sec ? p.ksplit : 0)) * 2) + h * a_half, a_blk, true, lim,
+            both);
     } else {
-      issue(ra, dst, aoff, (unsigned)t * a_kt + h * a_half, a_blk, false, 0);
+      issue(ra, dst, aoff, (unsigned)t * a_kt + h * a_half, a_blk, false, 0, both);
     }
   };
-  auto issue_b = [&](int t, int h) {
-    const unsigned dst = lds0 + ((t & 1) << 16) + (2 + h) * kHalf + wave * 1024;
+  auto issue_b_to = [&](int t, int h, unsigned dst) {
     if constexpr (B_KC) {
       const bool sec = t >= nk0;
       const int k0 = (sec ? t - nk0 : t) * WBK, lim = (sec ? p.K - p.ksplit : k_lim) - k0;
@@ -1404,12 +749,18 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
       issue((DUAL && h) ? rb1 : rb0, dst, boff, (unsigned)t * b_kt + h * b_half, b_blk, false, 0);
     }
   };
+  auto issue_a = [&](int t, int h, int stage) {
+    issue_a_to(t, h, lds0 + stage * STB + h * kHalf + wave * 1024, true);
+  };
+  auto issue_b = [&](int t, int h, int stage) {
+    issue_b_to(t, h, lds0 + stage * STB + (2 + h) * kHalf + wave * 1024);
+  };
 
-  floatx16 acc[4][2];
+  floatx16 acc[4][NB];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
@@ -1422,31 +773,31 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
   int abase = half_base(A_KC, wm * 64, lane), bbase = half_base(B_KC, wn * 32, lane);
   auto k_loop = [&](auto nh_c) {
     constexpr int NH = decltype(nh_c)::value;  // live A halves of this wave
-    bf16x8 af[2][2][4], bfr[2][4];  // [half][32-row block][k step], [half][k step]
+    // [half][32-row block][k step]; [half (wide) or tile parity (narrow)][k step]
+    bf16x8 af[2][2][4], bfr[2][4];
     // (the bases marked as changed: every XOR of them kept across the loop
     // would cost a register)
-    auto read_a = [&](int buf, int h) {
+    auto read_a = [&](int stage, int h) {
       if (h < NH) {
         asm("" : "+v"(abase));
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
           for (int i = 0; i < 2; ++i)
-            af[h][i][kk] = half_frag<A_KC>(smem + buf * 4 * kHalf + h * kHalf, abase, i, kk);
+            af[h][i][kk] = half_frag<A_KC>(smem + stage * STB + h * kHalf, abase, i, kk);
       }
     };
-    auto read_b = [&](int buf, int h) {
+    auto read_b = [&](int stage, int h, int set) {
       if (NH > 0) {
         asm("" : "+v"(bbase));
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-          bfr[h][kk] = half_frag<B_KC>(smem + buf * 4 * kHalf + (2 + h) * kHalf, bbase, 0, kk);
+          bfr[set][kk] = half_frag<B_KC>(smem + stage * STB + (2 + h) * kHalf, bbase, 0, kk);
       }
     };
-    auto phase = [&](auto&& mem, int ha, int hb) {
+    // one phase: mem (reads, loads, the wait), then A half ha times bfr[set] into column block j
+    auto phase = [&](auto&& mem, int ha, int set, int j) {
       mem();
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vm<10>();
       barrier();
       __builtin_amdgcn_sched_barrier(0);
       if (ha < NH) {
@@ -1454,33 +805,38 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
         for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
           for (int i = 0; i < 2; ++i)
-            acc[2 * ha + i][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                bfr[hb][kk], af[ha][i][kk], acc[2 * ha + i][hb], 0, 0, 0);
+            acc[2 * ha + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                bfr[set][kk], af[ha][i][kk], acc[2 * ha + i][j], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
       wait_lgkm0();
       barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto tile = [&](int t, auto par_c) {
-      constexpr int X = decltype(par_c)::value, Y = 1 - X;
-      phase([&] { read_b(X, Y); issue_a(t + 2, 0); }, 0, X);
-      phase([&] { read_a(X, 1); issue_b(t + 2, X); }, 0, Y);
-      phase([&] { read_a(Y, 0); issue_b(t + 2, Y); }, 1, Y);
-      phase([&] { read_b(Y, Y); issue_a(t + 2, 1); }, 1, X);
+    auto wait10 = [] {
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<10>();
     };
-    if (nk > 0) {
+    if (nk == 0) return;
+    if constexpr (!NARROW) {
+      auto tile = [&](int t, auto par_c) {
+        constexpr int X = decltype(par_c)::value, Y = 1 - X;  // X: this tile's stage
+        phase([&] { read_b(X, Y, Y); issue_a(t + 2, 0, X); wait10(); }, 0, X, X);
+        phase([&] { read_a(X, 1); issue_b(t + 2, X, X); wait10(); }, 0, Y, Y);
+        phase([&] { read_a(Y, 0); issue_b(t + 2, Y, X); wait10(); }, 1, Y, Y);
+        phase([&] { read_b(Y, Y, Y); issue_a(t + 2, 1, X); wait10(); }, 1, X, X);
+      };
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        issue_a(t, 0);
-        issue_b(t, t);
-        issue_b(t, 1 - t);
-        issue_a(t, 1);
+        issue_a(t, 0, t);
+        issue_b(t, t, t);
+        issue_b(t, 1 - t, t);
+        issue_a(t, 1, t);
       }
       wait_vm<10>();
       barrier();
       read_a(0, 0);
-      read_b(0, 0);
+      read_b(0, 0, 0);
       wait_lgkm0();
       barrier();
       if (wave >= 4) barrier();
@@ -1490,7 +846,115 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
         tile(t + 1, IntC<1>{});
         if (t + 2 >= nk) break;
       }
-      if (wave < 4) barrier();
+    } else {
+      int s0 = 0, s1 = 1, s2 = 2;  // stages of tiles t, t + 1, t + 2
+      auto tile = [&](int t, auto par_c) {
+        constexpr int X = decltype(par_c)::value;
+        phase(
+            [&] {
+              read_a(s0, 1);
+              issue_a(t + 2, 1, s2);
+              __builtin_amdgcn_sched_barrier(0);
+              wait_vm<8>();
+            },
+            0, X, 0);
+        phase([&] { read_a(s1, 0); read_b(s1, 0, 1 - X); issue_a(t + 3, 0, s0); issue_b(t + 3, 0, s0); wait10(); },
+              1, X, 0);
+        const int s = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = s;
+      };
+      issue_a(0, 0, 0);
+      issue_b(0, 0, 0);
+      issue_a(0, 1, 0);
+      issue_a(1, 0, 1);
+      issue_b(1, 0, 1);
+      issue_a(1, 1, 1);
+      issue_a(2, 0, 2);
+      issue_b(2, 0, 2);
+      wait_vm<10>();
+      barrier();
+      read_a(0, 0);
+      read_b(0, 0, 0);
+      wait_lgkm0();
+      barrier();
+      if (wave >= 4) barrier();
+      for (int t = 0;; t += 2) {
+        tile(t, IntC<0>{});
+        if (t + 1 >= nk) break;
+        tile(t + 1, IntC<1>{});
+        if (t + 2 >= nk) break;
+      }
+    }
+    if (wave < 4) barrier();
+  };
+  // A tile of at most LR live rows: the weights' stream bounds it, so the stages
+  // hold LR rows of A and the depth goes to B. One barrier a k-tile; tile t + 1's
+  // fragments are read while tile t's are multiplied, and tile t's stage is
+  // refilled with tile t + NS. 16 experts of 16 rows, N = 1024, K = 4096: 31 us, 134
+  // MB of weights at 4.3 TB/s; the fine layer's second row tiles and the
+  // balanced layer's light ones 1-6% of their launches faster than the phases.
+  auto light_loop = [&](auto lr_c) {
+    constexpr int LR = decltype(lr_c)::value;
+    constexpr int AB = LR * WBK * 2, LST = AB + NB * kHalf;  // bytes of A, of a stage
+    constexpr int NS = SMEM / LST, LPT = LR / 64 + 2 * NB;   // stages, loads a wave a tile
+    const bool act = wm * 64 < LR;  // (64 rows: the waves of wm = 0 multiply)
+    bf16x8 af[2][2][4], bfr[2][NB][4];  // [tile parity]
+    auto issue_tile = [&](int t, int stage) {
+      const unsigned st = lds0 + stage * LST + wave * 1024;
+      issue_a_to(t, 0, st, LR == 128);
+#pragma unroll
+      for (int h = 0; h < NB; ++h) issue_b_to(t, h, st + AB + h * kHalf);
+    };
+    auto read = [&](int stage, auto set_c) {
+      constexpr int set = decltype(set_c)::value;
+      if (!act) return;
+      asm("" : "+v"(abase), "+v"(bbase));
+      const char* sa = smem + stage * LST;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) af[set][i][kk] = half_frag<A_KC>(sa, abase, i, kk);
+#pragma unroll
+        for (int h = 0; h < NB; ++h) bfr[set][h][kk] = half_frag<B_KC>(sa + AB + h * kHalf, bbase, 0, kk);
+      }
+    };
+    if (nk == 0) return;
+#pragma unroll
+    for (int t = 0; t < NS; ++t) issue_tile(t, t);
+    wait_vm<(NS - 1) * LPT>();
+    barrier();
+    read(0, IntC<0>{});
+    wait_lgkm0();
+    int s0 = 0;  // tile t's stage
+    auto tile = [&](int t, auto set_c) {
+      constexpr int set = decltype(set_c)::value;
+      wait_vm<(NS - 2) * LPT>();
+      barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      const int s1 = s0 + 1 == NS ? 0 : s0 + 1;
+      issue_tile(t + NS, s0);
+      read(s1, IntC<1 - set>{});
+      if (act) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int h = 0; h < NB; ++h)
+              acc[i][h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][h][kk], af[set][i][kk],
+                                                                  acc[i][h], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      wait_lgkm0();
+      s0 = s1;
+    };
+    for (int t = 0;; t += 2) {
+      tile(t, IntC<0>{});
+      if (t + 1 >= nk) break;
+      tile(t + 1, IntC<1>{});
+      if (t + 2 >= nk) break;
     }
   };
   if constexpr (MODE == MODE_KSUM) {
@@ -1504,17 +968,18 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmParams p) {
       k_loop(IntC<2>{});
     }
   } else {
-    // live 64-row halves of this wave (wave-uniform): rows wm * 64 and 128 + wm * 64
-    const int live = cnt_e - mt * BM - wm * 64;
-    if (live > 128) k_loop(IntC<2>{});
-    else if (live > 0) k_loop(IntC<1>{});
-    else k_loop(IntC<0>{});
+    // light tiles, else live 64-row halves of this wave (wave-uniform): rows
+    // wm * 64 .. and 128 + wm * 64 ..
+    const int live = cnt_e - mt * BM;
+    if (live <= 64) light_loop(IntC<64>{});
+    else if (live <= 128) light_loop(IntC<128>{});
+    else if (live > 128 + wm * 64) k_loop(IntC<2>{});
+    else k_loop(IntC<1>{});
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();  // all loads landed and LDS reads done before the epilogue reuses the stages
-  gemm_epilogue<MODE, EPI, BM, BN, 512, SMEM, 128, 64, true>(p, acc, smem, e, mt, n0, row0, rows_e,
-                                                              cnt_e, wm, wn);
+  gemm_epilogue<MODE, EPI, BM, SMEM, 32 * NB>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm, wn);
 }
 
 // ---------------------------------------------------------------------------
@@ -1893,32 +1358,17 @@ GemmParams base_params(const Shape& s, const int32_t* counts, const int32_t* off
   return p;
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI, int BM, int BN, int NT>
-hipError_t run_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
-  long blocks;
-  if (MODE == MODE_ROWS) {
-    const int ncols = (EPI == EPI_SWIGLU_FWD) ? BN / 2 : BN;
-    p.mt_bound = rows_tiles_bound(s, BM);
-    p.ntiles = (p.N + ncols - 1) / ncols;
-    blocks = (long)p.mt_bound * p.ntiles;
-  } else {
-    blocks = (long)s.E * ((p.Mdim + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-  }
-  if (blocks == 0) return hipSuccess;
-  return traced(kind, st, [&] {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MODE, A_KC, B_KC, EPI, BM, BN, NT>),
-                       dim3((unsigned)blocks), dim3(NT), 0, st, p);
-  });
-}
-
-// Tile shape of the streaming kernel: 256 x 256 unless those tiles would
-// cover the launch in at most 1.25 rounds of the CUs, then 256 x 128.
+// Tile shape of the bf16 kernel: 256 x 256, or 256 x 128 where at most 160 wide
+// tiles would leave the CUs idle: at 128 wide tiles (4096 x 1024 x 3072 and the
+// like) 24 against 28 us and at 192 34 against 44 in favour of the narrow and
+// the wide ones.
 constexpr int kCUs = 256;
+constexpr int kNarrowMax = 160;
 std::atomic<int> g_tiles{FLOWMOE_TILES_AUTO};
 std::atomic<int> g_tile_order{FLOWMOE_TILE_ORDER_AUTO};
 
 template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW>
-hipError_t launch_dma(int kind, const Shape& s, GemmParams p, hipStream_t st) {
+hipError_t launch_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   constexpr int BN = NARROW ? 128 : 256;
   long blocks;
   if (MODE == MODE_ROWS) {
@@ -1943,41 +1393,26 @@ hipError_t launch_dma(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   }
   if (blocks == 0) return hipSuccess;
   return traced(kind, st, [&] {
-    if constexpr (NARROW)
-      hipLaunchKernelGGL((gemm_narrow_kernel<MODE, A_KC, B_KC, EPI>), dim3((unsigned)blocks),
-                         dim3(256), 0, st, p);
-    else
-      hipLaunchKernelGGL((gemm_wide_kernel<MODE, A_KC, B_KC, EPI>), dim3((unsigned)blocks),
-                         dim3(512), 0, st, p);
+    hipLaunchKernelGGL((gemm_bf16_kernel<MODE, A_KC, B_KC, EPI, NARROW>), dim3((unsigned)blocks),
+                       dim3(512), 0, st, p);
   });
 }
 
 template <int MODE, bool A_KC, bool B_KC, int EPI>
-hipError_t run_dma(int kind, const Shape& s, GemmParams p, hipStream_t st) {
+hipError_t run_gemm_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
+  if (MODE == MODE_KSUM && p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
   if constexpr (EPI == EPI_SWIGLU_FWD) {
-    return launch_dma<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
+    return launch_bf16<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
   } else {
     // wide tiles the launch would have (row mode: the live rows' tiles)
     const long rt = (MODE == MODE_ROWS) ? (s.rows + 255) / 256 : (long)s.E * ((p.Mdim + 255) / 256);
     const long wide = rt * ((p.N + 255) / 256);
     const int tiles = g_tiles.load(std::memory_order_relaxed);
     const bool narrow = tiles == FLOWMOE_TILES_NARROW ||
-                        (tiles == FLOWMOE_TILES_AUTO && wide <= kCUs + kCUs / 4);
-    if (narrow) return launch_dma<MODE, A_KC, B_KC, EPI, true>(kind, s, p, st);
-    return launch_dma<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
+                        (tiles == FLOWMOE_TILES_AUTO && wide <= kNarrowMax);
+    if (narrow) return launch_bf16<MODE, A_KC, B_KC, EPI, true>(kind, s, p, st);
+    return launch_bf16<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
   }
-}
-
-// The streaming kernel needs the row-mode reduction length (and a K split)
-// to be a multiple of its 32-deep k-tile; otherwise the register-staged
-// kernel runs.
-template <int MODE, bool A_KC, bool B_KC, int EPI>
-hipError_t run_gemm_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
-  if (MODE == MODE_KSUM && p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
-  const bool dma_ok = MODE == MODE_KSUM ||
-                      (p.K % DBK == 0 && (p.ksplit >= p.K || p.ksplit % DBK == 0));
-  if (dma_ok) return run_dma<MODE, A_KC, B_KC, EPI>(kind, s, p, st);
-  return run_bf16<MODE, A_KC, B_KC, EPI, 256, 256, 512>(kind, s, p, st);
 }
 
 template <int MODE, bool B_KC, int EPI, int FM>
@@ -2048,7 +1483,7 @@ hipError_t launch_gate_dw_gemm(const void* x, int T, int M, const void* d, int N
   // 256 x 256 tiles whatever the grid: these launches are bound by reading
   // x once, and the 8-wave tile's deeper ring (4 stages against 3) keeps
   // more of it in flight (the narrow tile took 1.2-1.7x as long)
-  return launch_dma<MODE_KSUM, false, false, EPI_GATE_DW, false>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
+  return launch_bf16<MODE_KSUM, false, false, EPI_GATE_DW, false>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
 }
 
 hipError_t launch_gate_dx_gemm(const void* dlhl, int T, int K, const void* wstack, int M,

@@ -33,8 +33,8 @@ import re
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 GEMM_SOURCES = ("csrc/gemm.hip", "csrc/common.hpp")
-GEMM_KERNEL = ("gemm_wide_kernel", "gemm_narrow_kernel")
-GATE_GEMM = ", 6>"  # epilogue 6: the gate backward's dW_g partials, not an expert GEMM
+GEMM_KERNEL = "gemm_bf16_kernel"
+GATE_GEMM = ", 6, "  # epilogue 6: the gate backward's dW_g partials, not an expert GEMM
 
 
 def expert_gemm(name: str) -> bool:
@@ -120,7 +120,7 @@ def cmd_traffic(a) -> None:
         for nm, k in kernels.items():
             lines.append(f"| `{nm}` | {k['dispatches']} | {k['fetch_bytes'] / 2**20:.1f} | "
                          f"{k['write_bytes'] / 2**20:.1f} |")
-        lines += ["", f"Expert GEMMs ({', '.join(GEMM_KERNEL)}), average over their {n} launches: "
+        lines += ["", f"Expert GEMMs ({GEMM_KERNEL}), average over their {n} launches: "
                       f"{res['gemm_bytes_per_launch'] / 2**20:.1f} MiB of HBM traffic per launch."]
         open(a.md, "w").write("\n".join(lines) + "\n")
 

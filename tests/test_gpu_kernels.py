@@ -787,3 +787,53 @@ def test_gate_f32_edges(T, M, E, k):
     ridx, rw = oracle.topk_select(host(lg), k)
     assert np.array_equal(idx.cpu().numpy(), ridx)
     assert_close(host(w), rw, "f32", "topk_w", tol=1e-5)
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("M,H", [(72, 136), (136, 72), (320, 200), (8, 448)])
+@pytest.mark.parametrize("layout", ["packed", "padded"])
+def test_expert_ffn_bf16_row_classes(M, H, act, layout, gemm_tiles):
+    """bf16 experts whose row tiles are of every class the kernel tells apart (at
+    most 64 and 128 live rows, one or both halves live in either wave row, full,
+    a second tile) and whose reductions end anywhere in a 64-deep k-tile (one to
+    five of them; in two parts for SwiGLU's dgrad): against the oracle, and the
+    two tile shapes bit-identical."""
+    need_gpu()
+    d = dev()
+    cnt = np.array([0, 1, 63, 64, 65, 128, 129, 192, 193, 256, 257, 385])
+    E, T, C = len(cnt), int(cnt.sum()), 390
+    rt = oracle.route(np.repeat(np.arange(E), cnt)[:, None], E, C, layout)
+    inp = make_inputs(get_config("balanced", T=T, M=M, H=H, E=E, k=1, act=act, seed=13))
+    x64, dy64 = (oracle.dispatch(as_f64(inp[n]), rt["row_src"], 1) for n in ("x", "dy"))
+    x, dy = (torch.from_numpy(v).to(d).bfloat16() for v in (x64, dy64))
+    w = {n: to_torch(inp[n], d) for n in ("w1", "w3", "w2")}
+    w64 = [None if inp[n] is None else as_f64(inp[n]) for n in ("w1", "w3", "w2")]
+    counts, offsets = (torch.from_numpy(rt[n].astype(np.int32)).to(d) for n in ("counts", "offsets"))
+    rows, HW = rt["rows"], 2 * H if act == "swiglu" else H
+    s = _shape(T, M, H, E, 1, C, "bf16", act, layout)
+    nws = L.flowmoe_workspace_bytes(s, L.WS_FFN_BWD)
+    ws = torch.empty(nws, dtype=torch.uint8, device=d)
+    got = {}
+    for tiles in ("wide", "narrow"):
+        gemm_tiles(tiles)
+        o = {n: torch.full((rows, c), 5.0, dtype=torch.bfloat16, device=d)
+             for n, c in (("h", HW), ("a", H), ("y", M), ("dx", M))}
+        o.update(dw1=torch.full((E, M, H), 9.0, device=d), dw2=torch.full((E, H, M), 9.0, device=d),
+                 dw3=torch.full((E, M, H), 9.0, device=d) if act == "swiglu" else None)
+        L.flowmoe_expert_ffn(s, x, counts, offsets, w["w1"], w["w3"], w["w2"], o["h"], o["a"], o["y"])
+        L.flowmoe_expert_ffn_bwd(s, dy, x, o["h"], o["a"], counts, offsets, w["w1"], w["w3"], w["w2"],
+                                 o["dx"], o["dw1"], o["dw3"], o["dw2"], 0, ws, nws)
+        got[tiles] = o
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(x64, rt["counts"], rt["offsets"], *w64, act)
+    rdx, rdw1, rdw3, rdw2 = oracle.expert_ffn_bwd(dy64, x64, ref, rt["counts"], rt["offsets"], *w64,
+                                                  act)[:4]
+    want = dict(h=ref["h1"] if act == "gelu" else np.concatenate([ref["h1"], ref["h3"]], axis=1),
+                a=ref["a"], y=ref["y_disp"], dx=rdx, dw1=rdw1, dw2=rdw2, dw3=rdw3)
+    nl = rows if layout == "padded" else T
+    for n, t in got["wide"].items():
+        if t is None:
+            continue
+        assert torch.equal(t, got["narrow"][n]), n
+        g = host(t)
+        assert_close(g[:nl] if t.dim() == 2 else g, want[n][:nl] if t.dim() == 2 else want[n], "bf16", n)
