@@ -159,253 +159,6 @@ __device__ __forceinline__ void shared_block_tile(int P, int nrows, int ncols, i
   nt = cb * SB + lc;
 }
 
-// Epilogue of the bf16 kernel: the accumulators of wave (wm, wn) of the tile,
-// acc[i][j][4*g + q] = C[row (i/2)*128 + wm*64 + (i%2)*32 + lane%32]
-//                       [col j*128 + wn*32 + 8*g + 4*(lane/32) + q],
-// to global memory, staged through LDS (smem: SMEM free bytes).
-template <int MODE, int EPI, int BM, int SMEM, int WN>
-__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&acc)[4][WN / 32],
-                                              char* smem, int e, int mt, int n0, int row0,
-                                              int rows_e, int cnt_e, int wm, int wn) {
-  constexpr int FM = 4, FN = WN / 32;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lrow = lane & 31, lcol = 4 * (lane >> 5);
-  {
-    // The wave's 128 x WN tile goes out 64 rows at a time through its own LDS
-    // region (fp32, 16-byte chunks XOR-swizzled by row), then each lane
-    // writes 8 consecutive outputs of one row: full 128-byte lines (bf16
-    // rows of the dispatched buffers, or fp32 rows of the weight gradients).
-    // The main loop ended with a barrier, so the tile buffers are free.
-    constexpr int SCH = WN / 4;  // 16-byte chunks per staged row
-    static_assert(8 * 64 * WN * 4 <= SMEM, "stage does not fit");
-    float* stage = reinterpret_cast<float*>(smem) + wave * 64 * WN;
-    bf16_t* C0 = static_cast<bf16_t*>(p.C0);
-    bf16_t* C1 = static_cast<bf16_t*>(p.C1);
-    const bf16_t* aux = static_cast<const bf16_t*>(p.aux);
-    auto sidx = [&](int r, int c4) { return r * WN + ((c4 ^ ((SCH == 8 ? r >> 1 : r) & (SCH - 1))) << 2); };
-    // tile row of row rr of 64-row half hf, and tile column of the wave's column c
-    auto tile_row = [&](int hf, int rr) { return hf * 128 + wm * 64 + rr; };
-    auto tile_col = [&](int c) { return (c >> 5) * 128 + wn * 32 + (c & 31); };
-    // forward biases: a lane's items all lie in one 8-column group (the item
-    // index is it * 64 + lane and 64 is a multiple of the groups per row), so
-    // its 8 (dual: 2 x 8) bias values are loaded once, before any store (a
-    // wait for a load issued after stores would wait for those stores too)
-    constexpr bool BIASED = MODE == MODE_ROWS && (EPI == EPI_STORE || EPI == EPI_GELU_FWD ||
-                                                  EPI == EPI_SWIGLU_FWD);
-    float bias0[8], bias1[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) bias0[q] = bias1[q] = 0.f;
-    if constexpr (BIASED) {
-      if (p.bias0 != nullptr || p.bias1 != nullptr) {
-        int n;
-        if constexpr (EPI == EPI_SWIGLU_FWD) {
-          constexpr int G8 = WN / 16;
-          static_assert(64 % G8 == 0, "one column group per lane");
-          const int c8 = lane % G8;
-          n = n0 + wn * (WN / 2) + (c8 >> 2) * 32 + (c8 & 3) * 8;
-        } else {
-          constexpr int G8 = WN / 8;
-          static_assert(64 % G8 == 0, "one column group per lane");
-          n = n0 + tile_col((lane % G8) * 8);
-        }
-        if (n < p.N) {
-          if (p.bias0 != nullptr) load8(p.bias0 + (long)e * p.bias_estride + n, bias0);
-          if (p.bias1 != nullptr) load8(p.bias1 + (long)e * p.bias_estride + n, bias1);
-        }
-      }
-    }
-#pragma unroll
-    for (int hf = 0; hf < FM / 2; ++hf) {
-      // activation-backward epilogues read the saved pre-activations: all of
-      // this half's loads go out before the staging, and none waits behind
-      // an output store (one memory round trip per half, not one per item)
-      constexpr bool AUXB = MODE == MODE_ROWS &&
-                            (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD || EPI == EPI_ADD);
-      constexpr int AG8 = WN / 8, APER = AUXB ? AG8 : 1;
-      Raw8b hr[APER], h3r[APER];
-      if constexpr (AUXB) {
-#pragma unroll
-        for (int it = 0; it < APER; ++it) {
-          const int item = it * 64 + lane;
-          const int rr = item / AG8, c8 = item % AG8;
-          const int ti = tile_row(hf, rr);
-          const int n = n0 + tile_col(c8 * 8);
-          const bool ok = mt * BM + ti < rows_e && n < p.N;
-          const long off = ok ? (long)(row0 + ti) * p.ldaux + n : 0;  // (clamped: every load issued)
-          hr[it] = raw8_load(aux + off);
-          if constexpr (EPI == EPI_SWIGLU_BWD) h3r[it] = raw8_load(aux + off + (ok ? p.Hh : 0));
-        }
-      }
-#pragma unroll
-      for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const int r = i2 * 32 + lrow, c4 = (j * 32 + 8 * gq + lcol) >> 2;
-            const floatx16& a = acc[hf * 2 + i2][j];
-            *reinterpret_cast<float4*>(stage + sidx(r, c4)) =
-                make_float4(a[4 * gq], a[4 * gq + 1], a[4 * gq + 2], a[4 * gq + 3]);
-          }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      auto read8 = [&](int r, int c8, float v[8]) {
-        const float4 lo = *reinterpret_cast<const float4*>(stage + sidx(r, 2 * c8));
-        const float4 hi = *reinterpret_cast<const float4*>(stage + sidx(r, 2 * c8 + 1));
-        v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
-        v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-      };
-      if constexpr (EPI == EPI_SWIGLU_FWD) {
-        // column pairs (W1, W3) of 32 each: WN/2 distinct outputs per row
-        constexpr int G8 = WN / 16;        // 8-column groups of distinct outputs per row
-        constexpr int PER = 64 * G8 / 64;  // items per lane
-#pragma unroll
-        for (int it = 0; it < PER; ++it) {
-          const int item = it * 64 + lane;
-          const int rr = item / G8, c8 = item % G8;  // c8: 8-group among the distinct columns
-          const int jp = c8 >> 2, cin = (c8 & 3) * 8;  // pair and offset inside its 32
-          const int ti = tile_row(hf, rr);
-          const int li = mt * BM + ti;
-          const int n = n0 + wn * (WN / 2) + jp * 32 + cin;
-          if (li >= rows_e || n >= p.N) continue;
-          const bool data = li < cnt_e;
-          float h1[8], h3[8], a[8];
-          read8(rr, (jp * 64 + cin) >> 3, h1);
-          read8(rr, (jp * 64 + 32 + cin) >> 3, h3);
-          if (data) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              h1[q] += bias0[q];
-              h3[q] += bias1[q];
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            if (!data) h1[q] = h3[q] = 0.f;
-            a[q] = silu_f(h1[q]) * h3[q];
-          }
-          const long g = row0 + ti;
-          store8(C0 + g * p.ldc + n, h1);
-          store8(C0 + g * p.ldc + p.Hh + n, h3);
-          store8(C1 + g * p.ldc1 + n, a);
-        }
-      } else if constexpr (MODE == MODE_KSUM) {  // fp32 weight gradient, C0 | C1 split at nsplit
-        // 16-byte items of 4 columns, WN / 4 to a staged row: a row's WN * 4
-        // bytes are written by consecutive lanes, so every store instruction
-        // writes whole 128-byte lines (of 64 / (WN / 4) rows); items of 8
-        // columns had left a 16-byte gap between the lanes of each store
-        constexpr int G4 = WN / 4;
-        constexpr int PER = 64 * G4 / 64;
-        constexpr int PB = PER >= 8 ? 8 : PER;  // items per batch of accumulation loads
-        float* D0 = static_cast<float*>(p.C0);
-        float* D1 = static_cast<float*>(p.C1);
-        auto dst_of = [&](int it, bool& ok) {
-          const int item = it * 64 + lane;
-          const int rr = item / G4, c4 = item % G4;
-          const int m = mt * BM + tile_row(hf, rr);
-          const int n = n0 + tile_col(c4 * 4);
-          ok = m < p.Mdim && n < p.N;  // N and nsplit are multiples of 8
-          return (n < p.nsplit) ? D0 + (long)e * p.c_estride + (long)m * p.ldc + n
-                                : D1 + (long)e * p.c_estride + (long)m * p.ldc + (n - p.nsplit);
-        };
-#pragma unroll
-        for (int b0 = 0; b0 < PER; b0 += PB) {
-          // accumulation: the batch's old values are all loaded before any
-          // store (from clamped addresses), one memory round trip per batch
-          float4 old[PB];
-          if (p.accumulate) {
-#pragma unroll
-            for (int i = 0; i < PB; ++i) {
-              bool ok;
-              float* d = dst_of(b0 + i, ok);
-              old[i] = *reinterpret_cast<const float4*>(ok ? d : D0);
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < PB; ++i) {
-            const int it = b0 + i;
-            bool ok;
-            float* dst = dst_of(it, ok);
-            if (!ok) continue;
-            const int item = it * 64 + lane;
-            float4 v = *reinterpret_cast<const float4*>(stage + sidx(item / G4, item % G4));
-            if (p.accumulate) {
-              v.x += old[i].x;
-              v.y += old[i].y;
-              v.z += old[i].z;
-              v.w += old[i].w;
-            }
-            *reinterpret_cast<float4*>(dst) = v;
-          }
-        }
-      } else {
-        constexpr int G8 = WN / 8;
-        constexpr int PER = 64 * G8 / 64;
-#pragma unroll
-        for (int it = 0; it < PER; ++it) {
-          const int item = it * 64 + lane;
-          const int rr = item / G8, c8 = item % G8;
-          const int ti = tile_row(hf, rr);
-          const int li = mt * BM + ti;
-          const int n = n0 + tile_col(c8 * 8);
-          if (li >= rows_e || n >= p.N) continue;
-          const bool data = li < cnt_e;
-          float v[8];
-          read8(rr, c8, v);
-          if (!data) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = 0.f;
-          }
-          if constexpr (EPI == EPI_STORE || EPI == EPI_GELU_FWD) {
-            if (data) {
-#pragma unroll
-              for (int q = 0; q < 8; ++q) v[q] += bias0[q];
-            }
-          }
-          const long g = row0 + ti;
-          if constexpr (EPI == EPI_STORE) {
-            store8(C0 + g * p.ldc + n, v);
-          } else if constexpr (EPI == EPI_ADD) {
-            float o[8];
-            raw8_f32(hr[it], o);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] += o[q];
-            store8(C0 + g * p.ldc + n, v);
-          } else if constexpr (EPI == EPI_GELU_FWD) {
-            float a[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) a[q] = gelu_f(v[q]);
-            store8(C0 + g * p.ldc + n, v);
-            store8(C1 + g * p.ldc1 + n, a);
-          } else if constexpr (EPI == EPI_GELU_BWD) {
-            float h[8];
-            raw8_f32(hr[it], h);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] *= gelu_grad_f(h[q]);
-            store8(C0 + g * p.ldc + n, v);
-          } else if constexpr (EPI == EPI_SWIGLU_BWD) {
-            float h1[8], h3[8], d3[8];
-            raw8_f32(hr[it], h1);
-            raw8_f32(h3r[it], h3);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float sg = sigmoid_f(h1[q]);
-              d3[q] = v[q] * h1[q] * sg;
-              v[q] = v[q] * h3[q] * sg * (1.f + h1[q] * (1.f - sg));
-            }
-            store8(C0 + g * p.ldc + n, v);
-            store8(C0 + g * p.ldc + p.Hh + n, d3);
-          }
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  }
-}
-
 constexpr int kRowGroup = 4;  // row tiles per group of the row-mode tile order
 
 template <int V>
@@ -543,6 +296,192 @@ __device__ __forceinline__ void wait_vm() {  // at most N vector-memory operatio
 }
 __device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
   __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+}
+
+// Epilogue of the bf16 kernel: the accumulators of wave (wm, wn) of the tile,
+// acc[i][j][4*g + q] = C[row (i/2)*128 + wm*64 + (i%2)*32 + lane%32]
+//                       [col j*128 + wn*32 + 8*g + 4*(lane/32) + q],
+// to global memory, 128 rows at a time through LDS (smem: 128 x 128 NB floats,
+// 16-byte chunks XOR-swizzled by row): all waves stage, then wave w writes rows
+// 16 w .. 16 w + 15 whole, consecutive lanes taking consecutive 16 bytes of a
+// row's 512 (bf16) or 1024 (fp32). A wave that stored its own 64 columns wrote
+// pieces of 64 or 128 bytes (weight gradients of a skewed layer's 16 experts, M =
+// 1024, H = 4096: 69 -> 63 us). nhf: 128-row halves to write.
+template <int MODE, int EPI, int BM, int NB>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&acc)[4][NB],
+                                              char* smem, int e, int mt, int n0, int row0,
+                                              int rows_e, int cnt_e, int wm, int wn, int nhf) {
+  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
+  constexpr int BN = 128 * NB;
+  // items of a row: 8 outputs (dual: of each of h1, h3 and a), or 4 fp32 ones
+  constexpr int IPR = DUAL ? 16 : MODE == MODE_KSUM ? BN / 4 : BN / 8;
+  constexpr int PER = 16 * IPR / 64;  // items a lane and half; all of one column group
+  static_assert(64 % IPR == 0, "one column group per lane");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lrow = lane & 31, lcol = 4 * (lane >> 5);
+  const int cg = lane % IPR, r_first = wave * 16 + lane / IPR;  // item it: row r_first + it * RSTEP
+  constexpr int RSTEP = 64 / IPR;
+  float* stage = reinterpret_cast<float*>(smem);
+  auto sidx = [&](int r, int c4) { return r * BN + ((c4 ^ (r & 15)) << 2); };
+  auto lds_barrier = [] {  // (LDS only: stores to global memory stay in flight)
+    wait_lgkm0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  bf16_t* C0 = static_cast<bf16_t*>(p.C0);
+  bf16_t* C1 = static_cast<bf16_t*>(p.C1);
+  const bf16_t* aux = static_cast<const bf16_t*>(p.aux);
+  const int n = n0 + cg * (MODE == MODE_KSUM ? 4 : 8);
+  const bool n_ok = n < p.N;  // (N and nsplit are multiples of 8)
+  // forward biases: a lane's 8 (dual: 2 x 8) values, loaded once, before any
+  // store (a wait for a load issued after stores would wait for those too)
+  constexpr bool BIASED = MODE == MODE_ROWS && (EPI == EPI_STORE || EPI == EPI_GELU_FWD || DUAL);
+  float bias0[8], bias1[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) bias0[q] = bias1[q] = 0.f;
+  if constexpr (BIASED) {
+    if (n_ok) {
+      if (p.bias0 != nullptr) load8(p.bias0 + (long)e * p.bias_estride + n, bias0);
+      if (p.bias1 != nullptr) load8(p.bias1 + (long)e * p.bias_estride + n, bias1);
+    }
+  }
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    if (hf >= nhf) break;
+    // activation-backward epilogues read the saved pre-activations: all of
+    // this half's loads go out before the staging, and none waits behind
+    // an output store (one memory round trip per half, not one per item)
+    constexpr bool AUXB = MODE == MODE_ROWS &&
+                          (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD || EPI == EPI_ADD);
+    Raw8b hr[AUXB ? PER : 1], h3r[AUXB ? PER : 1];
+    if constexpr (AUXB) {
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int ti = hf * 128 + r_first + it * RSTEP;
+        const bool ok = mt * BM + ti < rows_e && n_ok;
+        const long off = ok ? (long)(row0 + ti) * p.ldaux + n : 0;  // (clamped: every load issued)
+        hr[it] = raw8_load(aux + off);
+        if constexpr (EPI == EPI_SWIGLU_BWD) h3r[it] = raw8_load(aux + off + (ok ? p.Hh : 0));
+      }
+    }
+    if (hf > 0) lds_barrier();  // the first half's rows are read
+#pragma unroll
+    for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const floatx16& a = acc[hf * 2 + i2][j];
+          *reinterpret_cast<float4*>(
+              stage + sidx(wm * 64 + i2 * 32 + lrow, (j * 128 + wn * 32 + 8 * gq + lcol) >> 2)) =
+              make_float4(a[4 * gq], a[4 * gq + 1], a[4 * gq + 2], a[4 * gq + 3]);
+        }
+    lds_barrier();
+    auto read8 = [&](int r, int c8, float v[8]) {
+      const float4 lo = *reinterpret_cast<const float4*>(stage + sidx(r, 2 * c8));
+      const float4 hi = *reinterpret_cast<const float4*>(stage + sidx(r, 2 * c8 + 1));
+      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+      v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+    };
+    if constexpr (MODE == MODE_KSUM) {  // fp32 weight gradient, C0 | C1 split at nsplit
+      constexpr int PB = PER >= 8 ? 8 : PER;  // items per batch of accumulation loads
+      float* D0 = static_cast<float*>(p.C0);
+      float* D1 = static_cast<float*>(p.C1);
+      float* col = (n < p.nsplit ? D0 + n : D1 + (n - p.nsplit)) + (long)e * p.c_estride;
+#pragma unroll
+      for (int b0 = 0; b0 < PER; b0 += PB) {
+        // accumulation: the batch's old values are all loaded before any
+        // store (from clamped addresses), one memory round trip per batch
+        float4 old[PB];
+        if (p.accumulate) {
+#pragma unroll
+          for (int i = 0; i < PB; ++i) {
+            const int m = mt * BM + hf * 128 + r_first + (b0 + i) * RSTEP;
+            old[i] = *reinterpret_cast<const float4*>(m < p.Mdim && n_ok ? col + (long)m * p.ldc : D0);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+          const int rr = r_first + (b0 + i) * RSTEP, m = mt * BM + hf * 128 + rr;
+          if (m >= p.Mdim || !n_ok) continue;
+          float4 v = *reinterpret_cast<const float4*>(stage + sidx(rr, cg));
+          if (p.accumulate) {
+            v.x += old[i].x;
+            v.y += old[i].y;
+            v.z += old[i].z;
+            v.w += old[i].w;
+          }
+          *reinterpret_cast<float4*>(col + (long)m * p.ldc) = v;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int rr = r_first + it * RSTEP, ti = hf * 128 + rr;
+        const int li = mt * BM + ti;
+        if (li >= rows_e || !n_ok) continue;
+        const bool data = li < cnt_e;
+        const long g = row0 + ti;
+        float v[8];
+        read8(rr, cg, v);
+        if (!data) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = 0.f;
+        }
+        if constexpr (BIASED) {
+          if (data) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += bias0[q];
+          }
+        }
+        if constexpr (DUAL) {
+          float h3[8], a[8];
+          read8(rr, 16 + cg, h3);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            h3[q] = data ? h3[q] + bias1[q] : 0.f;
+            a[q] = silu_f(v[q]) * h3[q];
+          }
+          store8(C0 + g * p.ldc + n, v);
+          store8(C0 + g * p.ldc + p.Hh + n, h3);
+          store8(C1 + g * p.ldc1 + n, a);
+        } else if constexpr (EPI == EPI_STORE) {
+          store8(C0 + g * p.ldc + n, v);
+        } else if constexpr (EPI == EPI_ADD) {
+          float o[8];
+          raw8_f32(hr[it], o);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] += o[q];
+          store8(C0 + g * p.ldc + n, v);
+        } else if constexpr (EPI == EPI_GELU_FWD) {
+          float a[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) a[q] = gelu_f(v[q]);
+          store8(C0 + g * p.ldc + n, v);
+          store8(C1 + g * p.ldc1 + n, a);
+        } else if constexpr (EPI == EPI_GELU_BWD) {
+          float h[8];
+          raw8_f32(hr[it], h);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] *= gelu_grad_f(h[q]);
+          store8(C0 + g * p.ldc + n, v);
+        } else if constexpr (EPI == EPI_SWIGLU_BWD) {
+          float h1[8], h3[8], d3[8];
+          raw8_f32(hr[it], h1);
+          raw8_f32(h3r[it], h3);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const float sg = sigmoid_f(h1[q]);
+            d3[q] = v[q] * h1[q] * sg;
+            v[q] = v[q] * h3[q] * sg * (1.f + h1[q] * (1.f - sg));
+          }
+          store8(C0 + g * p.ldc + n, v);
+          store8(C0 + g * p.ldc + p.Hh + n, d3);
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -957,8 +896,37 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
       if (t + 2 >= nk) break;
     }
   };
+  // Weight gradient of an expert of few rows: every k-tile fits a stage, so all
+  // are loaded at once and each wave multiplies them with no barrier between.
+  auto short_loop = [&] {
+    for (int t = 0; t < nk; ++t) {
+      issue_a(t, 0, t);
+      issue_b(t, 0, t);
+      if constexpr (!NARROW) issue_b(t, 1, t);
+      issue_a(t, 1, t);
+    }
+    wait_vm<0>();
+    barrier();
+    for (int t = 0; t < nk; ++t) {
+      const char* st = smem + t * STB;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        bf16x8 bq[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) bq[j] = half_frag<B_KC>(st + (2 + j) * kHalf, bbase, 0, kk);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bf16x8 aq = half_frag<A_KC>(st + (i >> 1) * kHalf, abase, i & 1, kk);
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[j], aq, acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  };
   if constexpr (MODE == MODE_KSUM) {
-    for (int g = 0; g < p.nseg; ++g) {
+    if (p.nseg == 1 && nk <= NST) short_loop();
+    else for (int g = 0; g < p.nseg; ++g) {
       if (g > 0) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0);
@@ -979,7 +947,9 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();  // all loads landed and LDS reads done before the epilogue reuses the stages
-  gemm_epilogue<MODE, EPI, BM, SMEM, 32 * NB>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm, wn);
+  const int rows_t = MODE == MODE_ROWS ? rows_e - mt * BM : p.Mdim - mt * BM;
+  gemm_epilogue<MODE, EPI, BM, NB>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm, wn,
+                                   rows_t > 128 ? 2 : 1);
 }
 
 // ---------------------------------------------------------------------------
