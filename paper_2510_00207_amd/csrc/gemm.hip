@@ -1223,15 +1223,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
   }
 }
 
-// Bias gradients of the experts: per-expert column sums,
-// out[e][c] (+)= sum over expert e's rows r of src[r][c], over nseg row
-// segments (the chunks of a layer call: segment g's rows of expert e are
-// counts[g * E + e] rows from offsets[g * (E + 1) + e] of src + g * seg_stride)
-// in segment order; columns at or past nsplit go to out1[e][c - nsplit]
-// (SwiGLU's dH3 half), a null output is skipped. Block (512-column block,
-// expert): 64 lanes of 8 columns, wave w summing the rows w, w + 4, ... of
-// each segment in order (four rows in flight per lane), then the four
-// waves' sums added in wave order: deterministic.
 // C (+)= the S partial sums of P (S x n4 float4), added in split order
 __global__ __launch_bounds__(256) void sum_splits_kernel(const float4* __restrict__ P, int S,
                                                          long n4, float4* __restrict__ C,
@@ -1249,15 +1240,28 @@ __global__ __launch_bounds__(256) void sum_splits_kernel(const float4* __restric
   }
 }
 
+// Bias gradients of the experts: per-expert column sums,
+// out[e][c] (+)= sum over expert e's rows r of src[r][c], over nseg row
+// segments (the chunks of a layer call: segment g's rows of expert e are
+// counts[g * E + e] rows from offsets[g * (E + 1) + e] of src + g * seg_stride)
+// in segment order; columns at or past nsplit go to out1[e][c - nsplit]
+// (SwiGLU's dH3 half), a null output is skipped. Memory bounds it (src is read
+// once), so the grid is made of narrow blocks: 64 columns of one expert, 8 lanes
+// of 8 columns by 32 row lanes, row lane w summing the rows w, w + 32, ... in
+// order (four in flight), then the 32 sums added in a fixed order. Blocks of
+// 512 columns and 4 row lanes had left most of the CUs idle (8 experts of 750
+// rows, 1024 and 5456 columns: 64 -> 32 us for the two; 32 fp32 experts of 256 rows,
+// 512 and 1024 columns: 26 -> 18 us).
 template <typename TE>
 __global__ __launch_bounds__(256) void bias_grad_kernel(
     const TE* __restrict__ src, long ld, long seg_stride, const int32_t* __restrict__ counts,
     const int32_t* __restrict__ offsets, int E, int nseg, long rows_cap, int ncols, int nsplit,
     float* __restrict__ out0, float* __restrict__ out1, int accumulate) {
-  __shared__ float part[4][512];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int RL = 32;
+  __shared__ float part[RL][64], sum4[4][64];
+  const int tid = threadIdx.x, cl = tid & 7, w = tid >> 3;
   const int e = blockIdx.y;
-  const int c0 = blockIdx.x * 512 + lane * 8;  // ncols is a multiple of 8
+  const int c0 = blockIdx.x * 64 + cl * 8;  // ncols is a multiple of 8
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   auto add = [&](const auto& raw) {
     float v[8];
@@ -1271,38 +1275,35 @@ __global__ __launch_bounds__(256) void bias_grad_kernel(
       const int n = clip_rows(off, counts[g * E + e], rows_cap);
       const TE* base = src + g * seg_stride + off * ld + c0;
       int r = w;
-      for (; r + 12 < n; r += 16) {
+      for (; r + 3 * RL < n; r += 4 * RL) {
         const auto a0 = raw8_load(base + (long)r * ld);
-        const auto a1 = raw8_load(base + (long)(r + 4) * ld);
-        const auto a2 = raw8_load(base + (long)(r + 8) * ld);
-        const auto a3 = raw8_load(base + (long)(r + 12) * ld);
+        const auto a1 = raw8_load(base + (long)(r + RL) * ld);
+        const auto a2 = raw8_load(base + (long)(r + 2 * RL) * ld);
+        const auto a3 = raw8_load(base + (long)(r + 3 * RL) * ld);
         add(a0);
         add(a1);
         add(a2);
         add(a3);
       }
-      for (; r < n; r += 4) add(raw8_load(base + (long)r * ld));
+      for (; r < n; r += RL) add(raw8_load(base + (long)r * ld));
     }
   }
 #pragma unroll
-  for (int q = 0; q < 8; ++q) part[w][lane * 8 + q] = acc[q];
+  for (int q = 0; q < 8; ++q) part[w][cl * 8 + q] = acc[q];
   __syncthreads();
-  if (w == 0 && c0 < ncols) {
-    float* dst = c0 < nsplit ? out0 : out1;
+  const int col = tid & 63, g4 = tid >> 6;
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < RL / 4; ++i) s += part[g4 * (RL / 4) + i][col];
+  sum4[g4][col] = s;
+  __syncthreads();
+  const int c = blockIdx.x * 64 + col;
+  if (tid < 64 && c < ncols) {
+    float* dst = c < nsplit ? out0 : out1;
     if (dst == nullptr) return;
-    dst += c0 < nsplit ? (long)e * nsplit + c0 : (long)e * (ncols - nsplit) + (c0 - nsplit);
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      v[q] = ((part[0][lane * 8 + q] + part[1][lane * 8 + q]) + part[2][lane * 8 + q]) +
-             part[3][lane * 8 + q];
-    if (accumulate) {
-      float o[8];
-      load8(dst, o);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] += o[q];
-    }
-    store8(dst, v);
+    dst += c < nsplit ? (long)e * nsplit + c : (long)e * (ncols - nsplit) + (c - nsplit);
+    const float v = ((sum4[0][col] + sum4[1][col]) + sum4[2][col]) + sum4[3][col];
+    *dst = accumulate ? *dst + v : v;
   }
 }
 
@@ -1694,7 +1695,7 @@ hipError_t launch_expert_bias_grad(const Shape& s, int R, const void* dy_disp, c
   const long rows = s.rows;
   auto run = [&](const void* src, int ld, int ncols, int nsplit, float* o0, float* o1) {
     return traced(FLOWMOE_K_BIAS_GRAD, st, [&] {
-      const dim3 grid((unsigned)((ncols + 511) / 512), (unsigned)s.E);
+      const dim3 grid((unsigned)((ncols + 63) / 64), (unsigned)s.E);
       if (s.dtype == FLOWMOE_BF16)
         hipLaunchKernelGGL(bias_grad_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)src,
                            (long)ld, rows * ld, counts, offsets, s.E, R, rows, ncols, nsplit, o0, o1,
