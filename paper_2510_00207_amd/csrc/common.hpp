@@ -169,6 +169,100 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 __device__ __forceinline__ float sigmoid_f(float z) { return rcp_f(1.0f + __expf(-z)); }
 
 // ---------------------------------------------------------------------------
+// global -> LDS loads (LDS-DMA)
+// ---------------------------------------------------------------------------
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+// LDS byte address of a shared array, in a scalar register
+__device__ __forceinline__ unsigned lds_base(char* smem) {
+  return __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void_t*)smem);
+}
+
+// Raw buffer descriptor (stride 0, byte offsets) whose range check covers
+// `bytes` from `base`: loads past it return zeros.
+__device__ __forceinline__ u32x4 make_rsrc(const void* base, long bytes) {
+  const unsigned long a = reinterpret_cast<unsigned long>(base);
+  const unsigned n = bytes <= 0 ? 0u : (bytes > 0x7FFFFFFFL ? 0x7FFFFFFFu : (unsigned)bytes);
+  u32x4 d;
+  d.x = __builtin_amdgcn_readfirstlane((unsigned)a);
+  d.y = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
+  d.z = __builtin_amdgcn_readfirstlane(n);
+  d.w = 0x00020000u;
+  return d;
+}
+
+// One wave: 64 x 16 bytes from the buffer (per-lane byte offset voff) into
+// the 1 KB LDS block at LDS byte address m0v (wave-uniform, computed in
+// scalar registers: a vector-to-scalar move per load had put a dependent
+// chain in front of every load), lane-ordered. Issued as inline assembly so
+// that the compiler does not pair it with the LDS reads of other stages: the
+// kernel orders them itself with s_waitcnt vmcnt and barriers.
+__device__ __forceinline__ void dma16(u32x4 d, unsigned m0v, unsigned voff) {
+  // the descriptor is wave-uniform; say so, so that it sits in scalar registers
+  d.x = __builtin_amdgcn_readfirstlane(d.x);
+  d.y = __builtin_amdgcn_readfirstlane(d.y);
+  d.z = __builtin_amdgcn_readfirstlane(d.z);
+  d.w = __builtin_amdgcn_readfirstlane(d.w);
+  unsigned saved;  // m0 is reserved: keep the compiler's value intact
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\t"
+      "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(voff), "s"(d), "s"(m0v)
+      : "memory");
+}
+
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+}
+// N such loads of one buffer in a row, N = 1, 2 or 4, into LDS blocks STEP bytes
+// apart (one save of m0, one scalar add a load)
+template <int N, int STEP>
+__device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned (&voff)[N]) {
+  unsigned saved;
+  if constexpr (N == 1)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\t"
+        "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "v"(voff[0]), "s"(d), "s"(m0v)
+        : "memory");
+  else if constexpr (N == 2)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\t"
+        "buffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %5\n\t"
+        "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "v"(voff[0]), "v"(voff[1]), "s"(d), "s"(m0v), "i"(STEP)
+        : "memory", "scc");
+  else
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %6\n\t"
+        "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
+        "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
+        "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
+        "buffer_load_dwordx4 %4, %5, 0 offen lds\n\ts_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(d), "s"(m0v), "i"(STEP)
+        : "memory", "scc");
+}
+
+// barrier that orders LDS accesses only (loads from and stores to global memory
+// stay in flight)
+__device__ __forceinline__ void lds_barrier() {
+  wait_lgkm0();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 struct Shape {

@@ -244,60 +244,6 @@ __host__ __device__ constexpr long row_mode_blocks(long tile_bound) { return 8 *
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16_t;
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// Raw buffer descriptor (stride 0, byte offsets) whose range check covers
-// `bytes` from `base`: loads past it return zeros.
-__device__ __forceinline__ u32x4 make_rsrc(const void* base, long bytes) {
-  const unsigned long a = reinterpret_cast<unsigned long>(base);
-  const unsigned n = bytes <= 0 ? 0u : (bytes > 0x7FFFFFFFL ? 0x7FFFFFFFu : (unsigned)bytes);
-  u32x4 d;
-  d.x = __builtin_amdgcn_readfirstlane((unsigned)a);
-  d.y = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xFFFFu);
-  d.z = __builtin_amdgcn_readfirstlane(n);
-  d.w = 0x00020000u;
-  return d;
-}
-
-// One wave: 64 x 16 bytes from the buffer (per-lane byte offset voff) into
-// the 1 KB LDS block at LDS byte address m0v (wave-uniform, computed in
-// scalar registers: a vector-to-scalar move per load had put a dependent
-// chain in front of every load), lane-ordered. Issued as inline assembly so
-// that the compiler does not pair it with the LDS reads of other stages: the
-// kernel orders them itself with s_waitcnt vmcnt and barriers.
-__device__ __forceinline__ void dma16(u32x4 d, unsigned m0v, unsigned voff) {
-  // the descriptor is wave-uniform; say so, so that it sits in scalar registers
-  d.x = __builtin_amdgcn_readfirstlane(d.x);
-  d.y = __builtin_amdgcn_readfirstlane(d.y);
-  d.z = __builtin_amdgcn_readfirstlane(d.z);
-  d.w = __builtin_amdgcn_readfirstlane(d.w);
-  unsigned saved;  // m0 is reserved: keep the compiler's value intact
-  asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\t"
-      "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(voff), "s"(d), "s"(m0v)
-      : "memory");
-}
-
-
-// wait until at most n vector-memory operations and no LDS operation of this
-// wave are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vm_lgkm0() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-}
-
 // Epilogue of the bf16 kernel: the accumulators of wave (wm, wn) of the tile,
 // acc[i][j][4*g + q] = C[row (i/2)*128 + wm*64 + (i%2)*32 + lane%32]
 //                       [col j*128 + wn*32 + 8*g + 4*(lane/32) + q],
@@ -323,12 +269,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
   constexpr int RSTEP = 64 / IPR;
   float* stage = reinterpret_cast<float*>(smem);
   auto sidx = [&](int r, int c4) { return r * BN + ((c4 ^ (r & 15)) << 2); };
-  auto lds_barrier = [] {  // (LDS only: stores to global memory stay in flight)
-    wait_lgkm0();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
   bf16_t* C0 = static_cast<bf16_t*>(p.C0);
   bf16_t* C1 = static_cast<bf16_t*>(p.C1);
   const bf16_t* aux = static_cast<const bf16_t*>(p.aux);
@@ -567,7 +507,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void_t*)smem);
+  const unsigned lds0 = lds_base(smem);
 
   // ---- which tile ----
   int e = 0, mt = 0, nt = 0, row0 = 0, rows_e = 0, cnt_e = 0;
