@@ -160,41 +160,6 @@ __device__ __forceinline__ void store_cols(bf16_t* dst, const floatx16& a, int h
   }
 }
 
-// ROWS-row K and V tiles of one (sequence, head), double-buffered through
-// registers: every thread moves ROWS * D / 2048 16-byte chunks of each per tile
-template <int D, int ROWS = 64, int NT = 256>
-struct KVTiles {
-  static constexpr int CPR = D / 8;             // 16-byte chunks per row
-  static constexpr int TB = ROWS * D * 2;       // bytes of one tile
-  static constexpr int TOT = ROWS * CPR;        // chunks per tile
-  static constexpr int LD = (TOT + NT - 1) / NT; // chunks per thread per tile
-  u32x4 rk[LD], rv[LD];
-  __device__ __forceinline__ void load(const bf16_t* Kg, const bf16_t* Vg, long ld, int key0, int N,
-                                       int tid) {
-#pragma unroll
-    for (int u = 0; u < LD; ++u) {
-      const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR, key = key0 + r;
-      if (key < N && idx < TOT) {
-        rk[u] = *reinterpret_cast<const u32x4*>(Kg + key * ld + 8 * c);
-        rv[u] = *reinterpret_cast<const u32x4*>(Vg + key * ld + 8 * c);
-      } else {
-        rk[u] = u32x4{0, 0, 0, 0};
-        rv[u] = u32x4{0, 0, 0, 0};
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char* tk, char* tv, int tid) {
-#pragma unroll
-    for (int u = 0; u < LD; ++u) {
-      const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR;
-      if (TOT % NT == 0 || idx < TOT) {
-        *reinterpret_cast<u32x4*>(tk + toff<D>(r, c)) = rk[u];
-        *reinterpret_cast<u32x4*>(tv + toff<D>(r, c)) = rv[u];
-      }
-    }
-  }
-};
-
 // One operand's ROWS-row tiles of a (sequence, head) by LDS-DMA, in the layout
 // above: wave w of NW fills 1 KB blocks w, w + NW, ... (64 / CPR rows each), every
 // lane fetching the chunk that belongs at its place. Rows at or past N (every
@@ -243,7 +208,7 @@ __device__ __forceinline__ float pair_sum(float x) {
 // shortest tiles first, so that a CU's two blocks have complementary work
 // (ranks u and nt - 1 - u) instead of ranks u and u + nt / 2.
 __device__ __forceinline__ void decode(const AttnArgs& a, bool rev, int& tile, int& hd, int& sq,
-                                       int rows = 128) {
+                                       int rows) {
   const int per = a.heads * a.nseq, nt = (a.N + rows - 1) / rows;
   const int u = (int)(blockIdx.x / per), rest = (int)(blockIdx.x % per);
   const int h = (nt + 1) / 2;
@@ -470,17 +435,21 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
   }
 }
 
-template <int D, bool CAUSAL, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dq_kernel(AttnArgs a) {
-  constexpr int KS = D / 16, DB = D / 32, QB = 32 * NW, NT = 64 * NW;
-  constexpr int CPR = D / 8;
-  using Tiles = KVTiles<D, 32, NT>;
-  // 32-key K/V stages, then the dO rows of the block's 128 queries (read
-  // from LDS each tile rather than held in registers): 64 KB of LDS at
-  // D = 128, so two blocks share a CU, and the kernel fits in the 256 VGPRs
-  // that leaves without moving values through the AGPRs every step
-  __shared__ __attribute__((aligned(16))) char lds[2 * 2 * Tiles::TB + QB * D * 2];
-  char* const gt = lds + 2 * 2 * Tiles::TB;
+// dQ and delta: blocks of 4 waves of 32 queries, two to a CU, over 32-key tiles.
+//
+// As the forward it runs one tile ahead: S(t + 1) = K Q and dP(t + 1) = V dO are
+// issued between the elementwise work of tile t, dQ += K^T dS(t) follows, and each
+// LDS read is one (D = 64: two) groups of products ahead of its use. K(t) is read in
+// two steps (rows, then transposed), so K has three slots and V two; the block's dO
+// rows are read from LDS (registers hold Q). Before -> now: 4 x 4096 tokens, 32 heads
+// of 128, causal 970 -> 850 us; one sequence of 4096, 16 heads 171 -> 135; 4 x 1500, 20
+// heads of 64, bidirectional 112 -> 102.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a) {
+  constexpr int KS = D / 16, DB = D / 32, NW = 4, QB = 32 * NW;
+  using Dma = TileDma<D, 32, NW>;
+  constexpr int TB = Dma::TB, VB = 3 * TB, GB = 5 * TB;  // K slots, V slots, the dO rows
+  __shared__ __attribute__((aligned(1024))) char lds[GB + QB * D * 2];
   // the wave index through readfirstlane: the compiler then knows it is
   // wave-uniform, and the branches on a wave's query or key range are
   // scalar branches instead of exec-mask ones (backward 7-10% faster)
@@ -497,12 +466,22 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dq_kernel(AttnArgs a) {
   const int q0 = qt * QB, qw = q0 + 32 * w + lq;
   const bool live = qw < a.N;
 
+  const int kend = CAUSAL ? min(a.N, q0 + QB) : a.N;
+  const int nk = (kend + 31) / 32;
+  // (causal: a wave whose queries all precede a tile has nothing in it)
+  const int nkw = CAUSAL ? min(nk, (q0 + 32 * w + 31) / 32 + 1) : nk;
+  const long kstep = 32 * ld;
+  const Dma dma(lds_base(lds), w, lane, ld);
+  {
+    const Dma dmag(lds_base(lds), w, lane, a.M);
 #pragma unroll
-  for (int u = 0; u < QB * CPR / NT; ++u) {
-    const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR, q = q0 + r;
-    *reinterpret_cast<u32x4*>(gt + toff<D>(r, c)) =
-        q < a.N ? *reinterpret_cast<const u32x4*>(Gg + (long)q * a.M + 8 * c) : u32x4{0, 0, 0, 0};
+    for (int i = 0; i < NW; ++i)
+      dmag.load(Gg + (long)(q0 + 32 * i) * a.M, a.N - q0 - 32 * i, GB + i * TB);
   }
+  dma.load(Kg, kend, 0);
+  dma.load(Vg, kend, VB);
+  dma.load(Kg + kstep, kend - 32, TB);  // (past the last tile: no traffic)
+  dma.load(Vg + kstep, kend - 32, VB + TB);
   bf16x8 qf[KS];
   float dl = 0.0f;
 #pragma unroll
@@ -521,54 +500,122 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dq_kernel(AttnArgs a) {
 #pragma unroll
   for (int db = 0; db < DB; ++db) dq[db] = zero16();
 
-  const int kend = CAUSAL ? min(a.N, q0 + QB) : a.N;
-  const int nk = (kend + 31) / 32;
-  Tiles tl;
-  tl.load(Kg, Vg, ld, 0, a.N, tid);
-  tl.store(lds, lds + Tiles::TB, tid);
-  __syncthreads();
   int rbase = row_base<D>(lq, h2), tb0 = tr_base<D>(lane, 0), tb1 = tr_base<D>(lane, 1);
-  auto step = [&](const int kt, auto stc) {
-    constexpr int st = decltype(stc)::value;
-    opaque(rbase, tb0, tb1);
-    if (kt + 1 < nk) tl.load(Kg, Vg, ld, (kt + 1) * 32, a.N, tid);
-    const char* tk = lds + st * 2 * Tiles::TB;
-    const char* tv = tk + Tiles::TB;
-    const int kb0 = kt * 32;
-    if (!CAUSAL || kb0 <= q0 + 32 * w + 31) {
-      floatx16 s = zero16(), dp = zero16();
+  // read groups: 0 .. KS - 1, the K, V and dO rows at k step i of tile t + 1; then DB
+  // groups of tile t's K transposed, 16 keys by 64 columns each
+  constexpr int NG = KS + DB;
+  constexpr int RS = D == 128 ? 2 : 3;  // groups in registers (128: three spill)
+  bf16x8 fr[RS][3];
+  auto read_group = [&](const char* tk, const char* tv, const char* tkt, int i) {
+    if (i < KS) {
+      fr[i % RS][0] = frag_row_x<D>(tk, rbase, 0, i);
+      fr[i % RS][1] = frag_row_x<D>(tv, rbase, 0, i);
+      fr[i % RS][2] = frag_row_x<D>(lds + GB, rbase, 32 * w, i);
+    } else if (i < NG) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) s = mfma(frag_row_x<D>(tk, rbase, 0, ks), qf[ks], s);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        dp = mfma(frag_row_x<D>(tv, rbase, 0, ks), frag_row_x<D>(gt, rbase, 32 * w, ks), dp);
-      const bool edge = kb0 + 32 > a.N || (CAUSAL && kb0 + 31 > q0 + 32 * w);
+      for (int u = 0; u < 2; ++u)
+        fr[i % RS][u] = frag_tr_x<D>(tkt, tb0, tb1, 16 * ((i - KS) / (DB / 2)),
+                                    32 * (2 * ((i - KS) % (DB / 2)) + u));
+    }
+  };
+  floatx16 s[2], dp[2];  // [tile parity]
+  auto mul = [&](floatx16& x, floatx16& y, int i) {
+    x = mfma(fr[i % RS][0], qf[i], i == 0 ? zero16() : x);
+    y = mfma(fr[i % RS][1], fr[i % RS][2], i == 0 ? zero16() : y);
+  };
+  auto mask = [&](floatx16& x, int kb0) {
+    if (kb0 + 32 > a.N || (CAUSAL && kb0 + 31 > q0 + 32 * w)) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float pv = exp2_fast(s[r] * a.c2 - l2);
-        if (edge) {
-          const int key = kb0 + 8 * (r >> 2) + 4 * h2 + (r & 3);
-          if (key >= a.N || (CAUSAL && key > qw)) pv = 0.0f;
-        }
-        s[r] = pv * (dp[r] - dl);  // dS^T
-      }
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const bf16x8 pb = pfrag(s, s2);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          dq[db] = mfma(frag_tr_x<D>(tk, tb0, tb1, 16 * s2, 32 * db), pb, dq[db]);
+        const int key = kb0 + 8 * (r >> 2) + 4 * h2 + (r & 3);
+        if (key >= a.N || (CAUSAL && key > qw)) x[r] = -INFINITY;
       }
     }
-    if (kt + 1 < nk) {
-      char* nk_ = lds + (st ^ 1) * 2 * Tiles::TB;
-      tl.store(nk_, nk_ + Tiles::TB, tid);
+  };
+
+  wait_vm<0>();
+  lds_barrier();
+  read_group(lds, lds + VB, lds, 0);
+  if constexpr (RS > 2) read_group(lds, lds + VB, lds, 1);
+#pragma unroll
+  for (int i = 0; i < KS; ++i) {
+    if (i + RS - 1 < KS) read_group(lds, lds + VB, lds, i + RS - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(s[0], dp[0], i);
+  }
+  mask(s[0], 0);
+
+  int k0s = 0;  // tile t's K slot
+  auto step = [&](const int t, auto stc) {
+    constexpr int st = decltype(stc)::value;
+    opaque(rbase, tb0, tb1);
+    wait_vm<0>();   // K(t + 1) and V(t + 1)
+    lds_barrier();  // and every wave's reads of the slots refilled now are done
+    const int k1s = k0s == 2 ? 0 : k0s + 1, k2s = k1s == 2 ? 0 : k1s + 1;
+    const char* tk = lds + k1s * TB;
+    const char* tv = lds + VB + (st ^ 1) * TB;
+    const char* tkt = lds + k0s * TB;
+    const bool next = t + 1 < nkw;
+    if (next) {
+      read_group(tk, tv, tkt, 0);
+      if constexpr (RS > 2) read_group(tk, tv, tkt, 1);
     }
-    __syncthreads();
+    Kg += kstep;  // K(t + 1), V(t + 1)
+    Vg += kstep;
+    dma.load(Kg + kstep, kend - 32 * (t + 2), k2s * TB);
+    dma.load(Vg + kstep, kend - 32 * (t + 2), VB + st * TB);
+    k0s = k1s;
+    if (t >= nkw) return;
+    unsigned pw[8];  // dS^T of this lane, bf16 pairs
+    auto elem = [&](int r0, int r1) {
+#pragma unroll
+      for (int r = r0; r < r1; r += 2) {
+        const float d0 = exp2_fast(fmaf(s[st][r], a.c2, -l2)) * (dp[st][r] - dl);
+        const float d1 = exp2_fast(fmaf(s[st][r + 1], a.c2, -l2)) * (dp[st][r + 1] - dl);
+        pw[r >> 1] = pack_bf16x2(d0, d1);
+        asm volatile("" : "+v"(pw[r >> 1]));  // (computed here, not where it is used)
+      }
     };
-  for (int kt = 0; kt < nk; kt += 2) {
-    step(kt, Stage<0>{});
-    if (kt + 1 < nk) step(kt + 1, Stage<1>{});
+    __builtin_amdgcn_sched_barrier(0);
+    if (next) {
+      constexpr int CH = 16 / KS;  // scores beside a group's two products
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        read_group(tk, tv, tkt, i + RS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        elem(i * CH, (i + 1) * CH);
+        mul(s[st ^ 1], dp[st ^ 1], i);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x402, 9 * CH / 4, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mask(s[st ^ 1], 32 * (t + 1));
+    } else {
+      read_group(tk, tv, tkt, KS);
+      if constexpr (RS > 2) read_group(tk, tv, tkt, KS + 1);
+      elem(0, 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < DB; ++j) {
+      read_group(tk, tv, tkt, KS + j + RS - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const int g = j / (DB / 2);
+      const bf16x8 pb = __builtin_bit_cast(bf16x8, u32x4{pw[4 * g], pw[4 * g + 1], pw[4 * g + 2], pw[4 * g + 3]});
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int db = 2 * (j % (DB / 2)) + u;
+        dq[db] = mfma(fr[(KS + j) % RS][u], pb, dq[db]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  for (int t = 0; t < nk; t += 2) {
+    step(t, Stage<0>{});
+    if (t + 1 < nk) step(t + 1, Stage<1>{});
   }
   if (live) {
     bf16_t* dst = a.d_qkv + (tok0 + qw) * ld + (long)hd * D;
@@ -577,18 +624,21 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dq_kernel(AttnArgs a) {
   }
 }
 
-template <int D, bool CAUSAL, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dkdv_kernel(AttnArgs a) {
-  constexpr int KS = D / 16, DB = D / 32, CPR = D / 8, KB = 32 * NW, NT = 64 * NW;
-  constexpr int TQ = 32 * D * 2;                // one 32-row tile
-  constexpr int STG = 2 * TQ + 256;             // Q, dO, then 32 lse2 and 32 delta
-  constexpr int TOT = 32 * CPR;                 // chunks per 32-row tile
-  constexpr int LD = (TOT + NT - 1) / NT;       // chunks per thread per tile
-  // two query stages, then the V rows of the block's 128 keys (read from
-  // LDS each step rather than held in registers: the kernel then fits in the
-  // 256 VGPRs without moving values through the AGPRs every step)
-  __shared__ __attribute__((aligned(16))) char lds[2 * STG + KB * D * 2];
-  char* const vt = lds + 2 * STG;
+// dK and dV: blocks of 4 waves of 32 keys, two to a CU, over 32-query tiles. The
+// accumulators leave no registers for a tile ahead; within a tile every LDS read
+// (Q, dO and the block's V rows, then dO and Q transposed) is one (D = 64: two)
+// groups of products ahead of its use, S and dP alternate, and the other block of
+// the CU fills the elementwise part (half of it beside the first products of
+// dV and dK was 2-4% slower at D = 128). Before -> now, as above: 1258 -> 1120, 256 ->
+// 182 and 163 -> 127 us.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void attn_dkdv_kernel(AttnArgs a) {
+  constexpr int KS = D / 16, DB = D / 32, NW = 4, KB = 32 * NW;
+  using Dma = TileDma<D, 32, NW>;
+  constexpr int TQ = Dma::TB;           // one 32-row tile
+  constexpr int VT = 4 * TQ;            // two slots of Q and dO, then the block's V rows,
+  constexpr int ST = VT + KB * D * 2;   // then two slots of 32 lse2 and 32 delta
+  __shared__ __attribute__((aligned(1024))) char lds[ST + 2 * 256];
   // the wave index through readfirstlane: the compiler then knows it is
   // wave-uniform, and the branches on a wave's query or key range are
   // scalar branches instead of exec-mask ones (backward 7-10% faster)
@@ -602,109 +652,122 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_dkdv_kernel(AttnArgs a) 
   const long srow0 = (long)hd * a.T + tok0;
   const int k0 = kt * KB, kw = k0 + 32 * w + lq;
   const bool live = kw < a.N;
+  // query steps of 32: causal keys k0.. are seen by queries >= k0 only
+  const int qs0 = CAUSAL ? k0 : 0;
+  const int nqs = (a.N - qs0 + 31) / 32;
 
+  const Dma dma(lds_base(lds), w, lane, ld), dmag(lds_base(lds), w, lane, a.M);
+#pragma unroll
+  for (int i = 0; i < NW; ++i)
+    dma.load(Qg + 2L * a.M + (long)(k0 + 32 * i) * ld, a.N - k0 - 32 * i, VT + i * TQ);
   bf16x8 kf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
     kf[ks] = live ? *reinterpret_cast<const bf16x8*>(Qg + a.M + kw * ld + 16 * ks + 8 * h2) : zero8();
-#pragma unroll
-  for (int u = 0; u < KB * CPR / NT; ++u) {
-    const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR, key = k0 + r;
-    *reinterpret_cast<u32x4*>(vt + toff<D>(r, c)) =
-        key < a.N ? *reinterpret_cast<const u32x4*>(Qg + 2L * a.M + key * ld + 8 * c)
-                  : u32x4{0, 0, 0, 0};
-  }
+  float rstat = 0.0f;  // (the block's first 64 threads)
+  const float* sp = (tid < 32 ? a.lse : a.delta) + srow0 + (tid & 31);
+  auto load_stat = [&](int qb) {
+    if (tid < 64) rstat = qb + (tid & 31) < a.N ? sp[qb] * (tid < 32 ? kLog2e : 1.0f) : 0.0f;
+  };
+  auto store_stat = [&](int slot) {
+    if (tid < 64) reinterpret_cast<float*>(lds + ST + 256 * slot)[tid] = rstat;
+  };
+  const bf16_t* Qt = Qg + qs0 * ld;
+  const bf16_t* Gt = Gg + (long)qs0 * a.M;
+  dma.load(Qt, a.N - qs0, 0);
+  dmag.load(Gt, a.N - qs0, TQ);
+  load_stat(qs0);
+  store_stat(0);
   floatx16 dv[DB], dk[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
     dv[db] = zero16();
     dk[db] = zero16();
   }
-  // query steps of 32: causal keys k0.. are seen by queries >= k0 only
-  const int qs0 = CAUSAL ? k0 : 0;
-  const int nqs = (a.N - qs0 + 31) / 32;
-  u32x4 rq[LD], rg[LD];
-  float rstat = 0.0f;
-  auto load = [&](int qb) {
-#pragma unroll
-    for (int u = 0; u < LD; ++u) {
-      const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR, q = qb + r;
-      if (q < a.N && idx < TOT) {
-        rq[u] = *reinterpret_cast<const u32x4*>(Qg + q * ld + 8 * c);
-        rg[u] = *reinterpret_cast<const u32x4*>(Gg + (long)q * a.M + 8 * c);
-      } else {
-        rq[u] = u32x4{0, 0, 0, 0};
-        rg[u] = u32x4{0, 0, 0, 0};
-      }
-    }
-    if (tid < 64) {
-      const int q = qb + (tid & 31);
-      rstat = q < a.N ? (tid < 32 ? a.lse[srow0 + q] * kLog2e : a.delta[srow0 + q]) : 0.0f;
-    }
-  };
-  auto store = [&](char* stg) {
-#pragma unroll
-    for (int u = 0; u < LD; ++u) {
-      const int idx = tid + NT * u, r = idx / CPR, c = idx % CPR;
-      if (TOT % NT != 0 && idx >= TOT) continue;
-      *reinterpret_cast<u32x4*>(stg + toff<D>(r, c)) = rq[u];
-      *reinterpret_cast<u32x4*>(stg + TQ + toff<D>(r, c)) = rg[u];
-    }
-    if (tid < 64) reinterpret_cast<float*>(stg + 2 * TQ)[tid] = rstat;
-  };
-  if (nqs > 0) {
-    load(qs0);
-    store(lds);
-  }
-  __syncthreads();
   int rbase = row_base<D>(lq, h2), tb0 = tr_base<D>(lane, 0), tb1 = tr_base<D>(lane, 1);
+  // read groups: 0 .. KS - 1, the Q, dO and V rows at k step i; then 2 DB groups of dO
+  // and Q transposed, 16 queries by 32 columns each
+  constexpr int NG = KS + 2 * DB;
+  constexpr int RS = D == 128 ? 2 : 3;  // groups in registers (128: three spill)
+  bf16x8 fr[RS][3];
+  auto read_group = [&](const char* tq, int i) {
+    const char* tg = tq + TQ;
+    if (i < KS) {
+      fr[i % RS][0] = frag_row_x<D>(tq, rbase, 0, i);
+      fr[i % RS][1] = frag_row_x<D>(tg, rbase, 0, i);
+      fr[i % RS][2] = frag_row_x<D>(lds + VT, rbase, 32 * w, i);
+    } else if (i < NG) {
+      fr[i % RS][0] = frag_tr_x<D>(tg, tb0, tb1, 16 * ((i - KS) / DB), 32 * ((i - KS) % DB));
+      fr[i % RS][1] = frag_tr_x<D>(tq, tb0, tb1, 16 * ((i - KS) / DB), 32 * ((i - KS) % DB));
+    }
+  };
   auto step = [&](const int it, auto stc) {
     constexpr int st = decltype(stc)::value;
     opaque(rbase, tb0, tb1);
     const int qb = qs0 + 32 * it;
-    if (it + 1 < nqs) load(qb + 32);
-    const char* tq = lds + st * STG;
-    const char* tg = tq + TQ;
-    const float* l2 = reinterpret_cast<const float*>(tq + 2 * TQ);
-    const float* dls = l2 + 32;
-    if (!CAUSAL || qb + 31 >= k0 + 32 * w) {
-      floatx16 s = zero16(), dp = zero16();
+    wait_vm<0>();   // this tile's loads
+    lds_barrier();  // and every wave's reads of the other slot are done
+    const char* tq = lds + st * 2 * TQ;
+    const float* l2 = reinterpret_cast<const float*>(lds + ST + 256 * st);
+    const bool mine = !CAUSAL || qb + 31 >= k0 + 32 * w;
+    if (mine) {
+      read_group(tq, 0);
+      if constexpr (RS > 2) read_group(tq, 1);
+    }
+    Qt += 32 * ld;
+    Gt += 32L * a.M;
+    dma.load(Qt, a.N - qb - 32, (st ^ 1) * 2 * TQ);
+    dmag.load(Gt, a.N - qb - 32, (st ^ 1) * 2 * TQ + TQ);
+    if (it + 1 < nqs) load_stat(qb + 32);
+    if (mine) {
+      floatx16 s, dp;
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) s = mfma(frag_row_x<D>(tq, rbase, 0, ks), kf[ks], s);
+      for (int i = 0; i < KS; ++i) {
+        read_group(tq, i + RS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        s = mfma(fr[i % RS][0], kf[i], i == 0 ? zero16() : s);
+        dp = mfma(fr[i % RS][1], fr[i % RS][2], i == 0 ? zero16() : dp);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (qb + 32 > a.N || (CAUSAL && k0 + 32 * w + 31 > qb)) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        dp = mfma(frag_row_x<D>(tg, rbase, 0, ks), frag_row_x<D>(vt, rbase, 32 * w, ks), dp);
-      const bool edge = qb + 32 > a.N || (CAUSAL && k0 + 32 * w + 31 > qb);
+        for (int r = 0; r < 16; ++r) {
+          const int q = qb + 8 * (r >> 2) + 4 * h2 + (r & 3);
+          if (q >= a.N || (CAUSAL && kw > q)) s[r] = -INFINITY;
+        }
+      }
+      unsigned pp[8], pd[8];  // P and dS of this lane, bf16 pairs
 #pragma unroll
       for (int J = 0; J < 4; ++J) {
         const float4 lv = *reinterpret_cast<const float4*>(l2 + 8 * J + 4 * h2);
-        const float4 dv4 = *reinterpret_cast<const float4*>(dls + 8 * J + 4 * h2);
+        const float4 dv4 = *reinterpret_cast<const float4*>(l2 + 32 + 8 * J + 4 * h2);
         const float lr[4] = {lv.x, lv.y, lv.z, lv.w}, dr[4] = {dv4.x, dv4.y, dv4.z, dv4.w};
+        float pv[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int r = 4 * J + j;
-          float pv = exp2_fast(s[r] * a.c2 - lr[j]);
-          if (edge) {
-            const int q = qb + 8 * J + 4 * h2 + j;
-            if (q >= a.N || (CAUSAL && kw > q)) pv = 0.0f;
-          }
-          s[r] = pv;
-          dp[r] = pv * (dp[r] - dr[j]);  // dS
+          pv[j] = exp2_fast(fmaf(s[4 * J + j], a.c2, -lr[j]));
+          dp[4 * J + j] = pv[j] * (dp[4 * J + j] - dr[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          pp[2 * J + j / 2] = pack_bf16x2(pv[j], pv[j + 1]);
+          pd[2 * J + j / 2] = pack_bf16x2(dp[4 * J + j], dp[4 * J + j + 1]);
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const bf16x8 pb = pfrag(s, s2), pd = pfrag(dp, s2);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          dv[db] = mfma(frag_tr_x<D>(tg, tb0, tb1, 16 * s2, 32 * db), pb, dv[db]);
-          dk[db] = mfma(frag_tr_x<D>(tq, tb0, tb1, 16 * s2, 32 * db), pd, dk[db]);
-        }
+      for (int j = 0; j < 2 * DB; ++j) {
+        read_group(tq, KS + j + RS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int g = j / DB, db = j % DB, c = (KS + j) % RS;
+        dv[db] = mfma(fr[c][0], __builtin_bit_cast(bf16x8, u32x4{pp[4 * g], pp[4 * g + 1], pp[4 * g + 2], pp[4 * g + 3]}), dv[db]);
+        dk[db] = mfma(fr[c][1], __builtin_bit_cast(bf16x8, u32x4{pd[4 * g], pd[4 * g + 1], pd[4 * g + 2], pd[4 * g + 3]}), dk[db]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (it + 1 < nqs) store(lds + (st ^ 1) * STG);
-    __syncthreads();
-    };
+    if (it + 1 < nqs) store_stat(st ^ 1);
+  };
   for (int it = 0; it < nqs; it += 2) {
     step(it, Stage<0>{});
     if (it + 1 < nqs) step(it + 1, Stage<1>{});
@@ -731,27 +794,27 @@ AttnArgs attn_args(const AttnShape& m, int T, int M) {
   return a;
 }
 
-unsigned attn_blocks(const AttnArgs& a, int rows = 128) {
-  return (unsigned)(((a.N + rows - 1) / rows) * a.heads * a.nseq);
+unsigned attn_blocks(const AttnArgs& a) {
+  return (unsigned)(((a.N + 127) / 128) * a.heads * a.nseq);
 }
 
-// pair long and short causal tiles (decode) when the 4-wave grid (two
-// blocks per CU) is resident all at once: then the makespan is a CU's two
-// blocks together, not the longest-first order's
-int attn_pair(const AttnShape& m, const AttnArgs& a, bool wide) {
-  return m.causal && !wide && attn_blocks(a, 128) <= 2u * 256u ? 1 : 0;
+// pair long and short causal tiles (decode) when the grid (two blocks per CU) is
+// resident all at once: then the makespan is a CU's two blocks together, not
+// the longest-first order's
+int attn_pair(const AttnShape& m, const AttnArgs& a) {
+  return m.causal && attn_blocks(a) <= 2u * 256u ? 1 : 0;
 }
 
-#define FLOWMOE_ATTN_LAUNCH(KERNEL, a, st, ROWS, THREADS, ...)                                 \
-  do {                                                                                          \
-    const dim3 g(attn_blocks(a, ROWS)), b(THREADS);                                             \
-    if (m.D == 128) {                                                                           \
-      if (m.causal) hipLaunchKernelGGL((KERNEL<128, true, ##__VA_ARGS__>), g, b, 0, st, a);     \
-      else hipLaunchKernelGGL((KERNEL<128, false, ##__VA_ARGS__>), g, b, 0, st, a);             \
-    } else {                                                                                    \
-      if (m.causal) hipLaunchKernelGGL((KERNEL<64, true, ##__VA_ARGS__>), g, b, 0, st, a);      \
-      else hipLaunchKernelGGL((KERNEL<64, false, ##__VA_ARGS__>), g, b, 0, st, a);              \
-    }                                                                                           \
+#define FLOWMOE_ATTN_LAUNCH(KERNEL, a, st)                                       \
+  do {                                                                            \
+    const dim3 g(attn_blocks(a)), b(256);                                         \
+    if (m.D == 128) {                                                             \
+      if (m.causal) hipLaunchKernelGGL((KERNEL<128, true>), g, b, 0, st, a);      \
+      else hipLaunchKernelGGL((KERNEL<128, false>), g, b, 0, st, a);              \
+    } else {                                                                      \
+      if (m.causal) hipLaunchKernelGGL((KERNEL<64, true>), g, b, 0, st, a);       \
+      else hipLaunchKernelGGL((KERNEL<64, false>), g, b, 0, st, a);               \
+    }                                                                             \
   } while (0)
 
 }  // namespace
@@ -763,9 +826,8 @@ hipError_t launch_attn_fwd(const AttnShape& m, int T, int M, const void* qkv, vo
   a.qkv = static_cast<const bf16_t*>(qkv);
   a.out = static_cast<bf16_t*>(o);
   a.lse = lse;
-  a.pair = attn_pair(m, a, false);
-  return traced(FLOWMOE_K_ATTN_FWD, st,
-                [&] { FLOWMOE_ATTN_LAUNCH(attn_fwd_kernel, a, st, 128, 256); });
+  a.pair = attn_pair(m, a);
+  return traced(FLOWMOE_K_ATTN_FWD, st, [&] { FLOWMOE_ATTN_LAUNCH(attn_fwd_kernel, a, st); });
 }
 
 hipError_t launch_attn_bwd(const AttnShape& m, int T, int M, const void* qkv, const void* o,
@@ -779,19 +841,11 @@ hipError_t launch_attn_bwd(const AttnShape& m, int T, int M, const void* qkv, co
   a.d_qkv = static_cast<bf16_t*>(d_qkv);
   a.lse = const_cast<float*>(lse);
   a.delta = delta;
-  // 8-wave blocks (256 queries, or keys) when that grid still gives two
-  // blocks per CU: each staged tile then serves twice the MFMA work
-  const bool wide = attn_blocks(a, 256) >= 2u * 256u;
-  a.pair = attn_pair(m, a, wide);
-  hipError_t e = traced(FLOWMOE_K_ATTN_BWD_DQ, st, [&] {
-    if (wide) FLOWMOE_ATTN_LAUNCH(attn_dq_kernel, a, st, 256, 512, 8);
-    else FLOWMOE_ATTN_LAUNCH(attn_dq_kernel, a, st, 128, 256, 4);
-  });
+  a.pair = attn_pair(m, a);
+  hipError_t e = traced(FLOWMOE_K_ATTN_BWD_DQ, st, [&] { FLOWMOE_ATTN_LAUNCH(attn_dq_kernel, a, st); });
   if (e != hipSuccess) return e;
-  return traced(FLOWMOE_K_ATTN_BWD_DKDV, st, [&] {
-    if (wide) FLOWMOE_ATTN_LAUNCH(attn_dkdv_kernel, a, st, 256, 512, 8);
-    else FLOWMOE_ATTN_LAUNCH(attn_dkdv_kernel, a, st, 128, 256, 4);
-  });
+  return traced(FLOWMOE_K_ATTN_BWD_DKDV, st,
+                [&] { FLOWMOE_ATTN_LAUNCH(attn_dkdv_kernel, a, st); });
 }
 
 hipError_t launch_mha_fwd(const AttnShape& m, int T, int M, const void* in, const void* w_qkv,
