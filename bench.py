@@ -533,7 +533,7 @@ def main():
             "kept_rows": kept,
         },
         "roofline": {
-            "kernel": f"grouped GEMM (gemm_bf16_kernel, all {gemm_per_step} launches of a step)",
+            "kernel": f"grouped GEMM (gemm_bf16_rows_kernel, gemm_bf16_ksum_kernel, all {gemm_per_step} launches of a step)",
             "bound": "mfma",
             "achieved": round(achieved_tflops, 2),
             "peak": PEAK_BF16_TFLOPS,

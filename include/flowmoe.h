@@ -317,11 +317,13 @@ int32_t flowmoe_trace_stop(void);
 /* ---- grouped-GEMM tile shape ------------------------------------------------ */
 
 /* Output tile shapes of the bf16 grouped GEMM (expert FFN forward and
- * backward). AUTO, the default: 256 x 256 tiles (one block per compute unit)
- * unless a launch would have at most 1.25 x 256 of them, then 256 x 128
- * tiles (up to two blocks per compute unit). WIDE and NARROW force one
- * shape (the SwiGLU forward always takes 256 x 256). Both shapes accumulate
- * every output in the same k order: results are bit-identical. */
+ * backward). AUTO, the default: over the experts' rows the kernel takes the
+ * smallest of 128 x 128, 256 x 128 and 256 x 256 tiles that run as one round of
+ * the compute units, else 256 x 256, by the counts it finds on the device; the
+ * weight gradients take 256 x 128 tiles up to 160 wide ones. WIDE and NARROW
+ * force 256 x 256 or 256 x 128 (the SwiGLU forward has no 256 x 128 tile). Every
+ * shape accumulates every output in the same k order: results are
+ * bit-identical. */
 enum { FLOWMOE_TILES_AUTO = 0, FLOWMOE_TILES_WIDE = 1, FLOWMOE_TILES_NARROW = 2 };
 
 /* Set the tile shape for launches enqueued after the call, process-wide

@@ -26,6 +26,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 enum { MODE_ROWS = 0, MODE_KSUM = 1 };
+constexpr int kCUs = 256;
 enum {
   EPI_STORE = 0,       // C0 = acc
   EPI_GELU_FWD = 1,    // C0 = h = acc, C1 = a = gelu(acc)
@@ -50,8 +51,7 @@ struct GemmParams {
   const int32_t* offsets;
   int E;
   int padC;          // padded layout: every expert spans C rows (0 = packed)
-  int mt_bound;      // ROWS: row tiles per column tile in the grid
-  int ntiles;        // ROWS: column tiles
+  int tiles;         // ROWS, bf16: tile shape (FLOWMOE_TILES_*)
   void* C0;
   void* C1;
   long ldc, ldc1;
@@ -166,14 +166,20 @@ struct IntC {
   static constexpr int value = V;
 };
 
-// inclusive prefix sum of v over the lanes of a wave
+// inclusive prefix sum of v over the lanes of a wave: DPP moves inside the rows
+// of 16 lanes, then the row totals broadcast to the rows after them (six vector
+// adds; through ds_bpermute each of six exchanges is an LDS round trip)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
 __device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int u = __shfl_up(v, d, 64);
-    if (lane >= d) v += u;
-  }
+  v = dpp_add<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast 15: rows 1 and 3 add the row before
+  v = dpp_add<0x143, 0xC>(v);  // row_bcast 31: rows 2 and 3 add the first two
   return v;
 }
 
@@ -187,18 +193,21 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 // tiles) are walked in shared 16 x 16 blocks (shared_block_tile); inside the
 // light class, consecutive tiles walk kRowGroup row tiles x the column
 // tiles, row tiles fastest. Returns false for a block with no tile.
+struct LaneRows {  // lane x: expert x's live rows, first row, and rows with the padding
+  int c, o, r;
+};
+
 template <int BM>
-__device__ __forceinline__ bool row_tile_of_block(const GemmParams& p, int bid, int& e, int& mt,
-                                                  int& nt, int& rows_e, int& cnt_e, int& off_e) {
-  // lane x holds expert x (E <= 64): its count and first row are loaded
-  // together (one memory round trip), its tile counts per class summed over
+__device__ __forceinline__ bool row_tile_of_block(const GemmParams& p, int ntiles, const LaneRows& lr,
+                                                  int bid, int& e, int& mt, int& nt, int& rows_e,
+                                                  int& cnt_e, int& off_e) {
+  // lane x holds expert x (E <= 64): its count and first row were loaded
+  // together (one memory round trip), its tile counts per class are summed over
   // the lanes by a prefix scan, and the block's expert found by a ballot
   // (a walk over the experts in scalar registers cost ~0.15 us per expert)
   const int lane = threadIdx.x & 63;
   const bool live = lane < p.E;
-  const int c = live ? seg_count(p, 0, lane) : 0;
-  const int o = live ? seg_offset(p, 0, lane) : 0;
-  const int r = live ? (p.padC ? p.padC : c) : 0;
+  const int c = lr.c, o = lr.o, r = lr.r;
   const int te = (r + BM - 1) / BM;
   // heavy row tiles of this expert (joined order: all of them)
   const int he = p.joined ? te : min(te, (c + BM / 2) / BM);
@@ -206,17 +215,17 @@ __device__ __forceinline__ bool row_tile_of_block(const GemmParams& p, int bid, 
   const int hin = wave_incl_scan(he), lin = wave_incl_scan(le);
   const int HR = __builtin_amdgcn_readlane(hin, 63), LR = __builtin_amdgcn_readlane(lin, 63);
   const int x = bid & 7, i = bid >> 3;
-  const int H = HR * p.ntiles, L = LR * p.ntiles;
+  const int H = HR * ntiles, L = LR * ntiles;
   const int hx = (H >> 3) + (x < (H & 7)), lx = (L >> 3) + (x < (L & 7));
   bool heavy;
   int ml;
   if (i < hx) {
     heavy = true;
-    shared_block_tile(i * 8 + x, HR, p.ntiles, ml, nt);  // (i * 8 + x < H)
+    shared_block_tile(i * 8 + x, HR, ntiles, ml, nt);  // (i * 8 + x < H)
   } else if (i < hx + lx) {
     heavy = false;
     const int idx = x * (L >> 3) + min(x, L & 7) + (i - hx);
-    const int gsz = kRowGroup * p.ntiles;
+    const int gsz = kRowGroup * ntiles;
     const int g = idx / gsz, rg = idx - g * gsz;
     const int gm = min(kRowGroup, LR - g * kRowGroup);  // row tiles in this group
     nt = rg / gm;
@@ -493,16 +502,18 @@ __device__ __forceinline__ bf16x8 half_frag(const char* h, int base, int i, int 
   }
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW>
-__global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
-  constexpr int BM = 256, BN = NARROW ? 128 : 256;
+constexpr int kGemmSmem = 9 * kHalf;  // 144 KB
+
+// One tile of the kernels below. BM = 128: low tiles (row mode), light loops only.
+template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW, int BM>
+__device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int ntiles, const LaneRows& lr) {
+  constexpr int BN = NARROW ? 128 : 256;
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
   static_assert(!DUAL || !NARROW, "the dual forward pairs 128-column W1 and W3 halves");
   // k-tiles in LDS (stages), the halves of one (A0, A1, B0 and wide B1) and its bytes
   constexpr int NST = NARROW ? 3 : 2, NB = NARROW ? 1 : 2, STB = (2 + NB) * kHalf;
-  constexpr int SMEM = 9 * kHalf;  // 144 KB
+  constexpr int SMEM = kGemmSmem;
   static_assert(NST * STB <= SMEM, "k-tiles do not fit");
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -514,7 +525,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
   int seg_o = 0, seg_c = 0;  // KSUM: segment ranges, one lane per segment
   if constexpr (MODE == MODE_ROWS) {
     int off_e = 0;
-    if (!row_tile_of_block<BM>(p, blockIdx.x, e, mt, nt, rows_e, cnt_e, off_e)) return;
+    if (!row_tile_of_block<BM>(p, ntiles, lr, blockIdx.x, e, mt, nt, rows_e, cnt_e, off_e)) return;
     rows_e = clip_rows(off_e, rows_e, p.rows_cap);
     cnt_e = clip_rows(off_e, cnt_e, p.rows_cap);
     row0 = off_e + mt * BM;
@@ -880,16 +891,63 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmParams p) {
     // wm * 64 .. and 128 + wm * 64 ..
     const int live = cnt_e - mt * BM;
     if (live <= 64) light_loop(IntC<64>{});
-    else if (live <= 128) light_loop(IntC<128>{});
-    else if (live > 128 + wm * 64) k_loop(IntC<2>{});
-    else k_loop(IntC<1>{});
+    else if (BM == 128 || live <= 128) light_loop(IntC<128>{});
+    else if constexpr (BM > 128) {
+      if (live > 128 + wm * 64) k_loop(IntC<2>{});
+      else k_loop(IntC<1>{});
+    }
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();  // all loads landed and LDS reads done before the epilogue reuses the stages
   const int rows_t = MODE == MODE_ROWS ? rows_e - mt * BM : p.Mdim - mt * BM;
   gemm_epilogue<MODE, EPI, BM, NB>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm, wn,
-                                   rows_t > 128 ? 2 : 1);
+                                   BM > 128 && rows_t > 128 ? 2 : 1);
+}
+
+// Row mode: the tile shape is chosen from the experts' rows. Packed rows are known
+// on the device only (a skewed gate fills a fifth of the capacity): there every
+// block makes the same choice from the counts, and the host makes it for padded
+// ones. The chain of k-tiles sets the time of a launch of few tiles, and a
+// smaller tile's k-tile is shorter (0.6, 0.8-1.2 and 1.1-1.6 us for 128 x 128, 256 x
+// 128 and 256 x 256): so the smallest shape whose tiles, the experts' partial ones
+// included, fit one round of the 256 CUs, else 256 x 256. Against 256 x 128 tiles
+// wherever the rows' capacity gives at most 1.25 x 256 wide ones (kernel times, H =
+// 4096, M = 1024): T = 8192 top-1 on a heavy-tailed gate, E = 16, W2's forward 72.8
+// -> 59.5 us and W1's dgrad 59.4 -> 47.0 (128 x 128); T = 4096, k = 2, E = 8, W1's
+// dgrad 97.8 -> 89.0 and W2's forward 100.5 -> 102.3 (about 300 narrow tiles before,
+// 150 wide ones now). A launch of several rounds pays 0-2 % for the choice.
+constexpr int kTilesShort = -1;  // 128 x 128, beside the FLOWMOE_TILES_* values
+__host__ __device__ inline int rows_shape(int t256, int t128, int n128, bool dual) {
+  if ((long)t128 * n128 <= kCUs) return kTilesShort;
+  return !dual && (long)t256 * n128 <= kCUs ? FLOWMOE_TILES_NARROW : FLOWMOE_TILES_WIDE;
+}
+
+template <bool B_KC, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_rows_kernel(GemmParams p) {
+  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
+  __shared__ __attribute__((aligned(1024))) char smem[kGemmSmem];
+  const int lane = threadIdx.x & 63;
+  const bool live = lane < p.E;
+  LaneRows lr;
+  lr.c = live ? seg_count(p, 0, lane) : 0;
+  lr.o = live ? seg_offset(p, 0, lane) : 0;
+  lr.r = live ? (p.padC ? p.padC : lr.c) : 0;
+  const int n128 = (p.N + 127) / 128, n256 = DUAL ? n128 : (p.N + 255) / 256;
+  int shape = p.tiles;
+  if (shape == FLOWMOE_TILES_AUTO)
+    shape = rows_shape(__builtin_amdgcn_readlane(wave_incl_scan((lr.r + 255) / 256), 63),
+                       __builtin_amdgcn_readlane(wave_incl_scan((lr.r + 127) / 128), 63), n128, DUAL);
+  if (shape == kTilesShort) gemm_tile<MODE_ROWS, true, B_KC, EPI, !DUAL, 128>(p, smem, n128, lr);
+  else if (shape == FLOWMOE_TILES_WIDE || DUAL)
+    gemm_tile<MODE_ROWS, true, B_KC, EPI, false, 256>(p, smem, n256, lr);
+  else if constexpr (!DUAL) gemm_tile<MODE_ROWS, true, B_KC, EPI, true, 256>(p, smem, n128, lr);
+}
+
+template <int EPI, bool NARROW>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_ksum_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem[kGemmSmem];
+  gemm_tile<MODE_KSUM, false, false, EPI, NARROW, 256>(p, smem, 0, LaneRows{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1269,61 +1327,60 @@ GemmParams base_params(const Shape& s, const int32_t* counts, const int32_t* off
   return p;
 }
 
-// Tile shape of the bf16 kernel: 256 x 256, or 256 x 128 where at most 160 wide
-// tiles would leave the CUs idle: at 128 wide tiles (4096 x 1024 x 3072 and the
-// like) 24 against 28 us and at 192 34 against 44 in favour of the narrow and
-// the wide ones.
-constexpr int kCUs = 256;
-constexpr int kNarrowMax = 160;
 std::atomic<int> g_tiles{FLOWMOE_TILES_AUTO};
 std::atomic<int> g_tile_order{FLOWMOE_TILE_ORDER_AUTO};
 
-template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW>
-hipError_t launch_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
-  constexpr int BN = NARROW ? 128 : 256;
-  long blocks;
-  if (MODE == MODE_ROWS) {
-    const int ncols = (EPI == EPI_SWIGLU_FWD) ? 128 : BN;
-    p.mt_bound = rows_tiles_bound(s, 256);
-    p.ntiles = (p.N + ncols - 1) / ncols;
-    blocks = (s.rows == 0 || p.N == 0) ? 0 : row_mode_blocks((long)p.mt_bound * p.ntiles);
-    // joined tile order: the experts' weights stream from HBM (more than the
-    // Infinity Cache holds) and each expert spans few row tiles, so a light
-    // tile run after all heavy ones would read its weight panels from HBM
-    // again; with many row tiles per expert, or weights that stay cached,
-    // running the light tiles last packs the rounds better (measured: fine
-    // layer 7.63 -> 7.26 ms per step joined, balanced 0.68 -> 0.74 and large
-    // 32.2 -> 32.7 ms)
-    const double wbytes = 2.0 * s.E * (double)p.K * p.N * (EPI == EPI_SWIGLU_FWD ? 2 : 1);
-    const int order = g_tile_order.load(std::memory_order_relaxed);
-    p.joined = order == FLOWMOE_TILE_ORDER_JOINED ||
-               (order == FLOWMOE_TILE_ORDER_AUTO && wbytes > 256.0 * 1024 * 1024 &&
-                s.rows <= 2048L * s.E);
-  } else {
-    blocks = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + BN - 1) / BN);
-  }
-  if (blocks == 0) return hipSuccess;
+template <bool B_KC, int EPI>
+hipError_t run_rows(int kind, const Shape& s, GemmParams p, hipStream_t st) {
+  constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
+  if (s.rows == 0 || p.N == 0) return hipSuccess;
+  p.tiles = DUAL ? (g_tiles.load(std::memory_order_relaxed) == FLOWMOE_TILES_AUTO ? FLOWMOE_TILES_AUTO
+                                                                                  : FLOWMOE_TILES_WIDE)
+                 : g_tiles.load(std::memory_order_relaxed);
+  // the grid covers the wide tiles, or the narrow ones if asked for; the smaller
+  // shapes the kernel chooses have at most one round of tiles
+  const int ncols = DUAL || p.tiles == FLOWMOE_TILES_NARROW ? 128 : 256;
+  const long tiles = (long)rows_tiles_bound(s, 256) * ((p.N + ncols - 1) / ncols);
+  const long blocks = row_mode_blocks(std::max(tiles, p.tiles == FLOWMOE_TILES_AUTO ? (long)kCUs : 0L));
+  if (p.tiles == FLOWMOE_TILES_AUTO && s.layout == FLOWMOE_PADDED)
+    p.tiles = rows_shape(rows_tiles_bound(s, 256), rows_tiles_bound(s, 128), (p.N + 127) / 128, DUAL);
+  // joined tile order: the experts' weights stream from HBM (more than the
+  // Infinity Cache holds) and each expert spans few row tiles, so a light
+  // tile run after all heavy ones would read its weight panels from HBM
+  // again; with many row tiles per expert, or weights that stay cached,
+  // running the light tiles last packs the rounds better (measured: fine
+  // layer 7.63 -> 7.26 ms per step joined, balanced 0.68 -> 0.74 and large
+  // 32.2 -> 32.7 ms)
+  const double wbytes = 2.0 * s.E * (double)p.K * p.N * (DUAL ? 2 : 1);
+  const int order = g_tile_order.load(std::memory_order_relaxed);
+  p.joined = order == FLOWMOE_TILE_ORDER_JOINED ||
+             (order == FLOWMOE_TILE_ORDER_AUTO && wbytes > 256.0 * 1024 * 1024 &&
+              s.rows <= 2048L * s.E);
   return traced(kind, st, [&] {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MODE, A_KC, B_KC, EPI, NARROW>), dim3((unsigned)blocks),
-                       dim3(512), 0, st, p);
+    hipLaunchKernelGGL((gemm_bf16_rows_kernel<B_KC, EPI>), dim3((unsigned)blocks), dim3(512), 0, st, p);
   });
 }
 
-template <int MODE, bool A_KC, bool B_KC, int EPI>
-hipError_t run_gemm_bf16(int kind, const Shape& s, GemmParams p, hipStream_t st) {
-  if (MODE == MODE_KSUM && p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
-  if constexpr (EPI == EPI_SWIGLU_FWD) {
-    return launch_bf16<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
-  } else {
-    // wide tiles the launch would have (row mode: the live rows' tiles)
-    const long rt = (MODE == MODE_ROWS) ? (s.rows + 255) / 256 : (long)s.E * ((p.Mdim + 255) / 256);
-    const long wide = rt * ((p.N + 255) / 256);
-    const int tiles = g_tiles.load(std::memory_order_relaxed);
-    const bool narrow = tiles == FLOWMOE_TILES_NARROW ||
-                        (tiles == FLOWMOE_TILES_AUTO && wide <= kNarrowMax);
-    if (narrow) return launch_bf16<MODE, A_KC, B_KC, EPI, true>(kind, s, p, st);
-    return launch_bf16<MODE, A_KC, B_KC, EPI, false>(kind, s, p, st);
-  }
+template <int EPI, bool NARROW>
+hipError_t launch_ksum(int kind, const Shape& s, const GemmParams& p, hipStream_t st) {
+  constexpr int BN = NARROW ? 128 : 256;
+  const long blocks = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + BN - 1) / BN);
+  if (blocks == 0) return hipSuccess;
+  return traced(kind, st, [&] {
+    hipLaunchKernelGGL((gemm_bf16_ksum_kernel<EPI, NARROW>), dim3((unsigned)blocks), dim3(512), 0, st, p);
+  });
+}
+
+// Weight gradients: 256 x 256 tiles, or 256 x 128 where at most 160 wide ones
+// would leave CUs idle
+template <int EPI>
+hipError_t run_ksum(int kind, const Shape& s, const GemmParams& p, hipStream_t st) {
+  if (p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
+  const long wide = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + 255) / 256);
+  const int tiles = g_tiles.load(std::memory_order_relaxed);
+  if (tiles == FLOWMOE_TILES_NARROW || (tiles == FLOWMOE_TILES_AUTO && wide <= 160))
+    return launch_ksum<EPI, true>(kind, s, p, st);
+  return launch_ksum<EPI, false>(kind, s, p, st);
 }
 
 template <int MODE, bool B_KC, int EPI, int FM>
@@ -1394,7 +1451,7 @@ hipError_t launch_gate_dw_gemm(const void* x, int T, int M, const void* d, int N
   // 256 x 256 tiles whatever the grid: these launches are bound by reading
   // x once, and the 8-wave tile's deeper ring (4 stages against 3) keeps
   // more of it in flight (the narrow tile took 1.2-1.7x as long)
-  return launch_bf16<MODE_KSUM, false, false, EPI_GATE_DW, false>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
+  return launch_ksum<EPI_GATE_DW, false>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
 }
 
 hipError_t launch_gate_dx_gemm(const void* dlhl, int T, int K, const void* wstack, int M,
@@ -1424,8 +1481,8 @@ hipError_t launch_gate_dx_gemm(const void* dlhl, int T, int K, const void* wstac
   p.nseg = 1;
   p.rows_cap = T;
   if (add)
-    return run_gemm_bf16<MODE_ROWS, true, false, EPI_ADD>(FLOWMOE_K_GATE_BWD_TOKEN, s2, p, st);
-  return run_gemm_bf16<MODE_ROWS, true, false, EPI_STORE>(FLOWMOE_K_GATE_BWD_TOKEN, s2, p, st);
+    return run_rows<false, EPI_ADD>(FLOWMOE_K_GATE_BWD_TOKEN, s2, p, st);
+  return run_rows<false, EPI_STORE>(FLOWMOE_K_GATE_BWD_TOKEN, s2, p, st);
 }
 
 hipError_t launch_dense_gemm(int kind, long rows, const void* A, long lda, int K, const void* B,
@@ -1450,8 +1507,8 @@ hipError_t launch_dense_gemm(int kind, long rows, const void* A, long lda, int K
   p.nsplit = 1 << 30;
   p.nseg = 1;
   p.rows_cap = rows;
-  if (b_kc) return run_gemm_bf16<MODE_ROWS, true, true, EPI_STORE>(kind, s2, p, st);
-  return run_gemm_bf16<MODE_ROWS, true, false, EPI_STORE>(kind, s2, p, st);
+  if (b_kc) return run_rows<true, EPI_STORE>(kind, s2, p, st);
+  return run_rows<false, EPI_STORE>(kind, s2, p, st);
 }
 
 int dense_wgrad_splits(int Mdim, int N, long rows) {
@@ -1499,7 +1556,7 @@ hipError_t launch_dense_wgrad(int kind, long rows, int nseg, const void* A, long
   p.a_sstride = a_sstride;
   p.b_sstride = b_sstride;
   p.rows_cap = rows;
-  FLOWMOE_TRY((run_gemm_bf16<MODE_KSUM, false, false, EPI_WGRAD>(kind, s2, p, st)));
+  FLOWMOE_TRY((run_ksum<EPI_WGRAD>(kind, s2, p, st)));
   if (S == 1) return hipSuccess;
   const long n4 = (long)Mdim * N / 4;  // (ldc == N here)
   return traced(kind, st, [&] {
@@ -1540,9 +1597,9 @@ hipError_t launch_expert_ffn(const Shape& s, const void* x_disp, const int32_t* 
   p.bias_estride = H;
   if (s.dtype == FLOWMOE_BF16) {
     if (swiglu)
-      FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, false, EPI_SWIGLU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
+      FLOWMOE_TRY((run_rows<false, EPI_SWIGLU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
     else
-      FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, false, EPI_GELU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
+      FLOWMOE_TRY((run_rows<false, EPI_GELU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
   } else {
     if (swiglu) {
       FLOWMOE_TRY((run_f32<MODE_ROWS, false, EPI_SWIGLU_FWD>(FLOWMOE_K_FFN1, s, p, st)));
@@ -1564,7 +1621,7 @@ hipError_t launch_expert_ffn(const Shape& s, const void* x_disp, const int32_t* 
   q.bias0 = b2;
   q.bias_estride = M;
   if (s.dtype == FLOWMOE_BF16)
-    return run_gemm_bf16<MODE_ROWS, true, false, EPI_STORE>(FLOWMOE_K_FFN2, s, q, st);
+    return run_rows<false, EPI_STORE>(FLOWMOE_K_FFN2, s, q, st);
   return run_f32<MODE_ROWS, false, EPI_STORE>(FLOWMOE_K_FFN2, s, q, st);
 }
 
@@ -1595,9 +1652,9 @@ hipError_t launch_expert_ffn_dgrad(const Shape& s, const void* dy_disp, const vo
     p.ldaux = HW;
     if (bf) {
       if (swiglu)
-        FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, true, EPI_SWIGLU_BWD>(FLOWMOE_K_DGRAD1, s, p, st)));
+        FLOWMOE_TRY((run_rows<true, EPI_SWIGLU_BWD>(FLOWMOE_K_DGRAD1, s, p, st)));
       else
-        FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, true, EPI_GELU_BWD>(FLOWMOE_K_DGRAD1, s, p, st)));
+        FLOWMOE_TRY((run_rows<true, EPI_GELU_BWD>(FLOWMOE_K_DGRAD1, s, p, st)));
     } else {
       if (swiglu)
         FLOWMOE_TRY((run_f32<MODE_ROWS, true, EPI_SWIGLU_BWD>(FLOWMOE_K_DGRAD1, s, p, st)));
@@ -1620,7 +1677,7 @@ hipError_t launch_expert_ffn_dgrad(const Shape& s, const void* dy_disp, const vo
     p.C0 = dx_disp;
     p.ldc = M;
     if (bf)
-      FLOWMOE_TRY((run_gemm_bf16<MODE_ROWS, true, true, EPI_STORE>(FLOWMOE_K_DGRAD2, s, p, st)));
+      FLOWMOE_TRY((run_rows<true, EPI_STORE>(FLOWMOE_K_DGRAD2, s, p, st)));
     else
       FLOWMOE_TRY((run_f32<MODE_ROWS, true, EPI_STORE>(FLOWMOE_K_DGRAD2, s, p, st)));
   }
@@ -1679,7 +1736,7 @@ hipError_t launch_expert_ffn_wgrad(const Shape& s, int R, const void* dy_disp, c
     p.a_sstride = rows * H;
     p.b_sstride = rows * M;
     if (bf)
-      FLOWMOE_TRY((run_gemm_bf16<MODE_KSUM, false, false, EPI_WGRAD>(FLOWMOE_K_WGRAD2, s, p, st)));
+      FLOWMOE_TRY((run_ksum<EPI_WGRAD>(FLOWMOE_K_WGRAD2, s, p, st)));
     else
       FLOWMOE_TRY((run_f32<MODE_KSUM, false, EPI_WGRAD>(FLOWMOE_K_WGRAD2, s, p, st)));
   }
@@ -1702,7 +1759,7 @@ hipError_t launch_expert_ffn_wgrad(const Shape& s, int R, const void* dy_disp, c
     p.a_sstride = rows * M;
     p.b_sstride = rows * HW;
     if (bf)
-      FLOWMOE_TRY((run_gemm_bf16<MODE_KSUM, false, false, EPI_WGRAD>(FLOWMOE_K_WGRAD1, s, p, st)));
+      FLOWMOE_TRY((run_ksum<EPI_WGRAD>(FLOWMOE_K_WGRAD1, s, p, st)));
     else
       FLOWMOE_TRY((run_f32<MODE_KSUM, false, EPI_WGRAD>(FLOWMOE_K_WGRAD1, s, p, st)));
   }

@@ -33,8 +33,8 @@ import re
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 GEMM_SOURCES = ("csrc/gemm.hip", "csrc/common.hpp")
-GEMM_KERNEL = "gemm_bf16_kernel"
-GATE_GEMM = ", 6, "  # epilogue 6: the gate backward's dW_g partials, not an expert GEMM
+GEMM_KERNEL = "gemm_bf16_"
+GATE_GEMM = "ksum_kernel<6, "  # epilogue 6: the gate backward's dW_g partials, not an expert GEMM
 
 
 def expert_gemm(name: str) -> bool:

@@ -837,3 +837,48 @@ def test_expert_ffn_bf16_row_classes(M, H, act, layout, gemm_tiles):
         assert torch.equal(t, got["narrow"][n]), n
         g = host(t)
         assert_close(g[:nl] if t.dim() == 2 else g, want[n][:nl] if t.dim() == 2 else want[n], "bf16", n)
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("cnt", [[0, 1, 63, 64, 65, 127, 128, 129, 192, 255, 256, 257], [128] * 16,
+                                 [128] * 15 + [129], [256] * 16, [256] * 15 + [257]])
+@pytest.mark.parametrize("layout", ["packed", "padded"])
+def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
+    """The tile shape the row kernel chooses from the counts (padded: from the
+    capacity): every row class of the 128 x 128 tiles, and with 16 column tiles
+    the last launch of one round and the first of more for the 128- and the
+    256-row tiles. Forward and input gradients bit-identical to the forced
+    256 x 256 tiles, h against 64 bits."""
+    need_gpu()
+    d, bf = dev(), torch.bfloat16
+    E, M, H, T, C = len(cnt), 72, 2048, sum(cnt), max(cnt)
+    rt = oracle.route(np.repeat(np.arange(E), cnt)[:, None], E, C, layout)
+    rows, HW = rt["rows"], 2 * H if act == "swiglu" else H
+    rng = np.random.default_rng(5)
+    x, dy = (torch.from_numpy(oracle.dispatch(rng.standard_normal((T, M)), rt["row_src"], 1)).to(d).to(bf)
+             for _ in range(2))
+    w1, w3, w2 = (torch.from_numpy(rng.standard_normal(sh) * 0.1).to(d).to(bf)
+                  for sh in ((E, M, H), (E, M, H), (E, H, M)))
+    w3 = w3 if act == "swiglu" else None
+    counts, offsets = (torch.from_numpy(rt[n].astype(np.int32)).to(d) for n in ("counts", "offsets"))
+    s = _shape(T, M, H, E, 1, C, "bf16", act, layout)
+    nws = L.flowmoe_workspace_bytes(s, L.WS_FFN_BWD)
+    ws = torch.empty(nws, dtype=torch.uint8, device=d)
+    got = {}
+    for tiles in ("auto", "wide"):
+        gemm_tiles(tiles)
+        o = {n: torch.full((rows, c), 5.0, dtype=bf, device=d)
+             for n, c in (("h", HW), ("a", H), ("y", M), ("dx", M))}
+        dw1, dw2, dw3 = (torch.zeros(sh, device=d) for sh in ((E, M, H), (E, H, M), (E, M, H)))
+        L.flowmoe_expert_ffn(s, x, counts, offsets, w1, w3, w2, o["h"], o["a"], o["y"])
+        L.flowmoe_expert_ffn_bwd(s, dy, x, o["h"], o["a"], counts, offsets, w1, w3, w2, o["dx"], dw1,
+                                 dw3 if act == "swiglu" else None, dw2, 0, ws, nws)
+        got[tiles] = o
+    torch.cuda.synchronize()
+    for n in got["auto"]:
+        assert torch.equal(got["auto"][n], got["wide"][n]), n
+    h = host(got["auto"]["h"])
+    for e, (o, c) in enumerate(zip(rt["offsets"], cnt)):
+        ref = host(x[o:o + c]) @ np.concatenate([host(w[e]) for w in (w1, w3) if w is not None], axis=1)
+        # one rounding to bf16 (2^-9) of an fp32 sum of 72 products
+        assert_close(h[o:o + c], ref, "bf16", f"h[{e}]", tol=2.0 ** -8)
