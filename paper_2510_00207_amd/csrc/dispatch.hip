@@ -29,11 +29,12 @@ template <int V>
 struct KConst {
   static constexpr int value = V;
 };
-// f(KConst<KM>) with KM the smallest of 2, 4, 8 that is >= k
+// f(KConst<KM>) with KM the smallest of 2, 4, 6, 8 that is >= k
 template <typename F>
 __host__ void with_kmax(int k, F&& f) {
   if (k <= 2) f(KConst<2>{});
   else if (k <= 4) f(KConst<4>{});
+  else if (k <= 6) f(KConst<6>{});
   else f(KConst<8>{});
 }
 
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(
     for (int v = lane; v < vecs; v += 64) st16<NT>(x_disp + r * vecs + v, z);
     return;
   }
-  const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const long t = (long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= T) return;
   int sl[KM];
   bool any = false;
@@ -311,10 +312,23 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(
   }
 }
 
+// steps of 512 elements loaded together: 4 in the non-temporal (>= 256 MB)
+// bf16 calls of tokens with at most two experts, else 2 (bf16) or 1
+template <typename TE, int KM, bool NT>
+__host__ __device__ constexpr int row_steps() {
+  return sizeof(TE) == 2 ? ((NT && KM <= 2) ? 4 : 2) : 1;
+}
+
 // y[t] = sum_j w[t][j] * src[slot[t][j]] over kept j (w == nullptr: weight 1).
-// One wave per token, 8 elements per lane step; the k source rows of U
-// steps are all loaded before any is used (every load issued, from
-// in-bounds addresses), so each lane has k * U loads in flight. GATE
+// One wave per token and segment of U steps of 512 elements, 8 a lane; the k
+// source rows of the segment are all loaded before any is used (every load
+// issued, from in-bounds addresses), so each lane has k * U loads in flight.
+// Memory bounds it. A wave per token walking its segments one after the other
+// left the chip to 16 waves a CU that load and drain in step: with a wave a
+// segment, the token in scalar registers and arrays of 6 for k = 5 and 6, T = 4096,
+// M = 2048, k = 6: combine, its backward, dispatch and gate backward 135 -> 127 us
+// (the scalar token and the arrays of 6 alone: 134.7), and 122 with the combine
+// backward split alike. GATE
 // (dispatch backward of the layer): also adds the gate's share dl_t W_g^T,
 // with dl_t taken from the selection (gidx), its weights (gw) and their
 // gradients (gdw), and W_g^T given transposed in float (wgt, E x M).
@@ -327,7 +341,9 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(
     const TE* __restrict__ src, const int32_t* __restrict__ slot, const float* __restrict__ w,
     TE* __restrict__ y, int T, int M, int k, int kl, const int32_t* __restrict__ gidx,
     const float* __restrict__ gw, const float* __restrict__ gdw, const TE* __restrict__ wgt) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int U = row_steps<TE, KM, NT>();
+  const int segs = (M + 512 * U - 1) / (512 * U);
+  const int t = blockIdx.x / segs * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= T) return;
   const int lane = threadIdx.x & 63;
   int sl[KM];
@@ -356,10 +372,8 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(
     for (int j = 0; j < KM; ++j)
       if (j < k) gl[j] = gl[j] * (gdw[(long)t * k + j] - s);
   }
-  // steps of 512 elements loaded together: 4 in the non-temporal (>= 256 MB)
-  // bf16 calls of tokens with at most two experts, else 2 (bf16) or 1
-  constexpr int U = sizeof(TE) == 2 ? ((NT && KM <= 2) ? 4 : 2) : 1;
-  for (int m0 = lane * 8; m0 < M; m0 += 64 * 8 * U) {
+  const int m0 = blockIdx.x % segs * (512 * U) + lane * 8;
+  if (m0 < M) {
     decltype(raw8_load(src)) raw[U][KM];
     decltype(raw8_load(src)) yold[ADD ? U : 1];
     decltype(raw8_load(src)) graw[GATE ? U : 1][GATE ? KM : 1];
@@ -414,12 +428,15 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(
 }
 
 // combine backward, token part: dy_disp[slot] = w * dy[t], d_w = <dy[t], y_disp[slot]>
-// (kl as in combine_rows_kernel)
+// (kl as in combine_rows_kernel). tw waves of a block share a token, one a segment of its
+// rows (at most four, then walking segments), their partial dots added in order
+// through LDS; what it measured is with combine_rows_kernel.
 template <typename TE, int KM, bool NT>  // KM >= k: size of the per-token arrays
 __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const TE* __restrict__ dy, const TE* __restrict__ y_disp, const int32_t* __restrict__ slot,
     const float* __restrict__ w, const int32_t* __restrict__ counts, TE* __restrict__ dy_disp,
-    float* __restrict__ dw, int T, int M, int k, int kl, int E, int C, int token_blocks) {
+    float* __restrict__ dw, int T, int M, int k, int kl, int E, int C, int token_blocks,
+    int tw) {
   const int lane = threadIdx.x & 63;
   if ((int)blockIdx.x >= token_blocks) {
     // padded layout: zero rows [e*C + counts[e], (e+1)*C)
@@ -431,23 +448,24 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     for (int m = lane * 8; m < M; m += 64 * 8) store8_t<NT>(dy_disp + r * M + m, z);
     return;
   }
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave & (tw - 1);
+  const int t = (blockIdx.x * 4 + wave) / tw;
+  const bool live = t < T;  // (a wave past the last token still meets the barrier)
   int sl[KM];
   float wt[KM], dot[KM];
 #pragma unroll
   for (int j = 0; j < KM; ++j) {
     dot[j] = 0.f;
-    if (j < k) {
+    if (j < k && live) {
       sl[j] = slot[(long)t * k + j];
       wt[j] = w[(long)t * k + j];
     }
   }
   // dy and the k rows of y_disp of U steps loaded before any is used
-  // steps of 512 elements loaded together: 4 in the non-temporal (>= 256 MB)
-  // bf16 calls of tokens with at most two experts, else 2 (bf16) or 1
-  constexpr int U = sizeof(TE) == 2 ? ((NT && KM <= 2) ? 4 : 2) : 1;
-  for (int m0 = lane * 8; m0 < M; m0 += 64 * 8 * U) {
+  // (the same steps for both stream kinds: they fix the order of the sums)
+  constexpr int U = row_steps<TE, KM, false>();
+  const int m_end = live ? M : 0;
+  for (int m0 = part * (512 * U) + lane * 8; m0 < m_end; m0 += tw * (512 * U)) {
     decltype(raw8_load(dy)) graw[U], raw[U][KM];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -478,14 +496,35 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
       }
     }
   }
+  __shared__ float part_dot[4][KM];
 #pragma unroll
   for (int j = 0; j < KM; ++j) {
-    if (j < k) {
+    if (j < k && live) {
       float d = dot[j];
       for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off, 64);
-      if (lane == 0) dw[(long)t * k + j] = (sl[j] >= 0) ? d : 0.f;
+      if (lane == 0) part_dot[wave][j] = (sl[j] >= 0) ? d : 0.f;
     }
   }
+  __syncthreads();
+  if (live && part == 0 && lane < k) {
+    float d = part_dot[wave][lane];
+    for (int q = 1; q < tw; ++q) d += part_dot[wave + q][lane];
+    dw[(long)t * k + lane] = d;
+  }
+}
+
+// waves a token of combine_bwd_kernel: one a segment of its rows, at most 4
+template <typename TE, int KM>
+int bwd_waves(const Shape& s) {
+  constexpr int span = 512 * row_steps<TE, KM, false>();
+  return s.M <= span ? 1 : s.M <= 2 * span ? 2 : 4;
+}
+
+// blocks of combine_rows_kernel: four tokens by one segment of their rows
+template <typename TE, int KM, bool NT>
+dim3 combine_grid(const Shape& s) {
+  constexpr int span = 512 * row_steps<TE, KM, NT>();
+  return dim3((unsigned)((s.T + 3) / 4) * (unsigned)((s.M + span - 1) / span));
 }
 
 }  // namespace
@@ -547,19 +586,18 @@ hipError_t launch_combine(const Shape& s, const void* y_disp, const int32_t* slo
                           void* y, hipStream_t st) {
   if (s.T == 0) return hipSuccess;
   const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  const int blocks = (s.T + 3) / 4;
   return traced(FLOWMOE_K_COMBINE, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;
       if (s.dtype == FLOWMOE_BF16)
         with_nt(s, s.rows, [&](auto ntc) {
           hipLaunchKernelGGL((combine_rows_kernel<bf16_t, false, KMV, false, decltype(ntc)::value>),
-                             dim3(blocks), dim3(256), 0, st, (const bf16_t*)y_disp, slot, w,
-                             (bf16_t*)y, s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
+                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
+                             (const bf16_t*)y_disp, slot, w, (bf16_t*)y, s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
         });
       else
-        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, false, false>), dim3(blocks),
-                           dim3(256), 0, st, (const float*)y_disp, slot, w, (float*)y, s.T, s.M,
+        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, false, false>),
+                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)y_disp, slot, w, (float*)y, s.T, s.M,
                            s.k, kl, nullptr, nullptr, nullptr, nullptr);
     });
   });
@@ -574,19 +612,19 @@ hipError_t launch_dispatch_bwd_add(const Shape& s, const void* dx_disp, const in
                                    void* dx, hipStream_t st) {
   if (s.T == 0) return hipSuccess;
   const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  const int blocks = (s.T + 3) / 4;
   return traced(FLOWMOE_K_COMBINE, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;
       if (s.dtype == FLOWMOE_BF16)
         with_nt(s, s.rows, [&](auto ntc) {
           hipLaunchKernelGGL((combine_rows_kernel<bf16_t, false, KMV, true, decltype(ntc)::value>),
-                             dim3(blocks), dim3(256), 0, st, (const bf16_t*)dx_disp, slot, nullptr,
+                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
+                             (const bf16_t*)dx_disp, slot, nullptr,
                              (bf16_t*)dx, s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
         });
       else
-        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, true, false>), dim3(blocks),
-                           dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
+        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, true, false>),
+                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
                            s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
     });
   });
@@ -597,19 +635,19 @@ hipError_t launch_dispatch_bwd_gate(const Shape& s, const void* dx_disp, const i
                                     const void* wgt, void* dx, hipStream_t st) {
   if (s.T == 0) return hipSuccess;
   const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  const int blocks = (s.T + 3) / 4;
   return traced(FLOWMOE_K_COMBINE, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;
       if (s.dtype == FLOWMOE_BF16)
         with_nt(s, s.rows, [&](auto ntc) {
           hipLaunchKernelGGL((combine_rows_kernel<bf16_t, true, KMV, false, decltype(ntc)::value>),
-                             dim3(blocks), dim3(256), 0, st, (const bf16_t*)dx_disp, slot, nullptr,
+                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
+                             (const bf16_t*)dx_disp, slot, nullptr,
                              (bf16_t*)dx, s.T, s.M, s.k, kl, idx, w, dw, (const bf16_t*)wgt);
         });
       else
-        hipLaunchKernelGGL((combine_rows_kernel<float, true, KMV, false, false>), dim3(blocks),
-                           dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
+        hipLaunchKernelGGL((combine_rows_kernel<float, true, KMV, false, false>),
+                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
                            s.T, s.M, s.k, kl, idx, w, dw, (const float*)wgt);
     });
   });
@@ -620,24 +658,28 @@ hipError_t launch_combine_bwd(const Shape& s, const void* dy, const void* y_disp
                               const int32_t* offsets, void* dy_disp, float* dw, hipStream_t st) {
   (void)offsets;
   const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  const int token_blocks = (s.T + 3) / 4;
   const long fill_blocks = (s.layout == FLOWMOE_PADDED) ? ((long)s.E * s.C + 3) / 4 : 0;
-  const long blocks = token_blocks + fill_blocks;
-  if (blocks == 0) return hipSuccess;
+  if (s.T == 0 && fill_blocks == 0) return hipSuccess;
   return traced(FLOWMOE_K_COMBINE_BWD, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;
       if (s.dtype == FLOWMOE_BF16)
         with_nt(s, 2 * s.rows, [&](auto ntc) {
+          const int tw = bwd_waves<bf16_t, KMV>(s);
+          const long token_blocks = ((long)s.T * tw + 3) / 4;
           hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, KMV, decltype(ntc)::value>),
-                             dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t*)dy,
-                             (const bf16_t*)y_disp, slot, w, counts, (bf16_t*)dy_disp, dw, s.T, s.M,
-                             s.k, kl, s.E, s.C, token_blocks);
+                             dim3((unsigned)(token_blocks + fill_blocks)), dim3(256), 0, st,
+                             (const bf16_t*)dy, (const bf16_t*)y_disp, slot, w, counts,
+                             (bf16_t*)dy_disp, dw, s.T, s.M, s.k, kl, s.E, s.C, (int)token_blocks, tw);
         });
-      else
-        hipLaunchKernelGGL((combine_bwd_kernel<float, KMV, false>), dim3((unsigned)blocks),
-                           dim3(256), 0, st, (const float*)dy, (const float*)y_disp, slot, w, counts,
-                           (float*)dy_disp, dw, s.T, s.M, s.k, kl, s.E, s.C, token_blocks);
+      else {
+        const int tw = bwd_waves<float, KMV>(s);
+        const long token_blocks = ((long)s.T * tw + 3) / 4;
+        hipLaunchKernelGGL((combine_bwd_kernel<float, KMV, false>),
+                           dim3((unsigned)(token_blocks + fill_blocks)), dim3(256), 0, st,
+                           (const float*)dy, (const float*)y_disp, slot, w, counts, (float*)dy_disp,
+                           dw, s.T, s.M, s.k, kl, s.E, s.C, (int)token_blocks, tw);
+      }
     });
   });
 }

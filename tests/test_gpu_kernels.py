@@ -882,3 +882,50 @@ def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
         ref = host(x[o:o + c]) @ np.concatenate([host(w[e]) for w in (w1, w3) if w is not None], axis=1)
         # one rounding to bf16 (2^-9) of an fp32 sum of 72 products
         assert_close(h[o:o + c], ref, "bf16", f"h[{e}]", tol=2.0 ** -8)
+
+
+@pytest.mark.parametrize("dtype,k,M", [("f32", 1, 512), ("f32", 2, 520), ("f32", 5, 1544),
+                                       ("f32", 8, 2056), ("bf16", 1, 1024), ("bf16", 2, 1032),
+                                       ("bf16", 3, 2048), ("bf16", 4, 2056), ("bf16", 5, 1016),
+                                       ("bf16", 6, 2040), ("bf16", 7, 3080), ("bf16", 8, 4104)])
+@pytest.mark.parametrize("layout", ["packed", "padded"])
+@pytest.mark.parametrize("rows", ["auto", "nt"])
+def test_combine_row_segments(dtype, k, M, layout, rows):
+    """Rows of one to five segments (512 or 1024 elements; 2048 non-temporal
+    with at most two experts), ragged last ones among them, over tokens that
+    end inside a block: combine, dispatch backward and combine backward with 1, 2
+    and 4 waves a token against the oracle."""
+    need_gpu()
+    rng = np.random.default_rng(11)
+    T, E = 37, 8
+    idx, w = oracle.topk_select(rng.standard_normal((T, E)), k)
+    C = oracle.capacity(T, E, k, 0.8)  # (some dropped)
+    rt = oracle.route(idx, E, C, layout)
+    n, d = rt["rows"], dev()
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ys, dy, dxs = (torch.from_numpy(rng.standard_normal(sh)).to(d).to(td)
+                   for sh in ((n, M), (T, M), (n, M)))
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(d).to(torch.int32)
+    slot, counts, offsets = i32(rt["slot"]), i32(rt["counts"]), i32(rt["offsets"])
+    w_t = torch.from_numpy(w).to(d).float()
+    s = _shape(T, M, 8, E, k, C, dtype, layout=layout)
+    y, dx = (torch.full((T, M), 7.0, dtype=td, device=d) for _ in range(2))
+    dys, dtw = torch.full((n, M), 7.0, dtype=td, device=d), torch.full((T, k), 7.0, device=d)
+    L.flowmoe_set_row_streams(rows)
+    try:
+        L.flowmoe_combine(s, ys, slot, w_t, y)
+        L.flowmoe_combine_bwd(s, dy, ys, slot, w_t, counts, offsets, dys, dtw)
+        L.flowmoe_dispatch_bwd(s, dxs, slot, dx)
+    finally:
+        L.flowmoe_set_row_streams("auto")
+    torch.cuda.synchronize()
+    w64 = host(w_t)
+    rdy, rdw = oracle.combine_bwd(host(dy), host(ys), rt["slot"], w64)
+    live = n if layout == "padded" else int(rt["offsets"][-1])
+    assert_close(host(y), oracle.combine(host(ys), rt["slot"], w64), dtype, "y")
+    assert_close(host(dx), oracle.dispatch_bwd(host(dxs), rt["slot"]), dtype, "dx")
+    assert_close(host(dys)[:live], rdy[:live], dtype, "dy_disp")
+    assert torch.all(dys[live:] == 7.0)
+    # exact products of the inputs, at most 4104 of them summed in fp32 by 64 lanes of at
+    # most 72: each lane's sum is off by 72 x 2^-24 of its terms at most
+    assert_close(host(dtw), rdw, "f32", "d_topk_w")
