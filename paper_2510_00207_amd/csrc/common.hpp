@@ -192,28 +192,6 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* base, long bytes) {
   return d;
 }
 
-// One wave: 64 x 16 bytes from the buffer (per-lane byte offset voff) into
-// the 1 KB LDS block at LDS byte address m0v (wave-uniform, computed in
-// scalar registers: a vector-to-scalar move per load had put a dependent
-// chain in front of every load), lane-ordered. Issued as inline assembly so
-// that the compiler does not pair it with the LDS reads of other stages: the
-// kernel orders them itself with s_waitcnt vmcnt and barriers.
-__device__ __forceinline__ void dma16(u32x4 d, unsigned m0v, unsigned voff) {
-  // the descriptor is wave-uniform; say so, so that it sits in scalar registers
-  d.x = __builtin_amdgcn_readfirstlane(d.x);
-  d.y = __builtin_amdgcn_readfirstlane(d.y);
-  d.z = __builtin_amdgcn_readfirstlane(d.z);
-  d.w = __builtin_amdgcn_readfirstlane(d.w);
-  unsigned saved;  // m0 is reserved: keep the compiler's value intact
-  asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\t"
-      "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(voff), "s"(d), "s"(m0v)
-      : "memory");
-}
-
-
 template <int N>
 __device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
@@ -221,21 +199,38 @@ __device__ __forceinline__ void wait_vm() {  // at most N vector-memory operatio
 __device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
   __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
 }
-// N such loads of one buffer in a row, N = 1, 2 or 4, into LDS blocks STEP bytes
-// apart (one save of m0, one scalar add a load)
+// One wave: N (1, 2 or 4) loads of 64 x 16 bytes from one buffer (per-lane byte
+// offsets voff) into the 1 KB LDS blocks at LDS byte address m0v (wave-uniform,
+// computed in scalar registers: a vector-to-scalar move per load had put a
+// dependent chain in front of every load), m0v + STEP, ..., lane-ordered. Issued
+// as inline assembly so that the compiler does not pair them with the LDS reads
+// of other stages: the kernel orders them itself with s_waitcnt vmcnt and
+// barriers.
+//
+// The compiler's hazard pass does not look into the block, which therefore holds
+// the wait states itself: GFX9 needs 5 between a VALU write of a scalar register
+// and a vector-memory read of it, and where scalar registers run short the
+// compiler moves descriptor words into them (v_readfirstlane, v_readlane) right
+// before the block. Two s_mov and s_nop 2 make the 5.
+#define FLOWMOE_DMA_BEGIN(M0) "s_mov_b32 %0, m0\n\ts_mov_b32 m0, " M0 "\n\ts_nop 2\n\t"
 template <int N, int STEP>
 __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned (&voff)[N]) {
-  unsigned saved;
+  // the descriptor is wave-uniform; say so, so that it sits in scalar registers
+  d.x = __builtin_amdgcn_readfirstlane(d.x);
+  d.y = __builtin_amdgcn_readfirstlane(d.y);
+  d.z = __builtin_amdgcn_readfirstlane(d.z);
+  d.w = __builtin_amdgcn_readfirstlane(d.w);
+  unsigned saved;  // m0 is reserved: keep the compiler's value intact
   if constexpr (N == 1)
     asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\t"
+        FLOWMOE_DMA_BEGIN("%3")
         "buffer_load_dwordx4 %1, %2, 0 offen lds\n\ts_mov_b32 m0, %0"
         : "=&s"(saved)
         : "v"(voff[0]), "s"(d), "s"(m0v)
         : "memory");
   else if constexpr (N == 2)
     asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\t"
+        FLOWMOE_DMA_BEGIN("%4")
         "buffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %5\n\t"
         "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
         : "=&s"(saved)
@@ -243,7 +238,7 @@ __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned 
         : "memory", "scc");
   else
     asm volatile(
-        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %6\n\t"
+        FLOWMOE_DMA_BEGIN("%6")
         "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
         "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
         "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
@@ -252,6 +247,7 @@ __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned 
         : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(d), "s"(m0v), "i"(STEP)
         : "memory", "scc");
 }
+#undef FLOWMOE_DMA_BEGIN
 
 // barrier that orders LDS accesses only (loads from and stores to global memory
 // stay in flight)

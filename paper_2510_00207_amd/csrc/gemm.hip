@@ -617,8 +617,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
       o = ok ? o : 0xFFFFFFF0u;
       o2 = ok ? o2 : 0xFFFFFFF0u;
     }
-    dma16(r, dst, o);
-    if (both) dma16(r, dst + 8192, o2);
+    if (both) {
+      const unsigned off[2] = {o, o2};
+      dma16_row<2, 8192>(r, dst, off);
+    } else {
+      const unsigned off[1] = {o};
+      dma16_row<1, 0>(r, dst, off);
+    }
   };
   auto issue_a_to = [&](int t, int h, unsigned dst, bool both) {
     if constexpr (A_KC) {
