@@ -211,7 +211,8 @@ __device__ __forceinline__ void wait_lgkm0() {  // no LDS operation outstanding
 // the wait states itself: GFX9 needs 5 between a VALU write of a scalar register
 // and a vector-memory read of it, and where scalar registers run short the
 // compiler moves descriptor words into them (v_readfirstlane, v_readlane) right
-// before the block. Two s_mov and s_nop 2 make the 5.
+// before the block (two s_mov and s_nop 2 make the 5), and 1 between a write of
+// m0 and an LDS-DMA load (s_nop 0 after the s_add).
 #define FLOWMOE_DMA_BEGIN(M0) "s_mov_b32 %0, m0\n\ts_mov_b32 m0, " M0 "\n\ts_nop 2\n\t"
 template <int N, int STEP>
 __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned (&voff)[N]) {
@@ -231,7 +232,7 @@ __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned 
   else if constexpr (N == 2)
     asm volatile(
         FLOWMOE_DMA_BEGIN("%4")
-        "buffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %5\n\t"
+        "buffer_load_dwordx4 %1, %3, 0 offen lds\n\ts_add_u32 m0, m0, %5\n\ts_nop 0\n\t"
         "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
         : "=&s"(saved)
         : "v"(voff[0]), "v"(voff[1]), "s"(d), "s"(m0v), "i"(STEP)
@@ -239,9 +240,9 @@ __device__ __forceinline__ void dma16_row(u32x4 d, unsigned m0v, const unsigned 
   else
     asm volatile(
         FLOWMOE_DMA_BEGIN("%6")
-        "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
-        "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
-        "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\t"
+        "buffer_load_dwordx4 %1, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %2, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\ts_nop 0\n\t"
+        "buffer_load_dwordx4 %3, %5, 0 offen lds\n\ts_add_u32 m0, m0, %7\n\ts_nop 0\n\t"
         "buffer_load_dwordx4 %4, %5, 0 offen lds\n\ts_mov_b32 m0, %0"
         : "=&s"(saved)
         : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(d), "s"(m0v), "i"(STEP)

@@ -3,10 +3,11 @@
 The loads (buffer_load ... lds) are issued from inline assembly, which the
 compiler's hazard pass does not look into, so the blocks carry the wait states
 themselves. On GFX9 a VALU write of a scalar register (v_readfirstlane,
-v_readlane: where the compiler takes a descriptor word out of a vector
-register right before the block) needs 5 wait states before a vector-memory
-instruction reads that register. An instruction is one wait state, s_nop N is
-N + 1. CPU only: compiles the sources that issue such loads for gfx950 and
+v_readlane: where the compiler takes a descriptor word out of a vector register
+right before the block) needs 5 wait states before a vector-memory instruction
+reads that register, and a scalar write of m0 needs 1 before an LDS-DMA load,
+which takes its LDS address from m0. An instruction is one wait state, s_nop N
+is N + 1. CPU only: compiles the sources that issue such loads for gfx950 and
 walks back from every load."""
 import os
 import re
@@ -76,6 +77,13 @@ def valu_hazards(ins):
     return bad, loads
 
 
+def m0_hazards(ins):
+    """The loads right after an instruction that writes m0 (or a label)."""
+    loads = [i for i, x in enumerate(ins) if x and LOAD.match(x)]
+    return [(i, ins[i - 1]) for i in loads
+            if ins[i - 1] is None or re.match(r"s_\w+ m0,", ins[i - 1])]
+
+
 @pytest.fixture(scope="module")
 def listing(tmp_path_factory):
     """The gfx950 assembly of a source, compiled with the build's own flags."""
@@ -103,6 +111,8 @@ def test_checker_sees_the_hazard():
     assert valu_hazards(far) == ([], 1)
     assert valu_hazards([None, "s_nop 3", load]) == ([(2, load)], 1)
     assert valu_hazards([None, "s_nop 4", load]) == ([], 1)
+    assert m0_hazards(near + [load]) == [(3, near[2])]
+    assert m0_hazards(far) == []
     assert scalar_dest("v_cmp_gt_i32_e64 s[4:5], v1, v2") == {4, 5}
     assert scalar_dest("v_add_co_u32_e64 v1, s[8:9], v2, v3") == {8, 9}
 
@@ -112,3 +122,9 @@ def test_descriptor_wait_states(listing, name):
     bad, loads = valu_hazards(listing(name))
     assert loads > 100, loads
     assert not bad, f"{len(bad)} of {loads} loads, the first: {bad[:3]}"
+
+
+@pytest.mark.parametrize("name", ["gemm", "attn"])
+def test_m0_wait_states(listing, name):
+    bad = m0_hazards(listing(name))
+    assert not bad, f"{len(bad)} loads, the first: {bad[:3]}"
