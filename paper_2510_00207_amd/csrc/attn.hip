@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
   floatx16 o[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) o[db] = zero16();
-  float m = -INFINITY, l = 0.0f;  // l: this lane's share of the row's sum
+  float m = -INFINITY, l = 0.0f;
 
   int rbase = row_base<D>(lq, h2), tb0 = tr_base<D>(lane, 0), tb1 = tr_base<D>(lane, 1);
   auto mask = [&](floatx16 (&s)[2], int kb0) {
@@ -364,17 +364,19 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
     dma.load(Vg, kend - 64 * (t + 1), (2 + (st ^ 1)) * TB);
     if (!live) return;
     unsigned pw[16];  // the 32 probabilities of this lane, bf16 pairs
-    float rs[2] = {0.0f, 0.0f};
+    // (the sum in key order, then the lane pair's two halves, tile by tile: results do
+    // not depend on how the step is scheduled)
+    float rsum = 0.0f;
     auto exps = [&](int q0s, int q1s) {  // scores q0s .. q1s - 1: exponentials, sum, bf16
 #pragma unroll
       for (int q = q0s; q < q1s; q += 2) {
         const float p0 = exp2_fast(fmaf(sc[q >> 4][q & 15], a.c2, -m));
         const float p1 = exp2_fast(fmaf(sc[q >> 4][(q & 15) + 1], a.c2, -m));
-        rs[0] += p0;
-        rs[1] += p1;
+        rsum += p0;
+        rsum += p1;
         pw[q >> 1] = pack_bf16x2(p0, p1);
         // (computed here, not where they are used)
-        asm volatile("" : "+v"(pw[q >> 1]), "+v"(rs[0]), "+v"(rs[1]));
+        asm volatile("" : "+v"(pw[q >> 1]), "+v"(rsum));
       }
     };
     __builtin_amdgcn_sched_barrier(0);
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
       asm volatile("" : "+v"(mx));
       __builtin_amdgcn_sched_barrier(0);
     }
-    l += rs[0] + rs[1];
+    l += pair_sum(rsum);
     if (next) move_ref(mx);
   };
   for (int t = 0; t < nk; t += 2) {
@@ -426,7 +428,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
     if (t + 1 < nk) step(t + 1, Stage<1>{});
   }
   if (qw < a.N) {
-    l = pair_sum(l);
     const float inv = 1.0f / l;
     bf16_t* Og = a.out + (tok0 + qw) * a.M + (long)hd * D;
 #pragma unroll

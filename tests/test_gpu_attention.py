@@ -6,6 +6,8 @@ sequences, both head widths, causal and bidirectional; and the full-size
 large-layer attention (4 sequences of 4096 tokens, 32 heads of 128, causal)
 on sampled (sequence, head) pairs. bf16 results within 2e-2 max relative
 error, the float log-sum-exp within 1e-4."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -102,6 +104,42 @@ def test_attention_causal_rows_ignore_later_tokens():
     assert torch.equal(outs[0][0][:T - 1], outs[1][0][:T - 1])
     assert torch.equal(outs[0][1][:, :T - 1], outs[1][1][:, :T - 1])
     assert not torch.equal(outs[0][0][T - 1], outs[1][0][T - 1])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("hd", [64, 128])
+def test_attention_row_sum_order(hd, causal):
+    """The softmax's row sums are added in one order, whatever the kernel's schedule:
+    in a 64-key tile the 32 probabilities of either half (keys 0-3, 8-11, ... and
+    4-7, 12-15, ...) in key order, then the halves, then the tiles. With key 0 of
+    probability 1 and all others v < 2^-24, the 31 others of its half round away
+    one by one, the 32 of the other half add up, and so do the 64 of every later
+    tile: the log-sum-exp is log(1 + v (32 + 64 (tiles - 1))). Sums that are
+    split in another way keep more of the first half's."""
+    need_gpu()
+    L = _lib()
+    d = dev()
+    T, heads = 128, 1
+    b = 8.6875 * math.sqrt(hd / 64)
+    b = float(torch.tensor(b).bfloat16())
+    v = math.exp(-16.0 * b / math.sqrt(hd))
+    assert 2.0 ** -26 < v < 2.0 ** -24
+    qkv = torch.zeros(T, 3 * hd, device=d)
+    qkv[:, 0] = 16.0  # q . k = -16 b for every key but the first
+    qkv[1:, hd] = -b
+    s = L.make_shape(T, hd, 64, 1, 1, 0, L.BF16)
+    m = L.make_mha_shape(T, heads, hd, causal)
+    o = torch.zeros(T, hd, dtype=torch.bfloat16, device=d)
+    lse = torch.zeros(heads, T, device=d)
+    L.flowmoe_attention_fwd(s, m, qkv.bfloat16(), o, lse)
+    torch.cuda.synchronize()
+    got = host(lse)[0]
+    for t in (63, 127):  # (rows that see whole tiles, causal or not)
+        tiles = (t + 1) // 64 if causal else T // 64
+        want = v * (32 + 64 * (tiles - 1))
+        # each tile's sum is rounded to a multiple of 2^-23 (6e-8 off at most); two
+        # chains a half, added at the end, would keep 16 v = 4.5e-7 more
+        assert abs(got[t] - want) < 2e-7, (t, got[t], want)
 
 
 def test_attention_is_deterministic():
