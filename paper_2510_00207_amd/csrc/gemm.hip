@@ -79,6 +79,9 @@ struct GemmParams {
   // streaming kernel, row mode: an expert's light row tiles walked with its
   // heavy ones (1) or after every heavy tile (0)
   int joined;
+  // KSUM, bf16: reduction rows that one buffer descriptor covers (buffer_piece);
+  // longer reductions run in pieces of so many
+  int piece;
 };
 
 
@@ -567,16 +570,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
   int k_lim = 0;          // ROWS: reduction length (of the part before the split)
   if constexpr (MODE == MODE_ROWS) {
     ra = make_rsrc(A + (long)row0 * p.lda, (long)(cnt_e - mt * BM) * p.lda * 2);
-    const long span = (long)p.K * p.ldb;
+    k_lim = min(p.K, p.ksplit);
     if constexpr (B_KC) {
-      const long valid = (long)(p.N - n0) * p.ldb * 2;
+      const long valid = (long)min(p.N - n0, BN) * p.ldb * 2;
       rb0 = make_rsrc(B0 + (long)e * p.b_estride + (long)n0 * p.ldb, valid);
       rb1 = B1 != nullptr ? make_rsrc(B1 + (long)e * p.b_estride + (long)n0 * p.ldb, valid) : rb0;
     } else {
+      const long span = (long)p.K * p.ldb;
       rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
       rb1 = DUAL ? make_rsrc(B1 + (long)e * p.b_estride + n0, (span - n0) * 2) : rb0;
     }
-    k_lim = min(p.K, p.ksplit);
     nk = (k_lim + WBK - 1) / WBK;
     if (B_KC && p.K > p.ksplit) {
       nk0 = nk;
@@ -585,21 +588,28 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
     // a padding-only tile (padded layout) has nothing to reduce: zeros
     if (cnt_e <= mt * BM) nk = 0;
   } else {
-    const int m0 = mt * BM;
-    ra = make_rsrc(A + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
-    rb0 = make_rsrc(B0 + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
+    const int m0 = mt * BM, n = min(cnt_e, p.piece);
+    ra = make_rsrc(A + (long)row0 * p.lda + m0, ((long)n * p.lda - m0) * 2);
+    rb0 = make_rsrc(B0 + (long)row0 * p.ldb + n0, ((long)n * p.ldb - n0) * 2);
     rb1 = rb0;
-    nk = (cnt_e + WBK - 1) / WBK;
+    nk = (n + WBK - 1) / WBK;
   }
-  auto bind_segment = [&](int g) {  // KSUM: segment g (g >= 1) of the reduction
+  // KSUM: rows r0 .. r0 + piece - 1 of segment g of the reduction (g >= 1 or r0 > 0)
+  auto bind_rows = [&](int g, int r0) {
     row0 = g < 64 ? __builtin_amdgcn_readlane(seg_o, g) : seg_offset(p, g, e);
     cnt_e = clip_rows(row0, g < 64 ? __builtin_amdgcn_readlane(seg_c, g) : seg_count(p, g, e),
                       p.rows_cap);
-    const int m0 = mt * BM;
-    ra = make_rsrc(A + g * p.a_sstride + (long)row0 * p.lda + m0, ((long)cnt_e * p.lda - m0) * 2);
-    rb0 = make_rsrc(B0 + g * p.b_sstride + (long)row0 * p.ldb + n0, ((long)cnt_e * p.ldb - n0) * 2);
+    const int m0 = mt * BM, n = min(cnt_e - r0, p.piece);
+    const long r = (long)row0 + r0;
+    ra = make_rsrc(A + g * p.a_sstride + r * p.lda + m0, ((long)n * p.lda - m0) * 2);
+    rb0 = make_rsrc(B0 + g * p.b_sstride + r * p.ldb + n0, ((long)n * p.ldb - n0) * 2);
     rb1 = rb0;
-    nk = (cnt_e + WBK - 1) / WBK;
+    nk = (n + WBK - 1) / WBK;
+  };
+  auto drain = [] {  // every load and LDS read done before the stages are filled again
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
   };
 
   // Loads of half h of tile t's operand A or B. Chunks past the reduction
@@ -881,15 +891,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
     }
   };
   if constexpr (MODE == MODE_KSUM) {
-    if (p.nseg == 1 && nk <= NST) short_loop();
-    else for (int g = 0; g < p.nseg; ++g) {
-      if (g > 0) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();  // every load and LDS read of the last segment done before the refill
-        bind_segment(g);
+    if (p.nseg == 1 && nk <= NST && cnt_e <= p.piece) short_loop();
+    else {
+      for (int g = 0, r0 = 0;;) {
+        k_loop(IntC<2>{});
+        r0 += p.piece;
+        if (r0 >= cnt_e) {
+          r0 = 0;
+          if (++g >= p.nseg) break;
+        }
+        drain();
+        bind_rows(g, r0);
       }
-      k_loop(IntC<2>{});
     }
   } else {
     // light tiles, else live 64-row halves of this wave (wave-uniform): rows
@@ -902,9 +915,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
       else k_loop(IntC<1>{});
     }
   }
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();  // all loads landed and LDS reads done before the epilogue reuses the stages
+  drain();  // before the epilogue reuses the stages
   const int rows_t = MODE == MODE_ROWS ? rows_e - mt * BM : p.Mdim - mt * BM;
   gemm_epilogue<MODE, EPI, BM, NB>(p, acc, smem, e, mt, n0, row0, rows_e, cnt_e, wm, wn,
                                    BM > 128 && rows_t > 128 ? 2 : 1);
@@ -1332,6 +1343,10 @@ GemmParams base_params(const Shape& s, const int32_t* counts, const int32_t* off
   return p;
 }
 
+// Reduction rows of `ld` bf16 that a buffer descriptor's range (2^31 - 1 bytes)
+// covers, in whole k-tiles.
+int buffer_piece(long ld) { return (int)std::max<long>(WBK, 0x7FFFFFFFL / (2 * ld) / WBK * WBK); }
+
 std::atomic<int> g_tiles{FLOWMOE_TILES_AUTO};
 std::atomic<int> g_tile_order{FLOWMOE_TILE_ORDER_AUTO};
 
@@ -1367,8 +1382,9 @@ hipError_t run_rows(int kind, const Shape& s, GemmParams p, hipStream_t st) {
 }
 
 template <int EPI, bool NARROW>
-hipError_t launch_ksum(int kind, const Shape& s, const GemmParams& p, hipStream_t st) {
+hipError_t launch_ksum(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   constexpr int BN = NARROW ? 128 : 256;
+  p.piece = buffer_piece(std::max(p.lda, p.ldb));
   const long blocks = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + BN - 1) / BN);
   if (blocks == 0) return hipSuccess;
   return traced(kind, st, [&] {

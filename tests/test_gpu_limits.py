@@ -1,0 +1,47 @@
+"""Calls at the limits of the hardware's own sizes: reductions of more bytes than
+a buffer descriptor's range covers (2^31 - 1)."""
+import pytest
+import torch
+
+from gpu_helpers import dev, need_gpu
+from paper_2510_00207_amd import _lib as L
+from paper_2510_00207_amd.layer import MoELayer
+
+pytestmark = pytest.mark.gpu
+
+BF = torch.bfloat16
+
+
+def _rel(got, ref):
+    return float((got.double() - ref.double()).norm() / ref.double().norm())
+
+
+@pytest.mark.parametrize("R", [1, 2])
+def test_weight_gradients_beyond_descriptor_range(R):
+    """One expert of 140000 rows, H = 16384: 4.6 GB of dH in one chunk (past 2^32
+    bytes), 2.3 GB in each of two (past 2^31). Every row is in the sums."""
+    need_gpu()
+    d = dev()
+    T, M, H = 140000, 64, 16384
+    g = torch.Generator(device=d).manual_seed(3)
+    layer = MoELayer(T_total=T, M=M, H=H, E=1, k=1, R=R, f=1.0, device=d)
+    for name, std in (("x", 1.0), ("dy", 1.0), ("w1", 0.1), ("w2", 0.1), ("w_gate", 0.1)):
+        t = getattr(layer, name)
+        t.copy_(torch.randn(t.shape, generator=g, device=d) * std)
+    sc = torch.cuda.current_stream()
+    layer.forward(sc, sc)
+    layer.backward(sc, sc)
+    torch.cuda.synchronize()
+    w1, w2 = layer.w1[0].float(), layer.w2[0].float()
+    dw1, dw2 = torch.zeros(M, H, device=d), torch.zeros(H, M, device=d)
+    for t in range(0, T, 10000):
+        x, dy = layer.x[t:t + 10000].float(), layer.dy[t:t + 10000].float()
+        h = (x @ w1).requires_grad_()
+        a = torch.nn.functional.gelu(h)
+        (dh,) = torch.autograd.grad(a, h, dy @ w2.t().contiguous())
+        dw1 += x.t().contiguous() @ dh
+        dw2 += a.detach().t().contiguous() @ dy
+    # h, a and dH are rounded to bf16 (2^-9 each); the rows past 2^31 bytes are half of
+    # the sums
+    assert _rel(layer.dw1[0], dw1) < 1e-2
+    assert _rel(layer.dw2[0], dw2) < 1e-2
