@@ -79,8 +79,8 @@ struct GemmParams {
   // streaming kernel, row mode: an expert's light row tiles walked with its
   // heavy ones (1) or after every heavy tile (0)
   int joined;
-  // KSUM, bf16: reduction rows that one buffer descriptor covers (buffer_piece);
-  // longer reductions run in pieces of so many
+  // bf16: reduction rows of a non-K-contiguous operand that one buffer descriptor
+  // covers (buffer_piece); longer reductions run in pieces of so many
   int piece;
 };
 
@@ -508,7 +508,8 @@ __device__ __forceinline__ bf16x8 half_frag(const char* h, int base, int i, int 
 constexpr int kGemmSmem = 9 * kHalf;  // 144 KB
 
 // One tile of the kernels below. BM = 128: low tiles (row mode), light loops only.
-template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW, int BM>
+// PIECES (row mode): a B of more bytes than a buffer descriptor's range, in pieces.
+template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW, int BM, bool PIECES = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int ntiles, const LaneRows& lr) {
   constexpr int BN = NARROW ? 128 : 256;
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
@@ -576,7 +577,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
       rb0 = make_rsrc(B0 + (long)e * p.b_estride + (long)n0 * p.ldb, valid);
       rb1 = B1 != nullptr ? make_rsrc(B1 + (long)e * p.b_estride + (long)n0 * p.ldb, valid) : rb0;
     } else {
-      const long span = (long)p.K * p.ldb;
+      if constexpr (PIECES) k_lim = min(p.K, p.piece);
+      const long span = (long)k_lim * p.ldb;
       rb0 = make_rsrc(B0 + (long)e * p.b_estride + n0, (span - n0) * 2);
       rb1 = DUAL ? make_rsrc(B1 + (long)e * p.b_estride + n0, (span - n0) * 2) : rb0;
     }
@@ -605,6 +607,15 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
     rb0 = make_rsrc(B0 + g * p.b_sstride + r * p.ldb + n0, ((long)n * p.ldb - n0) * 2);
     rb1 = rb0;
     nk = (n + WBK - 1) / WBK;
+  };
+  // ROWS, M/N-contiguous B: k from kb on (kb > 0, a multiple of the piece)
+  auto bind_k = [&](int kb) {
+    k_lim = min(p.K - kb, p.piece);
+    ra = make_rsrc(A + (long)row0 * p.lda + kb, ((long)(cnt_e - mt * BM) * p.lda - kb) * 2);
+    const long b = (long)e * p.b_estride + (long)kb * p.ldb + n0, span = (long)k_lim * p.ldb - n0;
+    rb0 = make_rsrc(B0 + b, span * 2);
+    rb1 = DUAL ? make_rsrc(B1 + b, span * 2) : rb0;
+    nk = (k_lim + WBK - 1) / WBK;
   };
   auto drain = [] {  // every load and LDS read done before the stages are filled again
     asm volatile("" ::: "memory");
@@ -904,6 +915,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
         bind_rows(g, r0);
       }
     }
+  } else if constexpr (PIECES) {
+    for (int kb = 0;;) {
+      k_loop(IntC<2>{});
+      kb += p.piece;
+      if (kb >= p.K || nk == 0) break;
+      drain();
+      bind_k(kb);
+    }
   } else {
     // light tiles, else live 64-row halves of this wave (wave-uniform): rows
     // wm * 64 .. and 128 + wm * 64 ..
@@ -958,6 +977,23 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_rows_kernel(GemmParams p) {
   else if (shape == FLOWMOE_TILES_WIDE || DUAL)
     gemm_tile<MODE_ROWS, true, B_KC, EPI, false, 256>(p, smem, n256, lr);
   else if constexpr (!DUAL) gemm_tile<MODE_ROWS, true, B_KC, EPI, true, 256>(p, smem, n128, lr);
+}
+
+// The row mode over a B that exceeds a buffer descriptor's range (an expert's
+// weights of 2 GiB and more): 256 x 256 tiles, the reduction in pieces. Apart from
+// the kernel above, whose loops a piece loop around them makes spill (300 vector
+// registers).
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_rows_pieces_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem[kGemmSmem];
+  const int lane = threadIdx.x & 63;
+  const bool live = lane < p.E;
+  LaneRows lr;
+  lr.c = live ? seg_count(p, 0, lane) : 0;
+  lr.o = live ? seg_offset(p, 0, lane) : 0;
+  lr.r = live ? (p.padC ? p.padC : lr.c) : 0;
+  constexpr int NC = EPI == EPI_SWIGLU_FWD ? 128 : 256;
+  gemm_tile<MODE_ROWS, true, false, EPI, false, 256, true>(p, smem, (p.N + NC - 1) / NC, lr);
 }
 
 template <int EPI, bool NARROW>
@@ -1354,9 +1390,12 @@ template <bool B_KC, int EPI>
 hipError_t run_rows(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
   if (s.rows == 0 || p.N == 0) return hipSuccess;
+  p.piece = buffer_piece(p.ldb);
+  const bool pieces = !B_KC && p.K > p.piece;
   p.tiles = DUAL ? (g_tiles.load(std::memory_order_relaxed) == FLOWMOE_TILES_AUTO ? FLOWMOE_TILES_AUTO
                                                                                   : FLOWMOE_TILES_WIDE)
                  : g_tiles.load(std::memory_order_relaxed);
+  if (pieces) p.tiles = FLOWMOE_TILES_WIDE;
   // the grid covers the wide tiles, or the narrow ones if asked for; the smaller
   // shapes the kernel chooses have at most one round of tiles
   const int ncols = DUAL || p.tiles == FLOWMOE_TILES_NARROW ? 128 : 256;
@@ -1377,6 +1416,11 @@ hipError_t run_rows(int kind, const Shape& s, GemmParams p, hipStream_t st) {
              (order == FLOWMOE_TILE_ORDER_AUTO && wbytes > 256.0 * 1024 * 1024 &&
               s.rows <= 2048L * s.E);
   return traced(kind, st, [&] {
+    if constexpr (!B_KC)
+      if (pieces) {
+        hipLaunchKernelGGL(gemm_bf16_rows_pieces_kernel<EPI>, dim3((unsigned)blocks), dim3(512), 0, st, p);
+        return;
+      }
     hipLaunchKernelGGL((gemm_bf16_rows_kernel<B_KC, EPI>), dim3((unsigned)blocks), dim3(512), 0, st, p);
   });
 }

@@ -45,3 +45,32 @@ def test_weight_gradients_beyond_descriptor_range(R):
     # the sums
     assert _rel(layer.dw1[0], dw1) < 1e-2
     assert _rel(layer.dw2[0], dw2) < 1e-2
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_expert_weights_beyond_descriptor_range(act):
+    """Experts' weights of 2 GiB and more each: x W1 (W3) of 40000 x 27136 with rows of
+    every tile class, and a W2 of 27136 x 40000."""
+    need_gpu()
+    d = dev()
+    M, H, cnt = 40000, 27136, [3, 0, 300]
+    E, T = len(cnt), sum(cnt)
+    HW = 2 * H if act == "swiglu" else H
+    g = torch.Generator(device=d).manual_seed(5)
+    n = lambda *sh, std=1.0: torch.randn(*sh, generator=g, device=d, dtype=BF) * std
+    w1, w2 = n(E, M, H, std=0.005), n(E, H, M, std=0.005)
+    w3 = n(E, M, H, std=0.005) if act == "swiglu" else None
+    x = n(T, M)
+    counts = torch.tensor(cnt, dtype=torch.int32, device=d)
+    offsets = torch.tensor([0, 3, 3, 303], dtype=torch.int32, device=d)
+    s = L.make_shape(T, M, H, E, 1, 300, L.BF16, L.SWIGLU if act == "swiglu" else L.GELU, L.PACKED)
+    h, a, y = (torch.full((T, c), 5.0, dtype=BF, device=d) for c in (HW, H, M))
+    L.flowmoe_expert_ffn(s, x, counts, offsets, w1, w3, w2, h, a, y)
+    torch.cuda.synchronize()
+    for e, r in ((0, slice(0, 3)), (2, slice(3, 303))):
+        for j, w in enumerate((w1, w3) if act == "swiglu" else (w1,)):
+            ref = sum(x[r, k:k + 8000].float() @ w[e, k:k + 8000].float() for k in range(0, M, 8000))
+            # one rounding to bf16; the weight rows past 2^31 bytes are 1.1 % of the products
+            assert _rel(h[r, j * H:(j + 1) * H], ref) < 4e-3
+        ref = sum(a[r, k:k + 8000].float() @ w2[e, k:k + 8000].float() for k in range(0, H, 8000))
+        assert _rel(y[r], ref) < 4e-3
