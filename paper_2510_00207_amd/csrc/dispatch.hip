@@ -18,6 +18,7 @@
 //   than the recount, at 96 tiles 3x).
 // gather / combine / scatter kernels move whole rows with 16-byte vectors,
 //   one wave per row or token, accumulating in float in a fixed order.
+#include <algorithm>
 #include <atomic>
 
 #include "common.hpp"
@@ -328,7 +329,8 @@ __host__ __device__ constexpr int row_steps() {
 // segment, the token in scalar registers and arrays of 6 for k = 5 and 6, T = 4096,
 // M = 2048, k = 6: combine, its backward, dispatch and gate backward 135 -> 127 us
 // (the scalar token and the arrays of 6 alone: 134.7), and 122 with the combine
-// backward split alike. GATE
+// backward split alike. A grid's x has four tokens a block by segs of their segments, all
+// of them unless the call has too many tokens for that; y has the rest. GATE
 // (dispatch backward of the layer): also adds the gate's share dl_t W_g^T,
 // with dl_t taken from the selection (gidx), its weights (gw) and their
 // gradients (gdw), and W_g^T given transposed in float (wgt, E x M).
@@ -339,10 +341,9 @@ __host__ __device__ constexpr int row_steps() {
 template <typename TE, bool GATE, int KM, bool ADD, bool NT>  // KM >= k: per-token array size
 __global__ __launch_bounds__(256) void combine_rows_kernel(
     const TE* __restrict__ src, const int32_t* __restrict__ slot, const float* __restrict__ w,
-    TE* __restrict__ y, int T, int M, int k, int kl, const int32_t* __restrict__ gidx,
+    TE* __restrict__ y, int T, int M, int k, int kl, int segs, const int32_t* __restrict__ gidx,
     const float* __restrict__ gw, const float* __restrict__ gdw, const TE* __restrict__ wgt) {
   constexpr int U = row_steps<TE, KM, NT>();
-  const int segs = (M + 512 * U - 1) / (512 * U);
   const int t = blockIdx.x / segs * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= T) return;
   const int lane = threadIdx.x & 63;
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(
     for (int j = 0; j < KM; ++j)
       if (j < k) gl[j] = gl[j] * (gdw[(long)t * k + j] - s);
   }
-  const int m0 = blockIdx.x % segs * (512 * U) + lane * 8;
+  const int m0 = (blockIdx.y * segs + blockIdx.x % segs) * (512 * U) + lane * 8;
   if (m0 < M) {
     decltype(raw8_load(src)) raw[U][KM];
     decltype(raw8_load(src)) yold[ADD ? U : 1];
@@ -513,18 +514,50 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
   }
 }
 
-// waves a token of combine_bwd_kernel: one a segment of its rows, at most 4
+// blocks a grid may have in x: HIP counts its threads in 32 bits
+constexpr long kMaxBlocks = (1L << 32) / 256 - 1;
+
+// waves a token of combine_bwd_kernel: one a segment of its rows, at most 4, and
+// fewer where the token blocks (and `others`) would be more than a launch may have
 template <typename TE, int KM>
-int bwd_waves(const Shape& s) {
+int bwd_waves(const Shape& s, long others) {
   constexpr int span = 512 * row_steps<TE, KM, false>();
-  return s.M <= span ? 1 : s.M <= 2 * span ? 2 : 4;
+  int tw = s.M <= span ? 1 : s.M <= 2 * span ? 2 : 4;
+  while (tw > 1 && ((long)s.T * tw + 3) / 4 + others > kMaxBlocks) tw >>= 1;
+  return tw;
 }
 
-// blocks of combine_rows_kernel: four tokens by one segment of their rows
-template <typename TE, int KM, bool NT>
-dim3 combine_grid(const Shape& s) {
+template <typename TE, bool GATE, int KM, bool ADD, bool NT>
+void launch_combine_rows(const Shape& s, const void* src, const int32_t* slot, const float* w,
+                         void* y, const int32_t* gidx, const float* gw, const float* gdw,
+                         const void* wgt, hipStream_t st) {
+  const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
   constexpr int span = 512 * row_steps<TE, KM, NT>();
-  return dim3((unsigned)((s.T + 3) / 4) * (unsigned)((s.M + span - 1) / span));
+  const long blocks = ((long)s.T + 3) / 4, all = (s.M + span - 1) / span;
+  const int segs = (int)std::max<long>(1, std::min(all, kMaxBlocks / blocks));
+  const dim3 grid((unsigned)(blocks * segs), (unsigned)((all + segs - 1) / segs));
+  hipLaunchKernelGGL((combine_rows_kernel<TE, GATE, KM, ADD, NT>), grid, dim3(256), 0, st,
+                     (const TE*)src, slot, w, (TE*)y, s.T, s.M, s.k, kl, segs, gidx, gw, gdw,
+                     (const TE*)wgt);
+}
+
+template <bool GATE, bool ADD>
+hipError_t run_combine(const Shape& s, const void* src, const int32_t* slot, const float* w, void* y,
+                       const int32_t* gidx, const float* gw, const float* gdw, const void* wgt,
+                       hipStream_t st) {
+  if (s.T == 0) return hipSuccess;
+  return traced(FLOWMOE_K_COMBINE, st, [&] {
+    with_kmax(s.k, [&](auto kc) {
+      constexpr int KMV = decltype(kc)::value;
+      if (s.dtype == FLOWMOE_BF16)
+        with_nt(s, s.rows, [&](auto ntc) {
+          launch_combine_rows<bf16_t, GATE, KMV, ADD, decltype(ntc)::value>(s, src, slot, w, y, gidx,
+                                                                            gw, gdw, wgt, st);
+        });
+      else
+        launch_combine_rows<float, GATE, KMV, ADD, false>(s, src, slot, w, y, gidx, gw, gdw, wgt, st);
+    });
+  });
 }
 
 }  // namespace
@@ -584,23 +617,7 @@ hipError_t launch_dispatch(const Shape& s, const int32_t* idx, const void* x, in
 
 hipError_t launch_combine(const Shape& s, const void* y_disp, const int32_t* slot, const float* w,
                           void* y, hipStream_t st) {
-  if (s.T == 0) return hipSuccess;
-  const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  return traced(FLOWMOE_K_COMBINE, st, [&] {
-    with_kmax(s.k, [&](auto kc) {
-      constexpr int KMV = decltype(kc)::value;
-      if (s.dtype == FLOWMOE_BF16)
-        with_nt(s, s.rows, [&](auto ntc) {
-          hipLaunchKernelGGL((combine_rows_kernel<bf16_t, false, KMV, false, decltype(ntc)::value>),
-                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
-                             (const bf16_t*)y_disp, slot, w, (bf16_t*)y, s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
-        });
-      else
-        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, false, false>),
-                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)y_disp, slot, w, (float*)y, s.T, s.M,
-                           s.k, kl, nullptr, nullptr, nullptr, nullptr);
-    });
-  });
+  return run_combine<false, false>(s, y_disp, slot, w, y, nullptr, nullptr, nullptr, nullptr, st);
 }
 
 hipError_t launch_dispatch_bwd(const Shape& s, const void* dx_disp, const int32_t* slot, void* dx,
@@ -610,47 +627,14 @@ hipError_t launch_dispatch_bwd(const Shape& s, const void* dx_disp, const int32_
 
 hipError_t launch_dispatch_bwd_add(const Shape& s, const void* dx_disp, const int32_t* slot,
                                    void* dx, hipStream_t st) {
-  if (s.T == 0) return hipSuccess;
-  const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  return traced(FLOWMOE_K_COMBINE, st, [&] {
-    with_kmax(s.k, [&](auto kc) {
-      constexpr int KMV = decltype(kc)::value;
-      if (s.dtype == FLOWMOE_BF16)
-        with_nt(s, s.rows, [&](auto ntc) {
-          hipLaunchKernelGGL((combine_rows_kernel<bf16_t, false, KMV, true, decltype(ntc)::value>),
-                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
-                             (const bf16_t*)dx_disp, slot, nullptr,
-                             (bf16_t*)dx, s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
-        });
-      else
-        hipLaunchKernelGGL((combine_rows_kernel<float, false, KMV, true, false>),
-                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
-                           s.T, s.M, s.k, kl, nullptr, nullptr, nullptr, nullptr);
-    });
-  });
+  return run_combine<false, true>(s, dx_disp, slot, nullptr, dx, nullptr, nullptr, nullptr, nullptr,
+                                  st);
 }
 
 hipError_t launch_dispatch_bwd_gate(const Shape& s, const void* dx_disp, const int32_t* slot,
                                     const int32_t* idx, const float* w, const float* dw,
                                     const void* wgt, void* dx, hipStream_t st) {
-  if (s.T == 0) return hipSuccess;
-  const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
-  return traced(FLOWMOE_K_COMBINE, st, [&] {
-    with_kmax(s.k, [&](auto kc) {
-      constexpr int KMV = decltype(kc)::value;
-      if (s.dtype == FLOWMOE_BF16)
-        with_nt(s, s.rows, [&](auto ntc) {
-          hipLaunchKernelGGL((combine_rows_kernel<bf16_t, true, KMV, false, decltype(ntc)::value>),
-                             (combine_grid<bf16_t, KMV, decltype(ntc)::value>(s)), dim3(256), 0, st,
-                             (const bf16_t*)dx_disp, slot, nullptr,
-                             (bf16_t*)dx, s.T, s.M, s.k, kl, idx, w, dw, (const bf16_t*)wgt);
-        });
-      else
-        hipLaunchKernelGGL((combine_rows_kernel<float, true, KMV, false, false>),
-                           (combine_grid<float, KMV, false>(s)), dim3(256), 0, st, (const float*)dx_disp, slot, nullptr, (float*)dx,
-                           s.T, s.M, s.k, kl, idx, w, dw, (const float*)wgt);
-    });
-  });
+  return run_combine<true, false>(s, dx_disp, slot, nullptr, dx, idx, w, dw, wgt, st);
 }
 
 hipError_t launch_combine_bwd(const Shape& s, const void* dy, const void* y_disp,
@@ -665,7 +649,7 @@ hipError_t launch_combine_bwd(const Shape& s, const void* dy, const void* y_disp
       constexpr int KMV = decltype(kc)::value;
       if (s.dtype == FLOWMOE_BF16)
         with_nt(s, 2 * s.rows, [&](auto ntc) {
-          const int tw = bwd_waves<bf16_t, KMV>(s);
+          const int tw = bwd_waves<bf16_t, KMV>(s, fill_blocks);
           const long token_blocks = ((long)s.T * tw + 3) / 4;
           hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, KMV, decltype(ntc)::value>),
                              dim3((unsigned)(token_blocks + fill_blocks)), dim3(256), 0, st,
@@ -673,7 +657,7 @@ hipError_t launch_combine_bwd(const Shape& s, const void* dy, const void* y_disp
                              (bf16_t*)dy_disp, dw, s.T, s.M, s.k, kl, s.E, s.C, (int)token_blocks, tw);
         });
       else {
-        const int tw = bwd_waves<float, KMV>(s);
+        const int tw = bwd_waves<float, KMV>(s, fill_blocks);
         const long token_blocks = ((long)s.T * tw + 3) / 4;
         hipLaunchKernelGGL((combine_bwd_kernel<float, KMV, false>),
                            dim3((unsigned)(token_blocks + fill_blocks)), dim3(256), 0, st,

@@ -1,5 +1,6 @@
 """Calls at the limits of the hardware's own sizes: reductions of more bytes than
-a buffer descriptor's range covers (2^31 - 1)."""
+a buffer descriptor's range covers (2^31 - 1), and launches of more threads than
+HIP counts (2^32 - 1), were every token to take all the waves it usually does."""
 import pytest
 import torch
 
@@ -74,3 +75,41 @@ def test_expert_weights_beyond_descriptor_range(act):
             assert _rel(h[r, j * H:(j + 1) * H], ref) < 4e-3
         ref = sum(a[r, k:k + 8000].float() @ w2[e, k:k + 8000].float() for k in range(0, H, 8000))
         assert _rel(y[r], ref) < 4e-3
+
+
+def test_combine_of_many_tokens():
+    """2^25 fp32 tokens of two segments each: 2^32 threads with a wave a segment. Few of
+    the tokens have rows (in each, and in the last block); the others' are zeros."""
+    need_gpu()
+    d = dev()
+    T, M, n = 1 << 25, 520, 1000
+    s = L.make_shape(T, M, 8, 2, 1, n // 2, L.F32, L.GELU, L.PACKED)
+    rows = L.flowmoe_rows_capacity(s)
+    assert rows == n
+    g = torch.Generator(device=d).manual_seed(9)
+    tok = torch.randperm(T - 1, generator=g, device=d)[:n]
+    tok[0] = T - 1
+    slot = torch.full((T, 1), -1, dtype=torch.int32, device=d)
+    slot[tok, 0] = torch.arange(n, dtype=torch.int32, device=d)
+    w = torch.rand(T, 1, generator=g, device=d)
+    src = torch.randn(n, M, generator=g, device=d)
+    counts = torch.tensor([n // 2, n // 2], dtype=torch.int32, device=d)
+    offsets = torch.tensor([0, n // 2, n], dtype=torch.int32, device=d)
+    y = torch.empty(T, M, device=d)
+    for weight, call in ((w[tok], lambda: L.flowmoe_combine(s, src, slot, w, y)),
+                         (1.0, lambda: L.flowmoe_dispatch_bwd(s, src, slot, y))):
+        y.fill_(7.0)
+        call()
+        assert torch.equal(y[tok], weight * src)
+        y[tok] = 0
+        assert not any(c.any() for c in y.chunk(64))
+    y.fill_(0.5)
+    y[tok] = torch.randn(n, M, generator=g, device=d)
+    dys, dw = torch.full((n, M), 7.0, device=d), torch.full((T, 1), 7.0, device=d)
+    L.flowmoe_combine_bwd(s, y, src, slot, w, counts, offsets, dys, dw)
+    assert torch.equal(dys, w[tok] * y[tok])
+    ref = (y[tok].double() * src.double()).sum(1)
+    # 520 products summed in fp32, off by at most 2^-24 of their size each and at each sum
+    assert (dw[tok, 0].double() - ref).abs().max() < 520 * 2.0 ** -22
+    dw[tok] = 0
+    assert not dw.any()
