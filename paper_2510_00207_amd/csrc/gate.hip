@@ -274,7 +274,8 @@ __global__ __launch_bounds__(EP >= 4 ? 256 : 64 * EP) void gate_topk_kernel(
   __shared__ __attribute__((aligned(16))) float xs[TPB * XP];
   __shared__ __attribute__((aligned(16))) float ws[MC * EP];
   const int tid = threadIdx.x, e = tid % EP, slot = tid / EP * TPT;
-  const int t0 = blockIdx.x * TPB;
+  const int t0 = (blockIdx.y * gridDim.x + blockIdx.x) * TPB;
+  if (t0 >= T) return;
   const bool evalid = e < E;
   const int es = evalid ? e : 0;
   float4 xr[XL], wr[WL];
@@ -1266,7 +1267,10 @@ hipError_t launch_gate_topk(const Shape& s, const void* x, const void* w_gate, c
 #define FLOWMOE_GATE_F32(EPV)                                                                    \
   case EPV: {                                                                                    \
     constexpr int NT = EPV >= 4 ? 256 : 64 * EPV, TPB = NT / EPV * (EPV >= 16 ? 2 : 1);          \
-    hipLaunchKernelGGL(gate_topk_kernel<EPV>, dim3((s.T + TPB - 1) / TPB), dim3(NT), 0, st,      \
+    /* (HIP counts a grid's threads in x in 32 bits) */                                          \
+    constexpr unsigned most = (1L << 32) / NT - 1;                                               \
+    const unsigned n = (s.T + TPB - 1) / TPB, gx = n < most ? n : most;                          \
+    hipLaunchKernelGGL(gate_topk_kernel<EPV>, dim3(gx, (n + gx - 1) / gx), dim3(NT), 0, st,      \
                        (const float*)x, (const float*)w_gate, bias, logits, idx, w, s.T, s.M,    \
                        s.E, s.k, full);                                                          \
   } break

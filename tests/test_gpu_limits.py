@@ -113,3 +113,26 @@ def test_combine_of_many_tokens():
     assert (dw[tok, 0].double() - ref).abs().max() < 520 * 2.0 ** -22
     dw[tok] = 0
     assert not dw.any()
+
+
+def test_f32_gate_of_many_tokens():
+    """2^27 + 5 tokens at E = 64, eight a block of 256 threads: more than 2^32 threads."""
+    need_gpu()
+    d = dev()
+    T, M, E = (1 << 27) + 5, 8, 64
+    g = torch.Generator(device=d).manual_seed(9)
+    x = torch.randn(T, M, generator=g, device=d)
+    wg = torch.randn(M, E, generator=g, device=d)
+    logits = torch.full((T, E), 7.0, device=d)
+    idx = torch.full((T, 1), -5, dtype=torch.int32, device=d)
+    w = torch.full((T, 1), 7.0, device=d)
+    s = L.make_shape(T, M, 8, E, 1, 0, L.F32, L.GELU, L.PACKED)
+    L.flowmoe_gate_topk(s, x, wg, None, logits, idx, w)
+    torch.cuda.synchronize()
+    assert bool((w == 1).all())  # (the softmax over one)
+    for a in range(0, T, 1 << 24):
+        lg, ix = logits[a:a + (1 << 24)], idx[a:a + (1 << 24)].long()
+        assert torch.equal(lg.gather(1, ix)[:, 0], lg.max(1).values)
+    for r in (slice(0, 4096), slice((1 << 27) - 4096, None)):
+        ref = x[r].double() @ wg.double()
+        assert (logits[r].double() - ref).abs().max() < 1e-5 * ref.abs().max()
