@@ -424,6 +424,11 @@ inline hipError_t traced(int kind, hipStream_t st, F&& f) {
   return trace_mark(kind, true, st);
 }
 
+// blocks of 256 threads a grid may have in x. HIP counts its threads in 32 bits and
+// launches a grid that exceeds them with the count cut off: launchers whose grid
+// grows with the tokens or rows of a call check it before they enqueue anything.
+constexpr long kMaxBlocks = (1L << 32) / 256 - 1;
+
 inline size_t esize(int dtype) { return dtype == FLOWMOE_BF16 ? 2 : 4; }
 inline size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 

@@ -514,8 +514,11 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
   }
 }
 
-// blocks a grid may have in x: HIP counts its threads in 32 bits
-constexpr long kMaxBlocks = (1L << 32) / 256 - 1;
+// blocks that walk the tokens four a block, and the padded layout's rows beside them
+bool too_many_blocks(const Shape& s) {
+  const long fill = s.layout == FLOWMOE_PADDED ? ((long)s.E * s.C + 3) / 4 : 0;
+  return ((long)s.T + 3) / 4 + fill > kMaxBlocks;
+}
 
 // waves a token of combine_bwd_kernel: one a segment of its rows, at most 4, and
 // fewer where the token blocks (and `others`) would be more than a launch may have
@@ -546,6 +549,7 @@ hipError_t run_combine(const Shape& s, const void* src, const int32_t* slot, con
                        const int32_t* gidx, const float* gw, const float* gdw, const void* wgt,
                        hipStream_t st) {
   if (s.T == 0) return hipSuccess;
+  if (((long)s.T + 3) / 4 > kMaxBlocks) return hipErrorInvalidConfiguration;
   return traced(FLOWMOE_K_COMBINE, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;
@@ -572,6 +576,9 @@ size_t dispatch_ws_bytes(const Shape& s) {
 hipError_t launch_dispatch(const Shape& s, const int32_t* idx, const void* x, int32_t* counts,
                            int32_t* offsets, int32_t* slot, int32_t* row_src, int32_t* load,
                            void* x_disp, void* ws, hipStream_t st) {
+  // (the row copy walks the rows with one expert a token, else the tokens)
+  if (s.rows > 0 && (s.k == 1 ? (s.rows + 3) / 4 > kMaxBlocks : too_many_blocks(s)))
+    return hipErrorInvalidConfiguration;
   const int padded = s.layout == FLOWMOE_PADDED;
   const long n = (long)s.T * s.k;
   const long tiles = (n + kScanThreads - 1) / kScanThreads;
@@ -644,6 +651,7 @@ hipError_t launch_combine_bwd(const Shape& s, const void* dy, const void* y_disp
   const int kl = s.rows > 0 ? s.k : 0;  // no rows: no source loads
   const long fill_blocks = (s.layout == FLOWMOE_PADDED) ? ((long)s.E * s.C + 3) / 4 : 0;
   if (s.T == 0 && fill_blocks == 0) return hipSuccess;
+  if (too_many_blocks(s)) return hipErrorInvalidConfiguration;
   return traced(FLOWMOE_K_COMBINE_BWD, st, [&] {
     with_kmax(s.k, [&](auto kc) {
       constexpr int KMV = decltype(kc)::value;

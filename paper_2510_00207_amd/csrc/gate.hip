@@ -1292,6 +1292,7 @@ hipError_t launch_route(const Shape& s, const float* logits, int32_t* idx, float
   const int EP = pow2_at_least(s.E);
   const int per_block = 4 * (64 / EP);
   const int blocks = (s.T + per_block - 1) / per_block;
+  if (blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
   return traced(FLOWMOE_K_ROUTE, st, [&] {
     hipLaunchKernelGGL(route_kernel, dim3(blocks), dim3(kGateThreads), 0, st, logits, idx, w, s.T,
                        s.E, s.k, EP, (int)(s.gate == FLOWMOE_GATE_FULL));
@@ -1493,6 +1494,7 @@ hipError_t launch_gate_bwd(const Shape& s, const void* x, const void* w_gate, co
   // the sparse dx term reads W_g^T, which the dW_g reduce launch writes (with
   // d_logits = 0 the term is zero: dx is left as it is)
   if (gate_grad_zero(s)) dx = nullptr;
+  if (dx != nullptr && !full && ((long)s.T + 3) / 4 > kMaxBlocks) return hipErrorInvalidConfiguration;
   const bool wt = dx != nullptr && s.T > 0 && !full;
   hipError_t e = launch_gate_dw(s, x, logits, idx, w, dw, d_logits, dw_gate, dbias, accumulate, ws,
                                 st, wt ? w_gate : nullptr);

@@ -311,3 +311,26 @@ def test_layer_mha_validation(flowmoe_lib):
     with pytest.raises(ValueError):  # the binding checks the trace length first
         L.flowmoe_layer_bwd(s, 2, b, s_compute=0, s_comm=0, trace=[0] * (8 * 2 + 2))
     assert L.bwd_trace_len(2, True) == 24 and L.bwd_trace_len(2, False) == 18
+
+
+@pytest.mark.parametrize("call", ["route", "dispatch", "combine", "combine_bwd", "dispatch_bwd",
+                                  "gate_bwd"])
+def test_more_threads_than_a_grid_holds_refused(flowmoe_lib, call):
+    """Tokens (and padded rows) four to a block of 256 threads: from 2^26 of them on a
+    grid has 2^32 threads, which HIP would cut off. Refused with nothing enqueued."""
+    T, E, k = 1 << 26, 64, 2
+    s = L.make_shape(T, 8, 8, E, k, 8, L.BF16)
+    run = {
+        "route": lambda: L.flowmoe_route(s, FAKE, FAKE, FAKE, stream=0),
+        "dispatch": lambda: L.flowmoe_dispatch(s, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, None, FAKE,
+                                               stream=0),
+        "combine": lambda: L.flowmoe_combine(s, FAKE, FAKE, FAKE, FAKE, stream=0),
+        "combine_bwd": lambda: L.flowmoe_combine_bwd(s, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE,
+                                                     stream=0),
+        "dispatch_bwd": lambda: L.flowmoe_dispatch_bwd(s, FAKE, FAKE, FAKE, stream=0),
+        "gate_bwd": lambda: L.flowmoe_gate_topk_bwd(s, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE,
+                                                    None, FAKE, 0, FAKE, 1 << 40, stream=0),
+    }[call]
+    with pytest.raises(L.FlowMoEError) as ei:
+        run()
+    assert ei.value.status == L.ERR_HIP and "invalid configuration" in str(ei.value)
