@@ -320,7 +320,7 @@ int32_t flowmoe_trace_stop(void);
  * backward). AUTO, the default: over the experts' rows the kernel takes the
  * smallest of 128 x 128, 256 x 128 and 256 x 256 tiles that run as one round of
  * the compute units, else 256 x 256, by the counts it finds on the device; the
- * weight gradients take 256 x 128 tiles up to 160 wide ones. WIDE and NARROW
+ * weight gradients take 256 x 128 tiles where those do. WIDE and NARROW
  * force 256 x 256 or 256 x 128 (the SwiGLU forward has no 256 x 128 tile). Every
  * shape accumulates every output in the same k order: results are
  * bit-identical. */

@@ -1436,14 +1436,19 @@ hipError_t launch_ksum(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   });
 }
 
-// Weight gradients: 256 x 256 tiles, or 256 x 128 where at most 160 wide ones
-// would leave CUs idle
+// Weight gradients: 256 x 128 tiles where they run as one round of the CUs, else 256
+// x 256 (a round of wide tiles is shorter than two of narrow ones). Measured, wide
+// and narrow, experts of 1024 rows: 256 narrow tiles (8 experts of 1024 x 1024) 32.0
+// and 28.7 us, 240 (20 of 1024 x 384) 36.4 and 31.8; 288 (4 of 1536 x 1536) 33 and 42,
+// 320 (2 of 2560 x 2048) 32 and 42, 336 (3 of 1792 x 2048) 33 and 42. Under the line
+// narrow tiles lose where an expert has few of them, each read again by the next (32
+// of 512 x 512: 33 and 39 at 1024 rows, equal at 256, 16.5 and 15.0 at 100).
 template <int EPI>
 hipError_t run_ksum(int kind, const Shape& s, const GemmParams& p, hipStream_t st) {
   if (p.nseg < 1) return hipErrorInvalidValue;  // (a launcher bug)
-  const long wide = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + 255) / 256);
+  const long narrow = (long)s.E * ((p.Mdim + 255) / 256) * ((p.N + 127) / 128);
   const int tiles = g_tiles.load(std::memory_order_relaxed);
-  if (tiles == FLOWMOE_TILES_NARROW || (tiles == FLOWMOE_TILES_AUTO && wide <= 160))
+  if (tiles == FLOWMOE_TILES_NARROW || (tiles == FLOWMOE_TILES_AUTO && narrow <= kCUs))
     return launch_ksum<EPI, true>(kind, s, p, st);
   return launch_ksum<EPI, false>(kind, s, p, st);
 }

@@ -847,8 +847,9 @@ def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
     """The tile shape the row kernel chooses from the counts (padded: from the
     capacity): every row class of the 128 x 128 tiles, and with 16 column tiles
     the last launch of one round and the first of more for the 128- and the
-    256-row tiles. Forward and input gradients bit-identical to the forced
-    256 x 256 tiles, h against 64 bits."""
+    256-row tiles. The weight gradients have 192 and 256 narrow tiles (one round),
+    384 and 512 (SwiGLU's dW1 | dW3). Forward, input and weight gradients
+    bit-identical to the forced 256 x 256 tiles, h against 64 bits."""
     need_gpu()
     d, bf = dev(), torch.bfloat16
     E, M, H, T, C = len(cnt), 72, 2048, sum(cnt), max(cnt)
@@ -869,10 +870,12 @@ def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
         gemm_tiles(tiles)
         o = {n: torch.full((rows, c), 5.0, dtype=bf, device=d)
              for n, c in (("h", HW), ("a", H), ("y", M), ("dx", M))}
-        dw1, dw2, dw3 = (torch.zeros(sh, device=d) for sh in ((E, M, H), (E, H, M), (E, M, H)))
+        o.update({n: torch.full(sh, 9.0, device=d)
+                  for n, sh in (("dw1", (E, M, H)), ("dw2", (E, H, M)), ("dw3", (E, M, H)))
+                  if n != "dw3" or act == "swiglu"})
         L.flowmoe_expert_ffn(s, x, counts, offsets, w1, w3, w2, o["h"], o["a"], o["y"])
-        L.flowmoe_expert_ffn_bwd(s, dy, x, o["h"], o["a"], counts, offsets, w1, w3, w2, o["dx"], dw1,
-                                 dw3 if act == "swiglu" else None, dw2, 0, ws, nws)
+        L.flowmoe_expert_ffn_bwd(s, dy, x, o["h"], o["a"], counts, offsets, w1, w3, w2, o["dx"],
+                                 o["dw1"], o.get("dw3"), o["dw2"], 0, ws, nws)
         got[tiles] = o
     torch.cuda.synchronize()
     for n in got["auto"]:
