@@ -1518,10 +1518,11 @@ hipError_t launch_gate_dw_gemm(const void* x, int T, int M, const void* d, int N
   p.ksplit = 1 << 30;
   p.nseg = 1;
   p.rows_cap = T;
-  // 256 x 256 tiles whatever the grid: these launches are bound by reading
-  // x once, and the 8-wave tile's deeper ring (4 stages against 3) keeps
-  // more of it in flight (the narrow tile took 1.2-1.7x as long)
-  return launch_ksum<EPI_GATE_DW, false>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
+  // 256 x 128 tiles whatever the grid: N is at most 128 (the logit gradients' high
+  // and low halves), so half of a wide tile would be outside the output (T = 16384,
+  // M = 4096: E = 8 38.8 -> 32.8 us, E = 64 50.7 -> 45.6; T = 4096, M = 1024, E = 8 13.8 ->
+  // 10.6)
+  return launch_ksum<EPI_GATE_DW, true>(FLOWMOE_K_GATE_BWD_DW, s2, p, st);
 }
 
 hipError_t launch_gate_dx_gemm(const void* dlhl, int T, int K, const void* wstack, int M,
