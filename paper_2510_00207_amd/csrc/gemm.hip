@@ -8,8 +8,8 @@
 //   KSUM  C_e[Mdim x N]  = sum over rows r of e: A[r][.]^T B[r][.]  (wgrad):
 //         the reduction length K = counts[e] is ragged.
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16 over 256 x 256 or, where those are few, 256 x
-// 128 tiles, the operands streamed global -> LDS.
+// bf16 path: v_mfma_f32_32x32x16_bf16 over 256 x 256 tiles or, where those are few, 256 x
+// 128 or (row mode) 128 x 128 ones, the operands streamed global -> LDS.
 // fp32 path: v_mfma_f32_32x32x2_f32 over 128-, 64- or 32-row x 128-column tiles,
 // the same modes and epilogues.
 #include <math.h>

@@ -53,10 +53,13 @@ CORE_CASES = [
     (1, 64, 4, 64, True),
     (1, 1000, 1, 128, True),   # 8 query blocks, 16 key tiles, the last ragged
     (2, 97, 3, 64, False),
-    # grids of at least 512 blocks of 256 queries: the 8-wave forward blocks,
-    # with ragged tails
+    # grids of several rounds of blocks, with ragged tails (causal grids past 512
+    # blocks run their tiles longest first, without pairing)
     (4, 700, 48, 64, True),
     (2, 520, 96, 128, False),
+    # around the loops' look-ahead: one, two and three of the 64-key (forward) and
+    # 32-row (backward) tiles, a row short, whole and a row over
+    *[(2, n, 1, d, c) for n in (31, 32, 33, 63, 65, 129) for d in (64, 128) for c in (False, True)],
 ]
 
 

@@ -317,14 +317,14 @@ def tile_order():
 
 @pytest.mark.parametrize("biased", [False, True], ids=["nobias", "bias"])
 @pytest.mark.parametrize("MHT", [(200, 264, "auto"), (224, 288, "wide"), (224, 288, "narrow")],
-                         ids=["staged", "streaming-wide", "streaming-narrow"])
+                         ids=["auto", "wide", "narrow"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 @pytest.mark.parametrize("layout", ["packed", "padded"])
 def test_expert_ffn_fwd_bwd(dtype, act, layout, MHT, biased, gemm_tiles):
-    """(200, 264): reductions not multiples of 32 (register-staged bf16 GEMM);
-    (224, 288): multiples of 32 (LDS-streaming bf16 GEMM, 256 x 256 and
-    256 x 128 tiles); all ragged. The counts give row tiles of every class:
+    """(200, 264): reductions that end inside a 16-byte-chunk group of a 64-deep
+    k-tile, the tile shape chosen; (224, 288): 32 into one, 256 x 256 and 256 x 128
+    tiles forced; all ragged. The counts give row tiles of every class:
     empty, a few rows, under and over half a tile, full. Biased experts: b1
     (b3) and b2 on the data rows only, and their gradients as per-expert
     column sums."""
@@ -419,15 +419,15 @@ def test_expert_ffn_fwd_bwd(dtype, act, layout, MHT, biased, gemm_tiles):
         assert torch.equal(db["db2"], 2 * db2b)
 
 
-@pytest.mark.parametrize("M", [32, 64, 96, 160, 192])
+@pytest.mark.parametrize("M", [32, 64, 96, 160, 192, 256, 320, 384])
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 def test_expert_ffn_ring_depths(act, M, gemm_tiles):
-    """Short reductions on the LDS-streaming GEMM (wide 256 x 256 tiles, a
-    4-stage ring of 32-deep k-tiles): K = M of the first GEMM and of the
-    input-gradient GEMM gives 1, 2, 3, 5 and 6 k-tiles, K = H = 96 and
-    2H = 192 give 3 and 6, and the weight gradients reduce over expert row
-    counts of 1 to 6 k-tiles (ragged ones among them): every prologue-only,
-    partly steady and steady ring walk, each against the oracle."""
+    """Short reductions on wide 256 x 256 tiles (64-deep k-tiles, two in LDS; three
+    for tiles of few rows): K = M of the first GEMM and of the input-gradient GEMM
+    gives 1 to 6 k-tiles, K = H = 96 and 2H = 192 give 2 and 2 + 2 (in two parts),
+    and the weight gradients reduce over expert row counts of 1, 2 (loaded at
+    once) and 3 k-tiles, ragged ones among them: loops that end in their
+    prologue's tiles and beyond, each against the oracle."""
     need_gpu()
     gemm_tiles("wide")
     rng = np.random.default_rng(17)

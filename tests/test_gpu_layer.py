@@ -16,9 +16,8 @@ from paper_2510_00207_amd import _lib as L
 pytestmark = pytest.mark.gpu
 
 # reduced versions of the five workloads (same E, k, f, act, dtype, R), sized
-# for the oracle; H and M leave ragged GEMM tiles. Widths that are multiples
-# of 32 run the LDS-streaming GEMM everywhere; H = 456 (large_s) sends the
-# row-mode GEMMs with K = H to the register-staged kernel.
+# for the oracle; H and M leave ragged GEMM tiles, and H = 456 (large_s) a last
+# k-tile of 8 in the row-mode GEMMs with K = H.
 CASES = {
     "tiny": get_config("tiny"),
     "balanced_s": get_config("balanced", T=512, M=256, H=416),
