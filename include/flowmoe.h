@@ -27,7 +27,11 @@
  *  - Results are deterministic: no floating-point atomics anywhere.
  *  - Shapes: T tokens per call (one chunk), M model width, H expert hidden
  *    width, E experts (1..64), k experts per token (1..min(E, 8)), C the
- *    per-expert capacity (>= 0). M and H must be multiples of 8.
+ *    per-expert capacity (>= 0). M and H must be multiples of 8. Dispatch,
+ *    combine and their backwards walk the tokens (and padded rows) four to a
+ *    block of 256 threads: from 2^26 of them on they return FLOWMOE_ERR_HIP.
+ *    bf16 experts: M and H (SwiGLU: 2 H) below 2^22, the rows of a tile that a
+ *    32-bit byte offset reaches.
  *
  * Row buffers (x_disp, y_disp, dy_disp, dx_disp, h_save, a_save) hold
  * flowmoe_rows_capacity(shape) rows: min(T*k, E*C) for the packed layout,
