@@ -218,7 +218,8 @@ __device__ __forceinline__ void decode(const AttnArgs& a, bool rev, int& tile, i
   sq = rest / a.heads;
 }
 
-// Forward: blocks of 4 waves of 32 queries, two to a CU.
+// Forward: blocks of 4 waves of 32 queries (8 in some launches of heads of 64), two to
+// four to a CU.
 //
 // The matrix pipes should bound it, but a tile's softmax takes about as many issue
 // cycles as its 32 products take matrix cycles, and products that wait for their
@@ -228,15 +229,24 @@ __device__ __forceinline__ void decode(const AttnArgs& a, bool rev, int& tile, i
 // S(t + 1), and every LDS read two groups of products before its use. K and V
 // tiles come by LDS-DMA into two slots each: step t reads K(t + 1) and V(t), and
 // refills K(t)'s and V(t - 1)'s slots. Measured, before -> now: 4 x 4096 tokens, 32
-// heads of 128, causal 668 -> 600 us; one sequence of 4096, 16 heads 112 -> 93; 4 x
+// heads of 128, causal 635 -> 590 us; one sequence of 4096, 16 heads 112 -> 93; 4 x
 // 2048, 32 heads, bidirectional 326 -> 297. Blocks of 8 waves (half the staging)
 // are 0-4% slower, and 12% on short causal sequences; four slots instead of two,
 // raised priority around the V products, and timing copies without the barrier
 // or the wait for the loads change 0-2%, without the exponentials 7%, without the
 // DMA 17% (less switching): two independent blocks a CU hide what there is.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
-  constexpr int KS = D / 16, DB = D / 32, NW = 4, QB = 32 * NW;
+//
+// Heads of 64 have half the products for the same softmax, and room for four waves
+// on a SIMD (128 registers) if a step does not run ahead: then the other waves
+// hide a wave's softmax, and K(t), V(t) are used in turn. The one-tile-ahead loop
+// with two waves a SIMD had made them up to 13 % slower than the loop before it,
+// where a launch is several rounds. us of the loop before, ahead, in turn: 32
+// sequences of 512, 16 heads, bidirectional 56, 62, 51 (8 waves); 4 x 4096, 24 heads,
+// causal 252, 266, 229; 8 x 512 20, 19, 18; 1 x 4096, 8 heads 64, 54, 55.
+template <int D, bool CAUSAL, int NW>
+__global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 4) void attn_fwd_kernel(AttnArgs a) {
+  constexpr bool AHEAD = D == 128;
+  constexpr int KS = D / 16, DB = D / 32, QB = 32 * NW;
   using Dma = TileDma<D, 64, NW>;
   constexpr int TB = Dma::TB;
   __shared__ __attribute__((aligned(1024))) char lds[4 * TB];  // K slots 0, 1, then V slots 0, 1
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
   const long kstep = 64 * ld;
   dma.load(Kg, kend, 0);
   dma.load(Vg, kend, 2 * TB);
-  dma.load(Kg + kstep, kend - 64, TB);  // (past the last tile: no traffic)
+  if constexpr (AHEAD) dma.load(Kg + kstep, kend - 64, TB);  // (past the last tile: no traffic)
 
   bf16x8 qf[KS];
 #pragma unroll
@@ -330,21 +340,79 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
     for (int u = 0; u < 2; ++u) s[u] = mfma(fr[i % 3][u], qf[i], i == 0 ? zero16() : s[u]);
   };
 
-  floatx16 s[2][2];  // [tile parity][32-key block]
-  wait_vm<0>();
-  lds_barrier();
-  read_group(lds, lds, 0);
-  read_group(lds, lds, 1);
+  // heads of 64: K(t) and V(t) in slots t % 2; the scores, the softmax and the value
+  // products one after the other
+  auto step_in_turn = [&](const int t, auto stc) {
+    constexpr int st = decltype(stc)::value;
+    opaque(rbase, tb0, tb1);
+    wait_vm<0>();  // K(t) and V(t): loaded a step ago
+    lds_barrier();  // and every wave's reads of the slots refilled now are done
+    const char* tk = lds + st * TB;
+    const char* tv = lds + (2 + st) * TB;
+    const bool live = t < nkw;
+    if (live) {
+      read_group(tk, tv, 0);
+      read_group(tk, tv, 1);
+    }
+    Kg += kstep;  // K(t + 1), V(t + 1)
+    Vg += kstep;
+    dma.load(Kg, kend - 64 * (t + 1), (st ^ 1) * TB);
+    dma.load(Vg, kend - 64 * (t + 1), (2 + (st ^ 1)) * TB);
+    if (!live) return;
+    floatx16 sc[2];
 #pragma unroll
-  for (int i = 0; i < KS; ++i) {
-    if (i + 2 < KS) read_group(lds, lds, i + 2);
+    for (int i = 0; i < KS; ++i) {
+      read_group(tk, tv, i + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mul_k(sc, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mask(sc, 64 * t);
+    move_ref(row_max(sc));
+    unsigned pw[16];
+    float rsum = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 32; q += 2) {
+      const float p0 = exp2_fast(fmaf(sc[q >> 4][q & 15], a.c2, -m));
+      const float p1 = exp2_fast(fmaf(sc[q >> 4][(q & 15) + 1], a.c2, -m));
+      rsum += p0;
+      rsum += p1;
+      pw[q >> 1] = pack_bf16x2(p0, p1);
+    }
     __builtin_amdgcn_sched_barrier(0);
-    mul_k(s[0], i);
-  }
-  mask(s[0], 0);
-  move_ref(row_max(s[0]));
+#pragma unroll
+    for (int j = 0; j < VG; ++j) {
+      read_group(tk, tv, KS + j + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      const int g = j / (DB / 2);
+      const bf16x8 pb = __builtin_bit_cast(bf16x8, u32x4{pw[4 * g], pw[4 * g + 1], pw[4 * g + 2], pw[4 * g + 3]});
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int db = 2 * (j % (DB / 2)) + u;
+        o[db] = mfma(fr[(KS + j) % 3][u], pb, o[db]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    l += pair_sum(rsum);
+  };
 
-  auto step = [&](const int t, auto stc) {
+  floatx16 s[2][2];  // [tile parity][32-key block]
+  if constexpr (AHEAD) {
+    wait_vm<0>();
+    lds_barrier();
+    read_group(lds, lds, 0);
+    read_group(lds, lds, 1);
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      if (i + 2 < KS) read_group(lds, lds, i + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mul_k(s[0], i);
+    }
+    mask(s[0], 0);
+    move_ref(row_max(s[0]));
+  }
+
+  auto step_ahead = [&](const int t, auto stc) {
     constexpr int st = decltype(stc)::value;
     opaque(rbase, tb0, tb1);
     wait_vm<0>();  // K(t + 1) and V(t): loaded a step ago
@@ -422,6 +490,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnArgs a) {
     }
     l += pair_sum(rsum);
     if (next) move_ref(mx);
+  };
+  auto step = [&](const int t, auto stc) {
+    if constexpr (AHEAD) step_ahead(t, stc);
+    else step_in_turn(t, stc);
   };
   for (int t = 0; t < nk; t += 2) {
     step(t, Stage<0>{});
@@ -795,8 +867,8 @@ AttnArgs attn_args(const AttnShape& m, int T, int M) {
   return a;
 }
 
-unsigned attn_blocks(const AttnArgs& a) {
-  return (unsigned)(((a.N + 127) / 128) * a.heads * a.nseq);
+unsigned attn_blocks(const AttnArgs& a, int rows = 128) {
+  return (unsigned)(((a.N + rows - 1) / rows) * a.heads * a.nseq);
 }
 
 // pair long and short causal tiles (decode) when the grid (two blocks per CU) is
@@ -804,6 +876,22 @@ unsigned attn_blocks(const AttnArgs& a) {
 // the longest-first order's
 int attn_pair(const AttnShape& m, const AttnArgs& a) {
   return m.causal && attn_blocks(a) <= 2u * 256u ? 1 : 0;
+}
+
+// Forward of heads of 64 in blocks of 8 waves, which read K and V half as often:
+// where they are two rounds of two to a CU at least, and leave no half of a block
+// without queries. 4 and 8 waves, us: 32 and 64 sequences of 512, 16 heads,
+// bidirectional 58 and 51, 110 and 95; 16 sequences (one round), causal 21.8 and 23.0;
+// 128 of 128 (half empty) 29 and 33; 4 of 700, 48 heads (576 blocks) 41 and 45.
+bool fwd_wide(const AttnArgs& a) {
+  return attn_blocks(a, 256) >= 4u * 256u && 2 * attn_blocks(a, 256) == attn_blocks(a);
+}
+
+template <int D, int NW>
+void launch_fwd(const AttnShape& m, const AttnArgs& a, hipStream_t st) {
+  const dim3 g(attn_blocks(a, 32 * NW)), b(64 * NW);
+  if (m.causal) hipLaunchKernelGGL((attn_fwd_kernel<D, true, NW>), g, b, 0, st, a);
+  else hipLaunchKernelGGL((attn_fwd_kernel<D, false, NW>), g, b, 0, st, a);
 }
 
 #define FLOWMOE_ATTN_LAUNCH(KERNEL, a, st)                                       \
@@ -828,7 +916,11 @@ hipError_t launch_attn_fwd(const AttnShape& m, int T, int M, const void* qkv, vo
   a.out = static_cast<bf16_t*>(o);
   a.lse = lse;
   a.pair = attn_pair(m, a);
-  return traced(FLOWMOE_K_ATTN_FWD, st, [&] { FLOWMOE_ATTN_LAUNCH(attn_fwd_kernel, a, st); });
+  return traced(FLOWMOE_K_ATTN_FWD, st, [&] {
+    if (m.D == 128) launch_fwd<128, 4>(m, a, st);
+    else if (fwd_wide(a)) launch_fwd<64, 8>(m, a, st);
+    else launch_fwd<64, 4>(m, a, st);
+  });
 }
 
 hipError_t launch_attn_bwd(const AttnShape& m, int T, int M, const void* qkv, const void* o,

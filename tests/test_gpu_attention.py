@@ -57,6 +57,10 @@ CORE_CASES = [
     # blocks run their tiles longest first, without pairing)
     (4, 700, 48, 64, True),
     (2, 520, 96, 128, False),
+    # at least 1024 blocks of 256 queries, the last half of each ragged: the forward's
+    # 8-wave blocks of heads of 64
+    (22, 230, 48, 64, True),
+    (22, 230, 48, 64, False),
     # around the loops' look-ahead: one, two and three of the 64-key (forward) and
     # 32-row (backward) tiles, a row short, whole and a row over
     *[(2, n, 1, d, c) for n in (31, 32, 33, 63, 65, 129) for d in (64, 128) for c in (False, True)],
