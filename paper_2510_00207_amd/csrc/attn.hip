@@ -45,6 +45,7 @@ struct AttnArgs {
   float* lse;         // heads x T: natural log-sum-exp of each row's scores
   float* delta;       // heads x T: rowsum(dO * O) over the head's columns
   int T, M, N, heads, nseq;
+  int shared;  // query tiles of a head side by side on one XCD (decode)
   int pair;  // causal grid of one round of resident blocks: pair long and short tiles (decode)
   float c2;  // log2(e) / sqrt(D): a score times c2 is its base-2 exponent
   float rs;  // 1 / sqrt(D)
@@ -207,9 +208,21 @@ __device__ __forceinline__ float pair_sum(float x) {
 // the grid lands on the CUs of the first half) the second half runs the
 // shortest tiles first, so that a CU's two blocks have complementary work
 // (ranks u and nt - 1 - u) instead of ranks u and u + nt / 2.
-__device__ __forceinline__ void decode(const AttnArgs& a, bool rev, int& tile, int& hd, int& sq,
-                                       int rows) {
+//
+// `shared` (query tiles; shared_order): the tiles of a head one after the other on
+// one XCD (blocks go to the 8 XCDs round-robin), so that its K and V are read
+// through that L2 once. In the order above they are per blocks apart, and a launch
+// whose K and V exceed the caches reads them from HBM for every tile.
+__device__ __forceinline__ void decode(const AttnArgs& a, bool rev, bool shared, int& tile, int& hd,
+                                       int& sq, int rows) {
   const int per = a.heads * a.nseq, nt = (a.N + rows - 1) / rows;
+  if (shared && per % 8 == 0) {
+    const int i = blockIdx.x >> 3, rest = i / nt * 8 + (blockIdx.x & 7);
+    tile = rev ? nt - 1 - i % nt : i % nt;
+    hd = rest % a.heads;
+    sq = rest / a.heads;
+    return;
+  }
   const int u = (int)(blockIdx.x / per), rest = (int)(blockIdx.x % per);
   const int h = (nt + 1) / 2;
   const int r = a.pair && u >= h ? nt - 1 - (u - h) : u;  // rank in work order
@@ -256,7 +269,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 4) void attn_fwd_kernel(Att
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6),
             h2 = lane >> 5, lq = lane & 31;
   int qt, hd, sq;
-  decode(a, CAUSAL, qt, hd, sq, QB);
+  decode(a, CAUSAL, a.shared != 0, qt, hd, sq, QB);
   const long tok0 = (long)sq * a.N, ld = 3L * a.M;
   const bf16_t* Qg = a.qkv + tok0 * ld + (long)hd * D;
   const bf16_t* Kg = Qg + a.M;
@@ -529,7 +542,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6),
             h2 = lane >> 5, lq = lane & 31;
   int qt, hd, sq;
-  decode(a, CAUSAL, qt, hd, sq, QB);
+  decode(a, CAUSAL, a.shared != 0, qt, hd, sq, QB);
   const long tok0 = (long)sq * a.N, ld = 3L * a.M;
   const bf16_t* Qg = a.qkv + tok0 * ld + (long)hd * D;
   const bf16_t* Kg = Qg + a.M;
@@ -718,7 +731,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkdv_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6),
             h2 = lane >> 5, lq = lane & 31;
   int kt, hd, sq;
-  decode(a, false, kt, hd, sq, KB);
+  decode(a, false, false, kt, hd, sq, KB);
   const long tok0 = (long)sq * a.N, ld = 3L * a.M;
   const bf16_t* Qg = a.qkv + tok0 * ld + (long)hd * D;
   const bf16_t* Gg = a.d_o + tok0 * a.M + (long)hd * D;
@@ -887,6 +900,27 @@ bool fwd_wide(const AttnArgs& a) {
   return attn_blocks(a, 256) >= 4u * 256u && 2 * attn_blocks(a, 256) == attn_blocks(a);
 }
 
+// Query tiles of a head side by side (decode)? Bidirectional ones have equal work and
+// lose nothing by it: 64 sequences of 512, 16 heads of 128, forward 263 -> 198 us (227
+// with the 8-wave blocks before the one-tile-ahead loop, which read K and V half as
+// often), dQ 378 -> 301; 4 x 4096, 32 heads 1110 -> 1013 and 1646 -> 1521; one sequence
+// of 4096 the same. Causal tiles then no longer run longest first over the whole launch,
+// which costs up to 40 % where K and V stay in the 256 MB Infinity Cache; the forward
+// takes it where they do not (kv: their bytes) and the tiles of a head are few, or far
+// past it (T = 65536, heads of 128, width 2048: N = 512 421 -> 349 us, 1024 632 -> 447, 2048
+// 1004 -> 717, 4096 1345 -> 1208; half of that 199 -> 182, 261 -> 227, 375 -> 351, and
+// 580 -> 592 for 4096; N = 300, 189 MB, heads of 128 and 64, 143 -> 120 and 163 -> 129).
+// 8-wave blocks have half as many tiles and gain little (2-4 %) or lose up to 12 %.
+// The key tiles of dK and dV gain 11 % and lose 8 % on the bidirectional shapes, and
+// keep their order.
+bool shared_order(const AttnShape& m, const AttnArgs& a) {
+  if (!m.causal) return true;
+  if (m.D == 64 && fwd_wide(a)) return false;
+  const long mb = 1L << 20, kv = 4L * a.T * a.M, nt = (a.N + 127) / 128;
+  return kv >= 448 * mb || (kv >= 176 * mb && nt <= 3) ||
+         (kv >= 240 * mb && m.D == 128 && nt <= 16);
+}
+
 template <int D, int NW>
 void launch_fwd(const AttnShape& m, const AttnArgs& a, hipStream_t st) {
   const dim3 g(attn_blocks(a, 32 * NW)), b(64 * NW);
@@ -916,6 +950,7 @@ hipError_t launch_attn_fwd(const AttnShape& m, int T, int M, const void* qkv, vo
   a.out = static_cast<bf16_t*>(o);
   a.lse = lse;
   a.pair = attn_pair(m, a);
+  a.shared = shared_order(m, a);
   return traced(FLOWMOE_K_ATTN_FWD, st, [&] {
     if (m.D == 128) launch_fwd<128, 4>(m, a, st);
     else if (fwd_wide(a)) launch_fwd<64, 8>(m, a, st);
@@ -935,6 +970,7 @@ hipError_t launch_attn_bwd(const AttnShape& m, int T, int M, const void* qkv, co
   a.lse = const_cast<float*>(lse);
   a.delta = delta;
   a.pair = attn_pair(m, a);
+  a.shared = !m.causal;
   hipError_t e = traced(FLOWMOE_K_ATTN_BWD_DQ, st, [&] { FLOWMOE_ATTN_LAUNCH(attn_dq_kernel, a, st); });
   if (e != hipSuccess) return e;
   return traced(FLOWMOE_K_ATTN_BWD_DKDV, st,

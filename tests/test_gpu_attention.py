@@ -149,6 +149,33 @@ def test_attention_row_sum_order(hd, causal):
         assert abs(got[t] - want) < 2e-7, (t, got[t], want)
 
 
+@pytest.mark.parametrize("N,nseq,hd", [(300, 80, 128), (300, 80, 64), (1100, 30, 128)])
+def test_attention_forward_of_many_sequences(N, nseq, hd):
+    """Causal launches whose K and V exceed the Infinity Cache walk the query tiles of a
+    head side by side (few tiles of a head, or up to 16 of heads of 128): the
+    same bits as the sequences in launches of one, which walk them longest first."""
+    need_gpu()
+    L = _lib()
+    d = dev()
+    heads = 2048 // hd
+    T, M = nseq * N, 2048
+    g = torch.Generator(device=d).manual_seed(N)
+    qkv = torch.randn(T, 3 * M, generator=g, device=d, dtype=torch.bfloat16)
+    m = L.make_mha_shape(N, heads, hd, True)
+
+    def run(q):
+        o = torch.zeros(q.shape[0], M, dtype=torch.bfloat16, device=d)
+        lse = torch.zeros(heads, q.shape[0], device=d)
+        L.flowmoe_attention_fwd(L.make_shape(q.shape[0], M, 64, 1, 1, 0, L.BF16), m, q, o, lse)
+        return o, lse
+
+    o, lse = run(qkv)
+    for i in range(nseq):
+        r = slice(i * N, (i + 1) * N)
+        o1, lse1 = run(qkv[r].contiguous())
+        assert torch.equal(o[r], o1) and torch.equal(lse[:, r], lse1), i
+
+
 def test_attention_is_deterministic():
     need_gpu()
     r1 = run_core(512, 256, 256, 2, True, 11)[1]
