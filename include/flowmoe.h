@@ -325,7 +325,8 @@ int32_t flowmoe_trace_stop(void);
  * smallest of 128 x 128, 256 x 128 and 256 x 256 tiles that run as one round of
  * the compute units, else 256 x 256, by the counts it finds on the device; the
  * weight gradients take 256 x 128 tiles where those do. WIDE and NARROW
- * force 256 x 256 or 256 x 128 (the SwiGLU forward has no 256 x 128 tile). Every
+ * force 256 x 256 or 256 x 128 (the SwiGLU forward has no 256 x 128 tile; its
+ * smallest is 128 x 64 of each of its two projections, chosen by the shape). Every
  * shape accumulates every output in the same k order: results are
  * bit-identical. */
 enum { FLOWMOE_TILES_AUTO = 0, FLOWMOE_TILES_WIDE = 1, FLOWMOE_TILES_NARROW = 2 };

@@ -272,7 +272,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
   constexpr int BN = 128 * NB;
   // items of a row: 8 outputs (dual: of each of h1, h3 and a), or 4 fp32 ones
-  constexpr int IPR = DUAL ? 16 : MODE == MODE_KSUM ? BN / 4 : BN / 8;
+  constexpr int IPR = DUAL ? BN / 16 : MODE == MODE_KSUM ? BN / 4 : BN / 8;
   constexpr int PER = 16 * IPR / 64;  // items a lane and half; all of one column group
   static_assert(64 % IPR == 0, "one column group per lane");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -389,7 +389,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, floatx16 (&ac
         }
         if constexpr (DUAL) {
           float h3[8], a[8];
-          read8(rr, 16 + cg, h3);
+          read8(rr, IPR + cg, h3);
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
             h3[q] = data ? h3[q] + bias1[q] : 0.f;
@@ -505,6 +505,21 @@ __device__ __forceinline__ bf16x8 half_frag(const char* h, int base, int i, int 
   }
 }
 
+// The same of a quarter tile [64 k][64 columns]: 128-byte rows, chunk m of k-row k at
+// m ^ (4 (k / 2 % 2)) (four k-rows of 64 bytes fall into distinct banks).
+__device__ __forceinline__ int quarter_base(int r0, int lane) {
+  const int G = lane >> 4, sl = lane & 15;
+  const int col = r0 + (G & 1) * 16 + 4 * (sl & 3), kr = (G >> 1) * 8 + (sl >> 2);
+  return kr * 128 + (((col >> 3) ^ ((kr & 2) << 1)) << 4) + ((col & 7) << 1);
+}
+__device__ __forceinline__ bf16x8 quarter_frag(const char* q, int base, int kk) {
+  const char* a = q + base + kk * 2048;
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)a);
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a + 512));
+  const short __attribute__((ext_vector_type(8))) v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 constexpr int kGemmSmem = 9 * kHalf;  // 144 KB
 
 // One tile of the kernels below. BM = 128: low tiles (row mode), light loops only.
@@ -513,7 +528,10 @@ template <int MODE, bool A_KC, bool B_KC, int EPI, bool NARROW, int BM, bool PIE
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int ntiles, const LaneRows& lr) {
   constexpr int BN = NARROW ? 128 : 256;
   constexpr bool DUAL = EPI == EPI_SWIGLU_FWD;
-  static_assert(!DUAL || !NARROW, "the dual forward pairs 128-column W1 and W3 halves");
+  // the dual forward pairs 128-column W1 and W3 halves; narrow, the two 64-column
+  // quarters of one half
+  constexpr bool QUARTERS = DUAL && NARROW;
+  static_assert(!QUARTERS || BM == 128, "quarters in the light loops only");
   // k-tiles in LDS (stages), the halves of one (A0, A1, B0 and wide B1) and its bytes
   constexpr int NST = NARROW ? 3 : 2, NB = NARROW ? 1 : 2, STB = (2 + NB) * kHalf;
   constexpr int SMEM = kGemmSmem;
@@ -558,7 +576,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
   const int mnc_k = 4 * wave + (lane >> 4);
   const int mnc_c = ((lane & 15) ^ ((lane >> 4) << 2)) * 8;
   const unsigned aoff = (unsigned)(A_KC ? ((long)kc_row * p.lda + kc8) * 2 : ((long)mnc_k * p.lda + mnc_c) * 2);
-  const unsigned boff = (unsigned)(B_KC ? ((long)kc_row * p.ldb + kc8) * 2 : ((long)mnc_k * p.ldb + mnc_c) * 2);
+  // (quarters: 8 k-rows of 8 chunks a block)
+  const unsigned boff = (unsigned)(B_KC ? ((long)kc_row * p.ldb + kc8) * 2
+                                   : QUARTERS
+                                       ? ((long)kc_row * p.ldb + ((lane & 7) ^ ((lane >> 4 & 1) << 2)) * 8) * 2
+                                       : ((long)mnc_k * p.ldb + mnc_c) * 2);
   // byte steps: second block of a half, second half, k-tile
   const unsigned a_blk = (unsigned)((A_KC ? 64 : 32) * p.lda * 2), a_half = (unsigned)(A_KC ? 128 * p.lda * 2 : 256);
   const unsigned b_blk = (unsigned)((B_KC ? 64 : 32) * p.ldb * 2),
@@ -661,6 +683,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
       const bool sec = t >= nk0;
       const int k0 = (sec ? t - nk0 : t) * WBK, lim = (sec ? p.K - p.ksplit : k_lim) - k0;
       issue(sec ? rb1 : rb0, dst, boff, (unsigned)(k0 * 2) + h * b_half, b_blk, true, lim);
+    } else if constexpr (QUARTERS) {
+      issue(rb0, dst, boff, (unsigned)t * b_kt, 0, false, 0, false);
+      issue(rb1, dst + 8192, boff, (unsigned)t * b_kt, 0, false, 0, false);
     } else {
       issue((DUAL && h) ? rb1 : rb0, dst, boff, (unsigned)t * b_kt + h * b_half, b_blk, false, 0);
     }
@@ -686,7 +711,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
     asm volatile("" ::: "memory");
   };
 
-  int abase = half_base(A_KC, wm * 64, lane), bbase = half_base(B_KC, wn * 32, lane);
+  int abase = half_base(A_KC, wm * 64, lane);
+  int bbase = QUARTERS ? (wn >> 1) * 8192 + quarter_base((wn & 1) * 32, lane) : half_base(B_KC, wn * 32, lane);
   auto k_loop = [&](auto nh_c) {
     constexpr int NH = decltype(nh_c)::value;  // live A halves of this wave
     // [half][32-row block][k step]; [half (wide) or tile parity (narrow)][k step]
@@ -833,7 +859,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, char* smem, int n
 #pragma unroll
         for (int i = 0; i < 2; ++i) af[set][i][kk] = half_frag<A_KC>(sa, abase, i, kk);
 #pragma unroll
-        for (int h = 0; h < NB; ++h) bfr[set][h][kk] = half_frag<B_KC>(sa + AB + h * kHalf, bbase, 0, kk);
+        for (int h = 0; h < NB; ++h) {
+          if constexpr (QUARTERS) bfr[set][h][kk] = quarter_frag(sa + AB, bbase, kk);
+          else bfr[set][h][kk] = half_frag<B_KC>(sa + AB + h * kHalf, bbase, 0, kk);
+        }
       }
     };
     if (nk == 0) return;
@@ -977,6 +1006,22 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_rows_kernel(GemmParams p) {
   else if (shape == FLOWMOE_TILES_WIDE || DUAL)
     gemm_tile<MODE_ROWS, true, B_KC, EPI, false, 256>(p, smem, n256, lr);
   else if constexpr (!DUAL) gemm_tile<MODE_ROWS, true, B_KC, EPI, true, 256>(p, smem, n128, lr);
+}
+
+// The dual forward in tiles of 128 x (64 + 64), for launches of few tiles: a k-tile is
+// half the weights of a 128 x (128 + 128) one, so the chain of them is shorter and more
+// of it in flight, on twice the CUs. A kernel of its own: beside the other shapes in
+// the kernel above it made their loops up to 11 % slower (64 experts of 100 rows, M =
+// 2048, H = 1408: 208 -> 233 us).
+__global__ __launch_bounds__(512, 2) void gemm_bf16_pair64_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem[kGemmSmem];
+  const int lane = threadIdx.x & 63;
+  const bool live = lane < p.E;
+  LaneRows lr;
+  lr.c = live ? seg_count(p, 0, lane) : 0;
+  lr.o = live ? seg_offset(p, 0, lane) : 0;
+  lr.r = live ? (p.padC ? p.padC : lr.c) : 0;
+  gemm_tile<MODE_ROWS, true, false, EPI_SWIGLU_FWD, true, 128>(p, smem, (p.N + 63) / 64, lr);
 }
 
 // The row mode over a B that exceeds a buffer descriptor's range (an expert's
@@ -1415,6 +1460,23 @@ hipError_t run_rows(int kind, const Shape& s, GemmParams p, hipStream_t st) {
   p.joined = order == FLOWMOE_TILE_ORDER_JOINED ||
              (order == FLOWMOE_TILE_ORDER_AUTO && wbytes > 256.0 * 1024 * 1024 &&
               s.rows <= 2048L * s.E);
+  if constexpr (DUAL) {
+    // Tiles of 128 x (64 + 64) where all of them run at once, by the rows' bound and
+    // the experts' capacity (the grid covers the first, whatever the counts are). us
+    // of 128 x (128 + 128) and of these, experts x rows, M, H: 8 x 93, 4928, 320 (40
+    // tiles) 91 and 44; 1 x 1000, 4096, 1024 (128) 78 and 40; 1 x 64, 4096, 14336
+    // (224) 118 and 103; 8 x 128, 4096, 2048 (256) 143 and 114. In two rounds they
+    // gain nothing: 16 x 250, 1024, 704 (352) 31.3 and 31.2; 8 x 128, 1024, 2816
+    // (352) 39 and 40; 8 x 100, 4096, 3000 (376) 157 and 163; 8 x 128, 4096, 4096
+    // (512) 163 and 189.
+    const long n64 = (p.N + 63) / 64, bound = rows_tiles_bound(s, 128);
+    const long tiles64 = std::min(bound, (long)s.E * ((s.C + 127) / 128)) * n64;
+    if (g_tiles.load(std::memory_order_relaxed) == FLOWMOE_TILES_AUTO && !pieces && tiles64 <= kCUs)
+      return traced(kind, st, [&] {
+        hipLaunchKernelGGL(gemm_bf16_pair64_kernel, dim3((unsigned)row_mode_blocks(bound * n64)), dim3(512), 0,
+                           st, p);
+      });
+  }
   return traced(kind, st, [&] {
     if constexpr (!B_KC)
       if (pieces) {

@@ -841,18 +841,24 @@ def test_expert_ffn_bf16_row_classes(M, H, act, layout, gemm_tiles):
 
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 @pytest.mark.parametrize("cnt", [[0, 1, 63, 64, 65, 127, 128, 129, 192, 255, 256, 257], [128] * 16,
-                                 [128] * 15 + [129], [256] * 16, [256] * 15 + [257]])
+                                 [128] * 15 + [129], [256] * 16, [256] * 15 + [257],
+                                 [0, 65, 130, 200]])
 @pytest.mark.parametrize("layout", ["packed", "padded"])
-def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
+@pytest.mark.parametrize("M,H", [(72, 2048), (712, 520)])
+def test_expert_ffn_bf16_chosen_shape(M, H, cnt, act, layout, gemm_tiles):
     """The tile shape the row kernel chooses from the counts (padded: from the
     capacity): every row class of the 128 x 128 tiles, and with 16 column tiles
     the last launch of one round and the first of more for the 128- and the
     256-row tiles. The weight gradients have 192 and 256 narrow tiles (one round),
-    384 and 512 (SwiGLU's dW1 | dW3). Forward, input and weight gradients
-    bit-identical to the forced 256 x 256 tiles, h against 64 bits."""
+    384 and 512 (SwiGLU's dW1 | dW3). At H = 520 the SwiGLU forward takes its
+    128 x (64 + 64) tiles for packed rows of every class, for 16 experts of 128 and,
+    with padding, for four of up to 200 (9 column tiles, the last of 8 columns; 12
+    k-tiles through 4 or 6 stages; at H = 2048 those four have 256 tiles, the most that
+    take them); 288 tiles of the others are too many. Forward, input and weight gradients bit-identical to the forced
+    256 x 256 tiles, h against 64 bits."""
     need_gpu()
     d, bf = dev(), torch.bfloat16
-    E, M, H, T, C = len(cnt), 72, 2048, sum(cnt), max(cnt)
+    E, T, C = len(cnt), sum(cnt), max(cnt)
     rt = oracle.route(np.repeat(np.arange(E), cnt)[:, None], E, C, layout)
     rows, HW = rt["rows"], 2 * H if act == "swiglu" else H
     rng = np.random.default_rng(5)
@@ -883,7 +889,7 @@ def test_expert_ffn_bf16_chosen_shape(cnt, act, layout, gemm_tiles):
     h = host(got["auto"]["h"])
     for e, (o, c) in enumerate(zip(rt["offsets"], cnt)):
         ref = host(x[o:o + c]) @ np.concatenate([host(w[e]) for w in (w1, w3) if w is not None], axis=1)
-        # one rounding to bf16 (2^-9) of an fp32 sum of 72 products
+        # one rounding to bf16 (2^-9) of an fp32 sum of M products
         assert_close(h[o:o + c], ref, "bf16", f"h[{e}]", tol=2.0 ** -8)
 
 
