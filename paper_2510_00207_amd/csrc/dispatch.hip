@@ -327,9 +327,9 @@ __host__ __device__ constexpr int row_steps() {
 // Memory bounds it. A wave per token walking its segments one after the other
 // left the chip to 16 waves a CU that load and drain in step: with a wave a
 // segment, the token in scalar registers and arrays of 6 for k = 5 and 6, T = 4096,
-// M = 2048, k = 6: combine, its backward, dispatch and gate backward 135 -> 127 us
-// (the scalar token and the arrays of 6 alone: 134.7), and 122 with the combine
-// backward split alike. A grid's x has four tokens a block by segs of their segments, all
+// M = 2048, k = 6: combine, its backward, dispatch and gate backward 133 -> 122 us in
+// turn on one box (about 6 of it the combine's segments and 5 its backward's; the
+// scalar token and the arrays of 6 under 1). A grid's x has four tokens a block by segs of their segments, all
 // of them unless the call has too many tokens for that; y has the rest. GATE
 // (dispatch backward of the layer): also adds the gate's share dl_t W_g^T,
 // with dl_t taken from the selection (gidx), its weights (gw) and their
